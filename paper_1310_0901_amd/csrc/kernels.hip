@@ -1955,33 +1955,41 @@ __global__ void __launch_bounds__(256) k_small_reset(SmallAcc *acc, uint64_t n)
 // ---------------------------------------------------------------------------
 // A small upload from coherent host memory: one block copies n 8-byte words
 // with system-scope loads (they observe the host's latest writes); for the
-// few kilobytes of a table delta, a context state or fill ranges, a launch
-// waits less than a DMA copy.
+// kilobytes of a table delta or of fill ranges that are too many for a
+// launch's arguments, a launch waits less than a DMA copy.
 __global__ void __launch_bounds__(256) k_upload(const uint64_t *src, uint64_t *dst, uint64_t n)
 {
     for (uint64_t i = threadIdx.x; i < n; i += 256)
         dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// One block sets one range (pieces of at most 1 MiB): bytes to the first
+// 16-byte boundary, 16-byte stores, the last bytes.
+__device__ __forceinline__ void fill_range(const FillRange &fr)
+{
+    uint8_t *p = reinterpret_cast<uint8_t *>(fr.ptr);
+    const uint8_t v = (uint8_t)fr.val;
+    const uint64_t len = fr.len;
+    uint64_t head = (16u - (fr.ptr & 15u)) & 15u;
+    head = head < len ? head : len;
+    if (threadIdx.x < head) p[threadIdx.x] = v;
+    const uint64_t body = (len - head) & ~15ull;
+    const uint32_t w = 0x01010101u * v;
+    const u32x4 vv{w, w, w, w};
+    for (uint64_t o = head + 16ull * threadIdx.x; o < head + body; o += 16ull * blockDim.x)
+        *reinterpret_cast<u32x4 *>(p + o) = vv;
+    const uint64_t tail = len - head - body;
+    if (threadIdx.x < tail) p[head + body + threadIdx.x] = v;
+}
+
 __global__ void __launch_bounds__(256) k_fill(const FillRange *ranges, uint64_t k)
 {
-    for (uint64_t i = blockIdx.x; i < k; i += gridDim.x) {
-        const FillRange fr = ranges[i];
-        uint8_t *p = reinterpret_cast<uint8_t *>(fr.ptr);
-        const uint8_t v = (uint8_t)fr.val;
-        const uint64_t len = fr.len;
-        uint64_t head = (16u - (fr.ptr & 15u)) & 15u;
-        head = head < len ? head : len;
-        if (threadIdx.x < head) p[threadIdx.x] = v;
-        const uint64_t body = (len - head) & ~15ull;
-        const uint32_t w = 0x01010101u * v;
-        const u32x4 vv{w, w, w, w};
-        for (uint64_t o = head + 16ull * threadIdx.x; o < head + body; o += 16ull * blockDim.x)
-            *reinterpret_cast<u32x4 *>(p + o) = vv;
-        const uint64_t tail = len - head - body;
-        if (threadIdx.x < tail) p[head + body + threadIdx.x] = v;
-    }
+    for (uint64_t i = blockIdx.x; i < k; i += gridDim.x) fill_range(ranges[i]);
 }
+
+// The ranges of one allocation, or of a few fills, read from the launch's
+// arguments: no upload before the fill.
+__global__ void __launch_bounds__(256) k_fill_inline(FillArgs f) { fill_range(f.r[blockIdx.x]); }
 
 __global__ void __launch_bounds__(256) k_probe_read(const u32x4 *p, uint64_t n16, uint64_t *sink)
 {
@@ -2184,6 +2192,14 @@ hipError_t launch_fill(const FillRange *ranges_dev, uint64_t k, hipStream_t s)
     if (k == 0) return hipSuccess;
     const uint32_t grid = (uint32_t)(k < 65536 ? k : 65536);
     hipLaunchKernelGGL(k_fill, dim3(grid), dim3(256), 0, s, ranges_dev, k);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_inline(const FillArgs &f, uint64_t k, hipStream_t s)
+{
+    if (k == 0) return hipSuccess;
+    if (k > kFillInline) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_fill_inline, dim3((uint32_t)k), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 

@@ -164,15 +164,11 @@ struct cg_ctx {
     std::set<uint64_t> pend_del;
     std::map<uint64_t, AllocEntry> pend_ins;
     uint64_t *d_delta = nullptr;   // sorted deletes | inserted base | end | off
-    uint8_t *m_keep = nullptr;
-    uint32_t *m_loc = nullptr;
-    uint64_t *m_bsum = nullptr, *m_boff = nullptr;
     uint64_t *h_stage = nullptr;   // pinned staging for table uploads and large deltas
-    // coherent host staging that small uploads read from the device (k_upload):
-    // a table delta of up to kDeltaWords words and the context state; m_* are
-    // the device's addresses of the same memory
+    // coherent host staging of a table delta of up to kDeltaWords words, read
+    // from the device (k_upload) at its device address m_delta
     uint64_t *h_delta = nullptr, *m_delta = nullptr;
-    DevState *h_state = nullptr, *m_state = nullptr;
+    DevState state{};              // of the current version
     hipEvent_t ev_stage = nullptr;
     bool stage_busy = false;
     uint64_t versions_made = 0, merges = 0, full_uploads = 0;
@@ -270,10 +266,6 @@ int wait_ctx(cg_ctx *c, Workspace *w, hipStream_t s)
 int materialize(cg_ctx *c)
 {
     if (!c->full_dirty && c->pend_del.empty() && c->pend_ins.empty()) return CG_OK;
-    if (c->stage_busy) {
-        HIPTRY(c, hipEventSynchronize(c->ev_stage));
-        c->stage_busy = false;
-    }
     const int t = (c->cur + 1) % kVersions;
     TableVersion &nv = c->ver[t], &ov = c->ver[c->cur];
     for (auto &kv : nv.uses) HIPTRY(c, hipStreamWaitEvent(c->s, kv.second, 0));
@@ -285,46 +277,15 @@ int materialize(cg_ctx *c)
     const uint32_t ntop = (uint32_t)((n + (1ull << shift) - 1) >> shift);
     const uint64_t nd = c->pend_del.size(), ni = c->pend_ins.size();
     const bool full = c->full_dirty || nd + 3 * ni > 3 * M || (nd + ni) * 4 > n + 64;
-    uint64_t *hs = c->h_stage;
-    if (full) {
-        uint64_t *hb = hs, *he = hb + M, *ho = he + M, *ht = ho + M;
-        c->table.export_sorted(hb, he, ho);
-        for (uint32_t k = 0; k < ntop; ++k) ht[k] = hb[(uint64_t)k << shift];
-        if (n) {
-            HIPTRY(c, hipMemcpyAsync(nv.tab, hb, n * 8, hipMemcpyHostToDevice, c->s));
-            HIPTRY(c, hipMemcpyAsync(nv.tab + M, he, n * 8, hipMemcpyHostToDevice, c->s));
-            HIPTRY(c, hipMemcpyAsync(nv.tab + 2 * M, ho, n * 8, hipMemcpyHostToDevice, c->s));
-            HIPTRY(c, hipMemcpyAsync(nv.tab + 3 * M, ht, ntop * 8ull, hipMemcpyHostToDevice, c->s));
-        }
-        c->full_uploads++;
-    } else {
-        const uint64_t words = nd + 3 * ni;
-        const bool small = words <= kDeltaWords;
-        if (small) hs = c->h_delta;
-        uint64_t *hd = hs, *hib = hd + nd, *hie = hib + ni, *hio = hie + ni;
-        size_t k = 0;
-        for (uint64_t b : c->pend_del) hd[k++] = b;
-        k = 0;
-        for (const auto &kv : c->pend_ins) {
-            hib[k] = kv.first;
-            hie[k] = kv.first + kv.second.size;
-            hio[k] = kv.second.off;
-            ++k;
-        }
-        if (small) HIPTRY(c, launch_upload(c->m_delta, c->d_delta, words * 8, c->s));
-        else HIPTRY(c, hipMemcpyAsync(c->d_delta, hs, words * 8, hipMemcpyHostToDevice, c->s));
-        MergeArgs m{};
-        m.old_base = ov.tab; m.old_end = ov.tab + M; m.old_off = ov.tab + 2 * M; m.n_old = ov.n;
-        m.del = c->d_delta; m.n_del = nd;
-        m.ins_base = c->d_delta + nd; m.ins_end = c->d_delta + nd + ni; m.ins_off = c->d_delta + nd + 2 * ni;
-        m.n_ins = ni;
-        m.new_base = nv.tab; m.new_end = nv.tab + M; m.new_off = nv.tab + 2 * M; m.new_top = nv.tab + 3 * M;
-        m.top_shift = shift; m.ntop = ntop;
-        m.keep = c->m_keep; m.loc = c->m_loc; m.bsum = c->m_bsum; m.boff = c->m_boff;
-        HIPTRY(c, launch_merge(m, c->s));
-        c->merges++;
+    // a change that fits the merge's own arguments needs no staging; any other
+    // waits until the staging buffers' last upload is done
+    const uint64_t words = nd + 3 * ni;
+    const bool in_words = !full && words <= kMergeInline;
+    if (!in_words && c->stage_busy) {
+        HIPTRY(c, hipEventSynchronize(c->ev_stage));
+        c->stage_busy = false;
     }
-    DevState &st = *c->h_state;
+    DevState &st = c->state;
     st.table.base = nv.tab;
     st.table.end = nv.tab + M;
     st.table.off = nv.tab + 2 * M;
@@ -336,9 +297,51 @@ int materialize(cg_ctx *c)
     st.pool = (uint64_t)c->pool;
     st.size_bound = c->table.size_bound();
     st.pool_len = c->palloc->high();
-    HIPTRY(c, launch_upload(c->m_state, nv.st, sizeof(DevState), c->s));
-    HIPTRY(c, hipEventRecord(c->ev_stage, c->s));
-    c->stage_busy = true;
+    uint64_t *hs = c->h_stage;
+    if (full) {
+        uint64_t *hb = hs, *he = hb + M, *ho = he + M, *ht = ho + M;
+        c->table.export_sorted(hb, he, ho);
+        for (uint32_t k = 0; k < ntop; ++k) ht[k] = hb[(uint64_t)k << shift];
+        if (n) {
+            HIPTRY(c, hipMemcpyAsync(nv.tab, hb, n * 8, hipMemcpyHostToDevice, c->s));
+            HIPTRY(c, hipMemcpyAsync(nv.tab + M, he, n * 8, hipMemcpyHostToDevice, c->s));
+            HIPTRY(c, hipMemcpyAsync(nv.tab + 2 * M, ho, n * 8, hipMemcpyHostToDevice, c->s));
+            HIPTRY(c, hipMemcpyAsync(nv.tab + 3 * M, ht, ntop * 8ull, hipMemcpyHostToDevice, c->s));
+        }
+        HIPTRY(c, launch_state(st, nv.st, c->s));
+        c->full_uploads++;
+    } else {
+        MergeArgs m{};
+        const bool small = words <= kDeltaWords;
+        if (in_words) hs = m.words;
+        else if (small) hs = c->h_delta;
+        uint64_t *hd = hs, *hib = hd + nd, *hie = hib + ni, *hio = hie + ni;
+        size_t k = 0;
+        for (uint64_t b : c->pend_del) hd[k++] = b;
+        k = 0;
+        for (const auto &kv : c->pend_ins) {
+            hib[k] = kv.first;
+            hie[k] = kv.first + kv.second.size;
+            hio[k] = kv.second.off;
+            ++k;
+        }
+        if (in_words) m.in_words = 1;
+        else if (small) HIPTRY(c, launch_upload(c->m_delta, c->d_delta, words * 8, c->s));
+        else HIPTRY(c, hipMemcpyAsync(c->d_delta, hs, words * 8, hipMemcpyHostToDevice, c->s));
+        m.old_base = ov.tab; m.old_end = ov.tab + M; m.old_off = ov.tab + 2 * M; m.n_old = ov.n;
+        m.del = c->d_delta; m.n_del = nd;
+        m.ins_base = c->d_delta + nd; m.ins_end = c->d_delta + nd + ni; m.ins_off = c->d_delta + nd + 2 * ni;
+        m.n_ins = ni;
+        m.new_base = nv.tab; m.new_end = nv.tab + M; m.new_off = nv.tab + 2 * M; m.new_top = nv.tab + 3 * M;
+        m.top_shift = shift;
+        m.state = st; m.state_out = nv.st;
+        HIPTRY(c, launch_merge(m, c->s));
+        c->merges++;
+    }
+    if (!in_words) {
+        HIPTRY(c, hipEventRecord(c->ev_stage, c->s));
+        c->stage_busy = true;
+    }
     nv.n = n;
     c->cur = t;
     c->pend_del.clear();
@@ -386,6 +389,13 @@ int issue_fills(cg_ctx *c, const std::vector<FillRange> &rs, bool after_checks)
     if (after_checks) {
         int rc = ctx_begin(c);
         if (rc) return rc;
+    }
+    if (!rs.empty() && rs.size() <= kFillInline) {
+        // a few ranges travel in the launch's arguments: no staging, no upload
+        FillArgs a{};
+        std::copy(rs.begin(), rs.end(), a.r);
+        HIPTRY(c, launch_fill_inline(a, rs.size(), c->s));
+        return ctx_end(c);
     }
     while (i < rs.size()) {
         const int f = c->fill_next;
@@ -1116,16 +1126,9 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
         if (hipMalloc(&v.st, sizeof(DevState)) != hipSuccess) return bail(CG_ENOMEM);
     }
     if (hipMalloc(&c->d_delta, (3 * max_allocs + kMaxTop) * 8) != hipSuccess) return bail(CG_ENOMEM);
-    if (hipMalloc(&c->m_keep, max_allocs) != hipSuccess) return bail(CG_ENOMEM);
-    if (hipMalloc(&c->m_loc, max_allocs * 4) != hipSuccess) return bail(CG_ENOMEM);
-    if (hipMalloc(&c->m_bsum, (max_allocs / 256 + 2) * 8) != hipSuccess) return bail(CG_ENOMEM);
-    if (hipMalloc(&c->m_boff, (max_allocs / 256 + 2) * 8) != hipSuccess) return bail(CG_ENOMEM);
     if (hipHostMalloc(&c->h_stage, (3 * max_allocs + kMaxTop) * 8, hipHostMallocDefault) != hipSuccess)
         return bail(CG_ENOMEM);
     const unsigned coh = hipHostMallocMapped | hipHostMallocCoherent;
-    if (hipHostMalloc(&c->h_state, sizeof(DevState), coh) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&c->m_state, c->h_state, 0) != hipSuccess)
-        return bail(CG_ENOMEM);
     if (hipHostMalloc(&c->h_delta, kDeltaWords * 8, coh) != hipSuccess ||
         hipHostGetDevicePointer((void **)&c->m_delta, c->h_delta, 0) != hipSuccess)
         return bail(CG_ENOMEM);
@@ -1216,13 +1219,8 @@ int cg_destroy(cg_ctx *c)
     for (auto &f : c->inflight) (void)hipEventDestroy(f.ev);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
     (void)hipFree(c->d_delta);
-    (void)hipFree(c->m_keep);
-    (void)hipFree(c->m_loc);
-    (void)hipFree(c->m_bsum);
-    (void)hipFree(c->m_boff);
     (void)hipFree(c->d_fill);
     if (c->h_stage) (void)hipHostFree(c->h_stage);
-    if (c->h_state) (void)hipHostFree(c->h_state);
     if (c->h_delta) (void)hipHostFree(c->h_delta);
     if (c->h_fill) (void)hipHostFree(c->h_fill);
     if (c->ev_stage) (void)hipEventDestroy(c->ev_stage);
@@ -1615,7 +1613,7 @@ int cg_table_read(cg_ctx *c, uint64_t *base, uint64_t *end, uint64_t *off, uint6
     if (!rc) rc = materialize(c);
     if (rc) return rc;
     const TableVersion &v = c->ver[c->cur];
-    const DevState &st = *c->h_state;
+    const DevState &st = c->state;
     const uint64_t M = c->max_allocs;
     if (v.n > cap || st.table.ntop > top_cap) return fail(c, CG_EINVAL, "cg_table_read: buffers too small");
     HIPTRY(c, hipStreamSynchronize(c->s));

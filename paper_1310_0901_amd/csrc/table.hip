@@ -4,14 +4,25 @@
 // plus the allocations made since; the result goes to another buffer of the
 // version ring, so checks still in flight keep reading their own version.
 //
-//   k_merge_keep     one lane per old entry: keep flag (not freed), block-local
-//                    exclusive scan of the flags, block sums
-//   k_merge_sums     one block: exclusive scan of the block sums
-//   k_merge_scatter  one lane per kept old entry or inserted entry: its index
-//                    in the new table = kept entries before it + inserted
-//                    entries before it
-//   k_merge_top      every 2^shift-th base of the new table (LDS top level)
+//   k_merge        one lane per old entry: its index in the new table is its
+//                  old index, less the frees below it, plus the inserts below
+//                  it, and the entries that fall on every 2^shift-th index
+//                  also go to the top level; the version's DevState is written
+//                  by the first block
+//   k_state        the DevState alone (a version uploaded whole)
+//
+// Every freed base is in the old table, so "frees below" is a search in the
+// sorted frees and no scan over the old entries is needed.  Bound by latency
+// for tables of up to 100,000 entries (one launch, about 4 us), by the copy of
+// the table (48 B per entry) above.  A change of a few allocations, the usual
+// one when a server applies one event at a time, travels in the launch's own
+// arguments: a version then takes one launch, where two uploads from host
+// memory and four merge kernels took a chain of about 20 us and the host
+// waited for the staging buffer of the version before (20,000 requests with
+// 2,000 such events over 100,000 allocations: 145 -> 92 ms).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "xc_internal.h"
 
@@ -20,8 +31,9 @@ namespace {
 
 constexpr int kB = 256;
 
-// number of entries of a[0..n) that are < x (a sorted ascending)
-__device__ __forceinline__ uint64_t lower_bound(const uint64_t *a, uint64_t n, uint64_t x)
+// number of entries of a[0..n) that are < x / <= x (a sorted ascending)
+template <typename P>
+__device__ __forceinline__ uint64_t lower_bound(P a, uint64_t n, uint64_t x)
 {
     uint64_t lo = 0, hi = n;
     while (lo < hi) {
@@ -31,115 +43,100 @@ __device__ __forceinline__ uint64_t lower_bound(const uint64_t *a, uint64_t n, u
     return lo;
 }
 
-__global__ void __launch_bounds__(kB) k_merge_keep(MergeArgs m)
+template <typename P>
+__device__ __forceinline__ uint64_t upper_bound(P a, uint64_t n, uint64_t x)
 {
-    __shared__ uint32_t wsum[kB / 64];
-    const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-    const uint64_t i = (uint64_t)blockIdx.x * kB + tid;
-    uint32_t keep = 0;
-    if (i < m.n_old) {
-        const uint64_t b = m.old_base[i];
-        const uint64_t k = lower_bound(m.del, m.n_del, b);
-        keep = (k < m.n_del && m.del[k] == b) ? 0u : 1u;
+    uint64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const uint64_t mid = (lo + hi) >> 1;
+        if (a[mid] <= x) lo = mid + 1; else hi = mid;
     }
-    uint32_t x = keep;
-    for (uint32_t d = 1; d < 64u; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
-    if (lane == 63u) wsum[wid] = x;
-    __syncthreads();
-    uint32_t off = 0;
-    for (uint32_t k = 0; k < wid; ++k) off += wsum[k];
-    if (i < m.n_old) {
-        m.keep[i] = (uint8_t)keep;
-        m.loc[i] = off + x - keep;
-    }
-    if (tid == kB - 1) m.bsum[blockIdx.x] = off + x;
+    return lo;
 }
 
-__global__ void __launch_bounds__(1024) k_merge_sums(MergeArgs m)
+__device__ __forceinline__ void put(const MergeArgs &m, uint64_t pos, uint64_t base, uint64_t end, uint64_t off)
 {
-    __shared__ uint64_t wsum[16];
-    const uint32_t tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-    const uint64_t nb = (m.n_old + kB - 1) / kB;
-    const uint64_t per = (nb + 1023) / 1024;
-    const uint64_t b0 = tid * per, b1 = (b0 + per < nb) ? b0 + per : nb;
-    uint64_t s = 0;
-    for (uint64_t b = b0; b < b1; ++b) s += m.bsum[b];
-    uint64_t x = s;
-    for (uint32_t d = 1; d < 64u; d <<= 1) {
-        const uint64_t y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
-    if (lane == 63u) wsum[wid] = x;
-    __syncthreads();
-    uint64_t off = 0;
-    for (uint32_t k = 0; k < wid; ++k) off += wsum[k];
-    uint64_t run = off + x - s;
-    for (uint64_t b = b0; b < b1; ++b) {
-        m.boff[b] = run;
-        run += m.bsum[b];
-    }
-    if (tid == 1023) m.boff[nb] = off + x;   // number of kept entries
+    m.new_base[pos] = base;
+    m.new_end[pos] = end;
+    m.new_off[pos] = off;
+    if ((pos & ((1ull << m.top_shift) - 1ull)) == 0) m.new_top[pos >> m.top_shift] = base;
 }
 
-// kept entries among the first j old entries (none when the old version is
-// empty: then k_merge_keep and k_merge_sums do not run and boff is not written)
-__device__ __forceinline__ uint64_t kept_before(const MergeArgs &m, uint64_t j)
+__device__ __forceinline__ void put_state(const DevState &st, DevState *out)
 {
-    if (m.n_old == 0) return 0;
-    const uint64_t nb = (m.n_old + kB - 1) / kB;
-    if (j >= m.n_old) return m.boff[nb];
-    return m.boff[j / kB] + m.loc[j];
+    if (out && blockIdx.x == 0 && threadIdx.x == 0) *out = st;
 }
 
-__global__ void __launch_bounds__(kB) k_merge_scatter(MergeArgs m)
+// INLINE: the change is words[0, n_del + 3 n_ins) of the arguments; the old
+// entry at or after an insert places it (the lane past the last entry places
+// those after all), so no lane searches the old table.  Otherwise the change
+// lies in device memory and one lane per insert searches the old table.
+template <bool INLINE>
+__global__ void __launch_bounds__(kB) k_merge(MergeArgs m)
 {
+    __shared__ uint64_t sw[INLINE ? kMergeInline : 1];
+    put_state(m.state, m.state_out);
     const uint64_t i = (uint64_t)blockIdx.x * kB + threadIdx.x;
-    if (i < m.n_old) {
-        if (!m.keep[i]) return;
-        const uint64_t b = m.old_base[i];
-        const uint64_t pos = kept_before(m, i) + lower_bound(m.ins_base, m.n_ins, b);
-        m.new_base[pos] = b;
-        m.new_end[pos] = m.old_end[i];
-        m.new_off[pos] = m.old_off[i];
-    } else if (i < m.n_old + m.n_ins) {
-        const uint64_t j = i - m.n_old;
-        const uint64_t b = m.ins_base[j];
-        const uint64_t pos = j + kept_before(m, lower_bound(m.old_base, m.n_old, b));
-        m.new_base[pos] = b;
-        m.new_end[pos] = m.ins_end[j];
-        m.new_off[pos] = m.ins_off[j];
+    if constexpr (INLINE) {
+        for (uint32_t k = threadIdx.x; k < m.n_del + 3 * m.n_ins; k += kB) sw[k] = m.words[k];
+        __syncthreads();
+        if (i > m.n_old) return;
+        const uint64_t *del = sw, *ins = sw + m.n_del;
+        const uint64_t nd = m.n_del, ni = m.n_ins;
+        const uint64_t b = i < m.n_old ? m.old_base[i] : ~0ull;
+        // the inserts above the previous old entry, up to this one (all that are left, past the last)
+        uint64_t j = i ? upper_bound(ins, ni, m.old_base[i - 1]) : 0;
+        const uint64_t j1 = i < m.n_old ? upper_bound(ins, ni, b) : ni;
+        for (; j < j1; ++j) {
+            const uint64_t x = ins[j];
+            put(m, j + i - lower_bound(del, nd, x), x, ins[ni + j], ins[2 * ni + j]);
+        }
+        if (i >= m.n_old) return;
+        const uint64_t k = lower_bound(del, nd, b);
+        if (k < nd && del[k] == b) return;   // freed
+        put(m, i - k + lower_bound(ins, ni, b), b, m.old_end[i], m.old_off[i]);
+    } else {
+        if (i < m.n_old) {
+            const uint64_t b = m.old_base[i];
+            const uint64_t k = lower_bound(m.del, m.n_del, b);
+            if (k < m.n_del && m.del[k] == b) return;   // freed
+            put(m, i - k + lower_bound(m.ins_base, m.n_ins, b), b, m.old_end[i], m.old_off[i]);
+        } else if (i < m.n_old + m.n_ins) {
+            const uint64_t j = i - m.n_old;
+            const uint64_t x = m.ins_base[j];
+            put(m, j + lower_bound(m.old_base, m.n_old, x) - lower_bound(m.del, m.n_del, x), x, m.ins_end[j],
+                m.ins_off[j]);
+        }
     }
 }
 
-__global__ void __launch_bounds__(kB) k_merge_top(MergeArgs m)
-{
-    const uint64_t k = (uint64_t)blockIdx.x * kB + threadIdx.x;
-    if (k < m.ntop) m.new_top[k] = m.new_base[k << m.top_shift];
-}
+__global__ void k_state(DevState st, DevState *out) { put_state(st, out); }
 
 }  // namespace
 
 hipError_t launch_merge(const MergeArgs &m, hipStream_t s)
 {
-    const uint64_t nb = (m.n_old + kB - 1) / kB;
-    if (m.n_old) {
-        hipLaunchKernelGGL(k_merge_keep, dim3((uint32_t)nb), dim3(kB), 0, s, m);
-        hipLaunchKernelGGL(k_merge_sums, dim3(1), dim3(1024), 0, s, m);
+    if (m.in_words) {
+        const uint64_t blocks = (m.n_old + 1 + kB - 1) / kB;
+        hipLaunchKernelGGL((k_merge<true>), dim3((uint32_t)blocks), dim3(kB), 0, s, m);
+    } else {
+        const uint64_t tot = std::max<uint64_t>(m.n_old + m.n_ins, 1);
+        hipLaunchKernelGGL((k_merge<false>), dim3((uint32_t)((tot + kB - 1) / kB)), dim3(kB), 0, s, m);
     }
-    const uint64_t tot = m.n_old + m.n_ins;
-    if (tot) hipLaunchKernelGGL(k_merge_scatter, dim3((uint32_t)((tot + kB - 1) / kB)), dim3(kB), 0, s, m);
-    if (m.ntop) hipLaunchKernelGGL(k_merge_top, dim3((uint32_t)((m.ntop + kB - 1) / kB)), dim3(kB), 0, s, m);
+    return hipGetLastError();
+}
+
+hipError_t launch_state(const DevState &st, DevState *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_state, dim3(1), dim3(1), 0, s, st, out);
     return hipGetLastError();
 }
 
 hipError_t launch_merge_warm(hipStream_t s)
 {
     MergeArgs m{};
-    hipLaunchKernelGGL(k_merge_top, dim3(1), dim3(kB), 0, s, m);   // ntop = 0: loads the code only
-    return hipGetLastError();
+    m.in_words = 1;
+    return launch_merge(m, s);   // nothing to merge, no state: loads the code only
 }
 
 }  // namespace xc

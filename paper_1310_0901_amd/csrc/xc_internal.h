@@ -224,8 +224,10 @@ struct LaunchShape {
 };
 
 // Merge of a table version with the frees and allocations made since
-// (table.hip).  del / ins_* are sorted by base; keep / loc / bsum / boff are
-// scratch sized for n_old (boff has one extra entry: the kept count).
+// (table.hip): del / ins_* are sorted by base and lie in device memory, or,
+// with in_words, in words[]: n_del bases, then n_ins bases, ends and offsets.
+// The merge also writes the new version's DevState.
+constexpr uint64_t kMergeInline = 96;
 struct MergeArgs {
     const uint64_t *old_base, *old_end, *old_off;
     uint64_t n_old;
@@ -234,13 +236,21 @@ struct MergeArgs {
     const uint64_t *ins_base, *ins_end, *ins_off;
     uint64_t n_ins;
     uint64_t *new_base, *new_end, *new_off, *new_top;
-    uint32_t top_shift, ntop;
-    uint8_t *keep;
-    uint32_t *loc;
-    uint64_t *bsum, *boff;
+    DevState state;
+    DevState *state_out;
+    uint32_t top_shift;
+    uint32_t in_words;
+    uint64_t words[kMergeInline];
 };
 hipError_t launch_merge(const MergeArgs &m, hipStream_t s);
 hipError_t launch_merge_warm(hipStream_t s);
+hipError_t launch_state(const DevState &st, DevState *out, hipStream_t s);
+
+// Fill ranges that travel in a launch's own arguments.
+constexpr uint64_t kFillInline = 64;
+struct FillArgs {
+    FillRange r[kFillInline];
+};
 
 // kernel launchers (kernels.hip); all asynchronous on `s`
 hipError_t launch_classify(const BatchArgs &a, hipStream_t s);
@@ -269,6 +279,7 @@ hipError_t launch_batched(const BatchArgs &a, const LaunchShape &sh, hipStream_t
 hipError_t launch_plain(const BatchArgs &a, uint64_t rec, uint64_t units, const LaunchShape &sh,
                         hipStream_t s);
 hipError_t launch_fill(const FillRange *ranges_dev, uint64_t k, hipStream_t s);
+hipError_t launch_fill_inline(const FillArgs &f, uint64_t k, hipStream_t s);   // k <= kFillInline ranges
 // `bytes` (a multiple of 8) from coherent host memory (its device address) to device memory
 hipError_t launch_upload(const void *src, void *dst, uint64_t bytes, hipStream_t s);
 // a batch of a.count records in one launch of a.count * bpr blocks of sh.block threads

@@ -1,0 +1,82 @@
+"""Edges of the device paths: sizes where a kernel's split, its remainder or
+the rule that chooses it changes, against the oracle or a plain host model."""
+import numpy as np
+import pytest
+
+from paper_1310_0901_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def X():
+    from paper_1310_0901_amd import xfercheck
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    xfercheck.lib()
+    return xfercheck
+
+
+@pytest.mark.parametrize("n0", [0, 1, 63, 255, 256, 257, 5000])
+@pytest.mark.parametrize("words", [1, 3, 95, 96, 97, 400])
+def test_table_change_by_merge(X, n0, words):
+    """A table version made from the one before by `words` words of frees and
+    allocations (up to 96 travel in the launch's arguments, more through
+    device memory): every entry and the top level equal the sorted list.
+    Allocations go before, between, after and in place of the old entries."""
+    rng = np.random.default_rng(1000 * n0 + words)
+    step = 4096
+    base = W.DEV_BASE + step * 8 * np.arange(1, n0 + 1, dtype=np.int64)
+    ctx = X.cg_create(0, 64 << 20, n0 + 512)
+    try:
+        live = {int(b): 300 for b in base}
+        if n0:
+            X.shadow_alloc_batch(ctx, base, np.full(n0, 300))
+        X.cg_table_read(ctx, n0 + 16)                       # the version to change
+        nfree = min(words % 3 + 3 * int(rng.integers(0, words // 6 + 1)), n0)
+        nins = (words - nfree) // 3
+        nfree = min(words - 3 * nins, n0)
+        kill = rng.choice(base, nfree, replace=False) if nfree else []
+        for b in kill:
+            X.shadow_free(ctx, int(b))
+            live.pop(int(b))
+        slots = np.setdiff1d(W.DEV_BASE + step * np.arange(0, 8 * n0 + 520, dtype=np.int64), np.array(list(live)))
+        again = list(kill[: nins // 3])
+        new = np.unique(np.concatenate([again, rng.choice(slots, nins, replace=False)]).astype(np.int64))[:nins]
+        for b in new:
+            live[int(b)] = int(rng.integers(1, 300))
+            X.shadow_alloc(ctx, int(b), live[int(b)])
+        t = X.cg_table_read(ctx, n0 + 512)
+        keys = np.array(sorted(live), np.uint64)
+        sizes = np.array([live[int(k)] for k in keys], np.uint64)
+        assert np.array_equal(t["base"], keys) and np.array_equal(t["end"], keys + sizes)
+        assert np.array_equal(t["top"], keys[:: 1 << t["shift"]])
+        for b, o in zip(t["base"], t["off"]):
+            assert X.shadow_ptr(ctx, int(b)) == t["pool"] + int(o)
+    finally:
+        X.cg_destroy(ctx)
+
+
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 200])
+def test_fills_of_many_ranges(X, count):
+    """shadow_set_batch of up to 64 ranges (in the launch's arguments) and of
+    more (uploaded), at every start and length modulo 16: each byte set has
+    the last value written to it, every other keeps its own."""
+    from paper_1310_0901_amd import harness as H
+    rng = np.random.default_rng(count)
+    size = 1 << 20
+    ctx = X.cg_create(0, 4 << 20, 16)
+    try:
+        X.shadow_alloc(ctx, W.DEV_BASE, size)
+        cut = np.sort(rng.choice(size, 2 * count, replace=False))
+        a, n = cut[::2], cut[1::2] - cut[::2]
+        v = rng.integers(0, 255, count)
+        X.shadow_set_batch(ctx, W.DEV_BASE + a, n, v)
+        X.cg_sync(ctx)
+        want = np.full(size, 0xFF, np.uint8)
+        for s, k, x in zip(a, n, v):
+            want[s:s + k] = x
+        assert np.array_equal(H.read_device(X.shadow_ptr(ctx, W.DEV_BASE), size), want)
+    finally:
+        X.cg_destroy(ctx)
