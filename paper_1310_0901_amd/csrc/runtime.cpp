@@ -107,7 +107,7 @@ struct TimingPair {
     hipEvent_t a = nullptr, b = nullptr;
 };
 
-// One version of the device table: sorted base | end | off | top arrays and
+// One version of the device table: sorted base | end | off | top | mid | fine arrays and
 // the DevState that points at them.  `uses` holds, per stream, an event
 // recorded after the last check on that stream that read this version.
 struct TableVersion {
@@ -290,6 +290,14 @@ int materialize(cg_ctx *c)
     st.table.end = nv.tab + M;
     st.table.off = nv.tab + 2 * M;
     st.table.top = nv.tab + 3 * M;
+    uint32_t mid_shift = 0;
+    while (((n + (1ull << mid_shift) - 1) >> mid_shift) > (uint64_t)kMaxMid) ++mid_shift;
+    uint64_t *mid = nv.tab + 3 * M + kMaxTop;   // unused while every base fits the middle level
+    st.table.mid = mid_shift ? mid : nv.tab;
+    st.table.mid_shift = mid_shift;
+    uint64_t *fine = mid + kMaxMid;
+    st.table.fine = fine;
+    st.table.nmid = (uint32_t)((n + (1ull << mid_shift) - 1) >> mid_shift);
     st.table.n = n;
     st.table.top_shift = shift;
     st.table.ntop = ntop;
@@ -308,7 +316,7 @@ int materialize(cg_ctx *c)
             HIPTRY(c, hipMemcpyAsync(nv.tab + 2 * M, ho, n * 8, hipMemcpyHostToDevice, c->s));
             HIPTRY(c, hipMemcpyAsync(nv.tab + 3 * M, ht, ntop * 8ull, hipMemcpyHostToDevice, c->s));
         }
-        HIPTRY(c, launch_state(st, nv.st, c->s));
+        HIPTRY(c, launch_state(st, nv.st, mid_shift ? mid : nullptr, fine, c->s));
         c->full_uploads++;
     } else {
         MergeArgs m{};
@@ -333,7 +341,10 @@ int materialize(cg_ctx *c)
         m.ins_base = c->d_delta + nd; m.ins_end = c->d_delta + nd + ni; m.ins_off = c->d_delta + nd + 2 * ni;
         m.n_ins = ni;
         m.new_base = nv.tab; m.new_end = nv.tab + M; m.new_off = nv.tab + 2 * M; m.new_top = nv.tab + 3 * M;
+        m.new_mid = mid;
+        m.new_fine = fine;
         m.top_shift = shift;
+        m.mid_shift = mid_shift;
         m.state = st; m.state_out = nv.st;
         HIPTRY(c, launch_merge(m, c->s));
         c->merges++;
@@ -1122,7 +1133,7 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
     c->pool_bytes = pool;
     c->palloc = new PoolAllocator(pool, 256);
     for (auto &v : c->ver) {
-        if (hipMalloc(&v.tab, (3 * max_allocs + kMaxTop) * 8) != hipSuccess) return bail(CG_ENOMEM);
+        if (hipMalloc(&v.tab, (3 * max_allocs + kMaxTop + kMaxMid + (max_allocs >> kFineShift) + 1) * 8) != hipSuccess) return bail(CG_ENOMEM);
         if (hipMalloc(&v.st, sizeof(DevState)) != hipSuccess) return bail(CG_ENOMEM);
     }
     if (hipMalloc(&c->d_delta, (3 * max_allocs + kMaxTop) * 8) != hipSuccess) return bail(CG_ENOMEM);
@@ -1561,7 +1572,7 @@ int check_pointers(cg_ctx *c, const uint64_t *ptrs_dev, uint64_t count, cg_ptr_c
     int rc = materialize(c);
     if (rc) return rc;
     HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
-    HIPTRY(c, launch_pointers(c->ver[c->cur].st, ptrs_dev, count, out_dev, s));
+    HIPTRY(c, launch_pointers(c->ver[c->cur].st, c->state.table.nmid, (uint32_t)c->cu_count, ptrs_dev, count, out_dev, s));
     return note_use(c, s);
 }
 

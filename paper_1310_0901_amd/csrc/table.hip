@@ -7,9 +7,9 @@
 //   k_merge        one lane per old entry: its index in the new table is its
 //                  old index, less the frees below it, plus the inserts below
 //                  it, and the entries that fall on every 2^shift-th index
-//                  also go to the top level; the version's DevState is written
-//                  by the first block
-//   k_state        the DevState alone (a version uploaded whole)
+//                  also go to the levels above; the version's DevState
+//                  is written by the first block
+//   k_state        the DevState and the lower levels (a version uploaded whole)
 //
 // Every freed base is in the old table, so "frees below" is a search in the
 // sorted frees and no scan over the old entries is needed.  Bound by latency
@@ -60,6 +60,8 @@ __device__ __forceinline__ void put(const MergeArgs &m, uint64_t pos, uint64_t b
     m.new_end[pos] = end;
     m.new_off[pos] = off;
     if ((pos & ((1ull << m.top_shift) - 1ull)) == 0) m.new_top[pos >> m.top_shift] = base;
+    if (m.mid_shift && (pos & ((1ull << m.mid_shift) - 1ull)) == 0) m.new_mid[pos >> m.mid_shift] = base;
+    if ((pos & ((1u << kFineShift) - 1u)) == 0) m.new_fine[pos >> kFineShift] = base;
 }
 
 __device__ __forceinline__ void put_state(const DevState &st, DevState *out)
@@ -110,7 +112,13 @@ __global__ void __launch_bounds__(kB) k_merge(MergeArgs m)
     }
 }
 
-__global__ void k_state(DevState st, DevState *out) { put_state(st, out); }
+__global__ void __launch_bounds__(kB) k_state(DevState st, DevState *out, uint64_t *mid, uint64_t *fine)
+{
+    put_state(st, out);
+    const uint64_t k = (uint64_t)blockIdx.x * kB + threadIdx.x;
+    if ((k << kFineShift) < st.table.n) fine[k] = st.table.base[k << kFineShift];
+    if (mid && k < st.table.nmid) mid[k] = st.table.base[k << st.table.mid_shift];
+}
 
 }  // namespace
 
@@ -126,9 +134,10 @@ hipError_t launch_merge(const MergeArgs &m, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_state(const DevState &st, DevState *out, hipStream_t s)
+hipError_t launch_state(const DevState &st, DevState *out, uint64_t *mid, uint64_t *fine, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_state, dim3(1), dim3(1), 0, s, st, out);
+    const uint64_t k = std::max<uint64_t>(std::max<uint64_t>(mid ? st.table.nmid : 1, (st.table.n >> kFineShift) + 1), 1);
+    hipLaunchKernelGGL(k_state, dim3((uint32_t)((k + kB - 1) / kB)), dim3(kB), 0, s, st, out, mid, fine);
     return hipGetLastError();
 }
 

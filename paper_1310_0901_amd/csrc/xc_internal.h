@@ -64,8 +64,11 @@ struct Region {
 struct TableView {
     const uint64_t *base, *end, *off;
     const uint64_t *top;   // base[k << top_shift], k < ntop
+    const uint64_t *mid;   // base[k << mid_shift], k < nmid (base itself when mid_shift is 0)
+    const uint64_t *fine;  // base[k << kFineShift] (read when mid_shift is larger)
     uint64_t n;
     uint32_t top_shift, ntop;
+    uint32_t mid_shift, nmid;
 };
 
 // Device-resident view of the context (allocation table, host region, pool);
@@ -86,6 +89,8 @@ struct FillRange {
 };
 
 constexpr int kMaxTop = 1024;        // LDS-staged top level of the table
+constexpr int kMaxMid = 8192;        // entries of its middle level (64 KiB of LDS where a kernel stages it)
+constexpr uint32_t kFineShift = 4;   // 16 bases: one 128-byte line
 constexpr uint64_t kMinTile = 1024;  // smallest work tile, in 16-byte units
 constexpr int kClassifyBlock = 256;  // records per classify block
 constexpr uint64_t kScanLimit = 1ull << 62;  // byte indices scanned per record
@@ -235,16 +240,17 @@ struct MergeArgs {
     uint64_t n_del;
     const uint64_t *ins_base, *ins_end, *ins_off;
     uint64_t n_ins;
-    uint64_t *new_base, *new_end, *new_off, *new_top;
+    uint64_t *new_base, *new_end, *new_off, *new_top, *new_mid, *new_fine;   // new_mid: not written when mid_shift is 0
     DevState state;
     DevState *state_out;
-    uint32_t top_shift;
+    uint32_t top_shift, mid_shift;
     uint32_t in_words;
     uint64_t words[kMergeInline];
 };
 hipError_t launch_merge(const MergeArgs &m, hipStream_t s);
 hipError_t launch_merge_warm(hipStream_t s);
-hipError_t launch_state(const DevState &st, DevState *out, hipStream_t s);
+// the DevState, and the table's middle level when mid is not null, and its fine level
+hipError_t launch_state(const DevState &st, DevState *out, uint64_t *mid, uint64_t *fine, hipStream_t s);
 
 // Fill ranges that travel in a launch's own arguments.
 constexpr uint64_t kFillInline = 64;
@@ -297,7 +303,9 @@ hipError_t launch_2d_expand(const cg_transfer2d *recs, const uint64_t *first, ui
                             cg_transfer *rows, uint32_t *rec_of, hipStream_t s);
 hipError_t launch_2d_fold(const cg_transfer2d *recs, const uint64_t *first, uint64_t count, const uint32_t *rec_of,
                           const cg_verdict *rowv, uint64_t nrows, cg_verdict *out, hipStream_t s);
-hipError_t launch_pointers(const DevState *st, const uint64_t *ptrs, uint64_t count, cg_ptr_check *out, hipStream_t s);
+// nmid: entries of the table's middle level, cus: compute units
+hipError_t launch_pointers(const DevState *st, uint32_t nmid, uint32_t cus, const uint64_t *ptrs, uint64_t count,
+                           cg_ptr_check *out, hipStream_t s);
 hipError_t launch_probe_read(const void *p, uint64_t bytes, uint64_t *sink, hipStream_t s);
 hipError_t launch_probe_copy(void *d, const void *p, uint64_t bytes, hipStream_t s);
 hipError_t launch_probe_l2(const void *p, uint64_t slice_bytes, uint32_t passes, uint32_t blocks, uint64_t *sink,

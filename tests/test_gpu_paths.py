@@ -80,3 +80,41 @@ def test_fills_of_many_ranges(X, count):
         assert np.array_equal(H.read_device(X.shadow_ptr(ctx, W.DEV_BASE), size), want)
     finally:
         X.cg_destroy(ctx)
+
+
+@pytest.mark.parametrize("nalloc", [0, 1, 2, 3, 1024, 1025, 8191, 8192, 8193, 16385, 131071, 131073, 140001])
+def test_pointers_at_table_edges(X, nalloc):
+    """check_pointers around the sizes where the table's middle level (8,192
+    entries) stops holding every base, its stride doubles, and the fine level
+    (every 16th base, from 131,073 entries on) joins in: pointers one
+    below, at, inside, at the end of and one past the end of allocations, some
+    of them adjacent, at 1 pointer and at 70,000 (both workgroup sizes)."""
+    from oracle import oracle
+    rng = np.random.default_rng(nalloc)
+    sizes = rng.integers(1, 700, nalloc)
+    gaps = rng.integers(0, 2, nalloc) * rng.integers(1, 300, nalloc)
+    base = W.DEV_BASE + np.cumsum(sizes + gaps) - sizes
+    ctx = X.cg_create(0, 256 << 20, nalloc + 16)
+    try:
+        if nalloc:
+            X.shadow_alloc_batch(ctx, base, sizes)
+        ends = np.concatenate([base - 1, base, base + sizes // 2, base + sizes - 1, base + sizes, base + sizes + 1,
+                               [0, 1, (1 << 63) - 1]])
+        for count in (1, 70_000):
+            p = rng.choice(ends, count).astype(np.uint64)
+            t = torch.from_numpy(p.view(np.int64)).cuda()
+            out = torch.zeros((count, 3), dtype=torch.int64, device="cuda")
+            X.check_pointers(ctx, t.data_ptr(), count, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().view(W.PTR_DTYPE).reshape(-1)
+            # the oracle scans its list: give it the allocations the sample can lie in
+            keep = np.arange(nalloc) if nalloc <= 1025 else np.unique(rng.choice(nalloc, 400))
+            ok = np.isin(p.astype(np.int64), np.concatenate([e[keep] for e in (base - 1, base, base + sizes // 2,
+                         base + sizes - 1, base + sizes, base + sizes + 1)] + [np.array([0, 1, (1 << 63) - 1])]))
+            near = np.unique(np.clip(np.concatenate([keep - 1, keep, keep + 1, keep + 2]), 0, max(nalloc - 1, 0)))
+            near = near[:nalloc] if nalloc else np.zeros(0, np.int64)
+            want = oracle.pointers(base[near].astype(np.uint64), sizes[near].astype(np.uint64), p[ok])
+            for f in ("flags", "base", "avail"):
+                assert np.array_equal(got[ok][f], want[f]), (count, f)
+    finally:
+        X.cg_destroy(ctx)
