@@ -25,17 +25,19 @@
 //                  each position's record;
 //   k_scan_sums    one block: exclusive scan of the per-block sums, tile size;
 //   k_prefix_tiles global prefix; k_tile_starts first record of every tile;
-//   k_batched      persistent kernel: tiles of the flattened 16-byte unit space,
-//                  one contiguous chunk per XCD for a segmented batch, taken
-//                  from per-chunk device counters; 16-byte V loads and aligned
-//                  16-bit A loads, SWAR non-zero masks, popcount / ctz for the
-//                  undefined count and first fault, DPP wave reductions, rare
-//                  global atomics; optional realigned V store to the
-//                  destination shadow.
+//   k_batched      persistent kernel: tiles of the flattened 16-byte unit space
+//                  (one tile per wave when the batch is small), for a
+//                  segmented batch one contiguous chunk per XCD, taken from
+//                  per-chunk device counters; 16-byte V windows at any
+//                  alignment and their A bits, SWAR non-zero masks, popcount /
+//                  ctz for the undefined count and first fault, DPP wave
+//                  reductions, rare global atomics; optional non-temporal V
+//                  store to the destination shadow.
 // The plain path runs k_classify once, then k_plain once per record.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "xc_internal.h"
 
@@ -43,6 +45,8 @@ namespace xc {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4u __attribute__((aligned(1)));   // at any byte address
+typedef uint32_t u32u __attribute__((aligned(1)));
 
 constexpr uint64_t NONE = CG_NONE;
 
@@ -71,6 +75,11 @@ __device__ __forceinline__ uint32_t nz16(u32x4 v)
     return nz4(v.x) | (nz4(v.y) << 4) | (nz4(v.z) << 8) | (nz4(v.w) << 12);
 }
 
+// At the head of a branch that is rarely taken: keeps it a branch.  Worked
+// without one, the masks and sums of all of an unrolled loop's windows live in
+// registers at once, and half the waves fit.
+__device__ __forceinline__ void stay_branched() { asm volatile(""); }
+
 // 4-bit mask -> byte mask (0x00 / 0xFF per byte); the shifted copies of m do
 // not overlap, so the multiply has no carries.
 __device__ __forceinline__ uint32_t expand4(uint32_t m)
@@ -83,31 +92,13 @@ __device__ __forceinline__ uint32_t expand4(uint32_t m)
 __device__ __forceinline__ u32x4 prop_val(u32x4 v, uint32_t ok)
 {
     if (ok == 0xFFFFu) return v;
+    stay_branched();
     u32x4 r;
     r.x = v.x | ~expand4(ok & 0xFu);
     r.y = v.y | ~expand4((ok >> 4) & 0xFu);
     r.z = v.z | ~expand4((ok >> 8) & 0xFu);
     r.w = v.w | ~expand4((ok >> 12) & 0xFu);
     return r;
-}
-
-// Bytes [s, s + 16) of the 32-byte concatenation a || b.
-__device__ __forceinline__ u32x4 window(u32x4 a, u32x4 b, uint32_t s)
-{
-    const uint32_t q = s >> 2, r = s & 3u;
-    uint32_t w0, w1, w2, w3, w4;
-    switch (q) {
-    case 0: w0 = a.x; w1 = a.y; w2 = a.z; w3 = a.w; w4 = b.x; break;
-    case 1: w0 = a.y; w1 = a.z; w2 = a.w; w3 = b.x; w4 = b.y; break;
-    case 2: w0 = a.z; w1 = a.w; w2 = b.x; w3 = b.y; w4 = b.z; break;
-    default: w0 = a.w; w1 = b.x; w2 = b.y; w3 = b.z; w4 = b.w; break;
-    }
-    u32x4 o;
-    o.x = __builtin_amdgcn_alignbyte(w1, w0, r);
-    o.y = __builtin_amdgcn_alignbyte(w2, w1, r);
-    o.z = __builtin_amdgcn_alignbyte(w3, w2, r);
-    o.w = __builtin_amdgcn_alignbyte(w4, w3, r);
-    return o;
 }
 
 // Global (address space 1) views of device addresses, so that the compiler
@@ -117,7 +108,7 @@ template <typename T> using gcptr = const __attribute__((address_space(1))) T *;
 
 __device__ __forceinline__ void store_word_masked(uint64_t p, uint32_t w, uint32_t m)
 {
-    if (m == 0xFu) { *reinterpret_cast<gptr<uint32_t>>(p) = w; return; }
+    if (m == 0xFu) { *reinterpret_cast<gptr<u32u>>(p) = w; return; }
     gptr<uint8_t> b = reinterpret_cast<gptr<uint8_t>>(p);
     if (m & 1u) b[0] = (uint8_t)w;
     if (m & 2u) b[1] = (uint8_t)(w >> 8);
@@ -125,27 +116,15 @@ __device__ __forceinline__ void store_word_masked(uint64_t p, uint32_t w, uint32
     if (m & 8u) b[3] = (uint8_t)(w >> 24);
 }
 
-// Store the bytes of v selected by m at the 16-byte aligned address p.
+// Store the bytes of v selected by m at p (any alignment).
 __device__ __forceinline__ void store_masked(uint64_t p, u32x4 v, uint32_t m)
 {
-    if (m == 0xFFFFu) { *reinterpret_cast<gptr<u32x4>>(p) = v; return; }
+    if (m == 0xFFFFu) { __builtin_nontemporal_store(v, reinterpret_cast<gptr<u32x4u>>(p)); return; }
+    stay_branched();
     if (m & 0x000Fu) store_word_masked(p, v.x, m & 0xFu);
     if (m & 0x00F0u) store_word_masked(p + 4, v.y, (m >> 4) & 0xFu);
     if (m & 0x0F00u) store_word_masked(p + 8, v.z, (m >> 8) & 0xFu);
     if (m & 0xF000u) store_word_masked(p + 12, v.w, (m >> 12) & 0xFu);
-}
-
-template <bool NT>
-__device__ __forceinline__ u32x4 ld16(uint64_t addr)
-{
-    gcptr<u32x4> p = reinterpret_cast<gcptr<u32x4>>(addr);
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-
-__device__ __forceinline__ uint32_t ld_u16(uint64_t addr)
-{
-    return *reinterpret_cast<gcptr<uint16_t>>(addr);
 }
 
 __device__ __forceinline__ int32_t clamp32(int64_t x)
@@ -165,6 +144,22 @@ __device__ __forceinline__ uint32_t ufl32(uint32_t x) { return (uint32_t)__built
 __device__ __forceinline__ uint64_t ufl64(uint64_t x)
 {
     return ((uint64_t)ufl32((uint32_t)(x >> 32)) << 32) | ufl32((uint32_t)x);
+}
+
+// *p through scalar loads: p is the same for the whole wave, and the kernel
+// does not write what it points at.
+template <typename T>
+__device__ __forceinline__ T ld_uniform(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    using cword = const __attribute__((address_space(4))) uint32_t;
+    cword *q = reinterpret_cast<cword *>(ufl64(reinterpret_cast<uint64_t>(p)));
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) w[k] = q[k];
+    T x;
+    __builtin_memcpy(&x, w, sizeof(T));
+    return x;
 }
 
 // ---- DPP wave reductions (every lane of the wave must be active) --------
@@ -218,7 +213,89 @@ __device__ __forceinline__ uint32_t wave_or32(uint32_t x)
            (uint32_t)__builtin_amdgcn_readlane((int)x, 32) | (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
 }
 
+__device__ __forceinline__ uint64_t wave_or64(uint64_t x)
+{
+    return (uint64_t)wave_or32((uint32_t)x) | ((uint64_t)wave_or32((uint32_t)(x >> 32)) << 32);
+}
+
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+
+// Loads and stores of a window of 16 V bytes at any byte address.  Unaligned 16-byte accesses run at 0.93-1.0 of the aligned rate on gfx950
+// (64 MiB and 2 GiB copies at source and destination offsets of 0, 1, 4, 8 and
+// 13 bytes), so both sides of a record are read and written in the same
+// windows and nothing is realigned in registers.
+
+template <bool NT>
+__device__ __forceinline__ u32x4 ld16(uint64_t addr)
+{
+    gcptr<u32x4u> p = reinterpret_cast<gcptr<u32x4u>>(addr);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+// The destination shadow is written once and not read again by the batch:
+// non-temporal stores keep it out of the caches' way (2 GiB copied with
+// non-temporal loads: 889 us with cached stores, 750-800 without).
+__device__ __forceinline__ void st16(uint64_t addr, u32x4 v)
+{
+    __builtin_nontemporal_store(v, reinterpret_cast<gptr<u32x4u>>(addr));
+}
+
+// A bits [bit, bit + 16) of the bitmap, from one unaligned word inside its nab
+// bytes; bits outside it come out as any value.
+__device__ __forceinline__ uint32_t ld_a16(uint64_t a16, int64_t nab, int64_t bit)
+{
+    int64_t b = bit >> 3;
+    b = b < 0 ? 0 : (b > nab - 4 ? nab - 4 : b);
+    const uint32_t w = *reinterpret_cast<gcptr<u32u>>(a16 + (uint64_t)b);
+    const int64_t s = bit - 8 * b;   // -15 .. 31 for bits that matter
+    return (s >= 0 ? (s < 32 ? w >> (uint32_t)s : 0u) : w << (uint32_t)(-s & 31)) & 0xFFFFu;
+}
+
+__device__ __forceinline__ int64_t a_bytes(const Region &R) { return (int64_t)(((R.hl + 63) >> 6) << 3); }
+
+// The same for windows from bit `bit` on, 16 bits apart, with 32-bit offsets.
+struct AWords {
+    uint64_t base;         // address of the word of window 0 (which may lie outside the bitmap)
+    int32_t lo, hi, s;     // first and last byte offset from there inside the bitmap, first bit in the word
+    __device__ __forceinline__ AWords(const Region &R, int64_t bit)
+    {
+        const int64_t b = bit >> 3;
+        base = (uint64_t)R.a16 + (uint64_t)b;
+        lo = clamp32(-b);
+        hi = clamp32(a_bytes(R) - 4 - b);
+        s = (int32_t)(bit & 7);
+    }
+    // the window 16 w bits on
+    __device__ __forceinline__ uint32_t at(int32_t w) const { return word(2 * w, s); }
+    // the window n bits on (n >= 0)
+    __device__ __forceinline__ uint32_t bits(int32_t n) const { return word((s + n) >> 3, (s + n) & 7); }
+
+private:
+    __device__ __forceinline__ uint32_t word(int32_t p, int32_t bit) const
+    {
+        const int32_t q = p < lo ? lo : (p > hi ? hi : p);
+        const uint32_t x = *reinterpret_cast<gcptr<u32u>>(base + (uint64_t)(int64_t)q);
+        const int32_t k = bit + 8 * (p - q);   // -16 < k < 32 where any bit matters
+        return (k >= 0 ? x >> (uint32_t)(k & 31) : x << (uint32_t)(-k & 31)) & 0xFFFFu;
+    }
+};
+
+// The 16 bytes s bytes after those of v (before, for s < 0; |s| < 16), with
+// zeros where v has none.
+__device__ __forceinline__ u32x4 byte_shift(u32x4 v, int32_t s)
+{
+    uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+    if (s > 0) {
+        if (s >= 8) { lo = hi; hi = 0; s -= 8; }
+        if (s) { lo = (lo >> (8 * s)) | (hi << (64 - 8 * s)); hi >>= 8 * s; }
+    } else if (s < 0) {
+        s = -s;
+        if (s >= 8) { hi = lo; lo = 0; s -= 8; }
+        if (s) { hi = (hi << (8 * s)) | (lo >> (64 - 8 * s)); lo <<= 8 * s; }
+    }
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
 
 // ---------------------------------------------------------------------------
 // descriptor in registers
@@ -227,7 +304,7 @@ struct DV {
     uint64_t src_sh, dst_sh;
     int64_t v_lo, v_hi, d_lo, d_hi, a_src, a_dst;
     uint64_t e0, units;
-    uint32_t ctl, phi, psi, delta, s;
+    uint32_t ctl, o;
 };
 
 __device__ __forceinline__ DV make_dv(const Desc &x)
@@ -237,44 +314,42 @@ __device__ __forceinline__ DV make_dv(const Desc &x)
     d.v_lo = x.v_lo; d.v_hi = x.v_hi; d.d_lo = x.d_lo; d.d_hi = x.d_hi;
     d.a_src = x.a_src; d.a_dst = x.a_dst; d.e0 = x.e0; d.units = x.units;
     d.ctl = x.ctl;
-    d.phi = (d.ctl >> CTL_PHI_SHIFT) & 15u;
-    d.psi = (d.ctl >> CTL_PSI_SHIFT) & 15u;
-    d.delta = (d.ctl & CTL_DELTA) ? 1u : 0u;
-    d.s = (d.phi - d.psi) & 15u;
+    d.o = desc_o(x);
     return d;
 }
 
 // Per-lane descriptor (lanes may work on different records).
 __device__ __forceinline__ DV load_desc(const Desc *D, uint64_t t) { return make_dv(D[t]); }
 
-// Wave-uniform descriptor: every field forced into scalar registers.
-__device__ __forceinline__ DV load_desc_uniform(const Desc *D, uint64_t t)
-{
-    const Desc &x = D[t];
-    Desc u;
-    u.src_sh = ufl64(x.src_sh); u.dst_sh = ufl64(x.dst_sh);
-    u.v_lo = (int64_t)ufl64((uint64_t)x.v_lo); u.v_hi = (int64_t)ufl64((uint64_t)x.v_hi);
-    u.d_lo = (int64_t)ufl64((uint64_t)x.d_lo); u.d_hi = (int64_t)ufl64((uint64_t)x.d_hi);
-    u.a_src = (int64_t)ufl64((uint64_t)x.a_src); u.a_dst = (int64_t)ufl64((uint64_t)x.a_dst);
-    u.e0 = ufl64(x.e0); u.units = ufl64(x.units); u.ctl = ufl32(x.ctl);
-    return make_dv(u);
-}
+// Wave-uniform descriptor, in scalar registers.
+__device__ __forceinline__ DV load_desc_uniform(const Desc *D, uint64_t t) { return make_dv(ld_uniform(D + t)); }
 
-// Source chunk c: V bytes, valid-byte mask, and (host source) the in-range
-// bytes whose A bit is 0.  Nothing is read outside the valid byte range.
+// The first and the last 16-aligned chunk holding a valid source byte.  A
+// window that is only partly valid may reach outside the shadow; it is loaded
+// from its address clamped to these two, where every byte is inside the
+// allocation's slot or the region's padded V bytes, and shifted into place
+// (every valid byte of the window lies in the clamped load).
+__device__ __forceinline__ uint64_t src_first(const DV &d) { return (d.src_sh + d.o + (uint64_t)d.v_lo) & ~15ull; }
+__device__ __forceinline__ uint64_t src_last(const DV &d) { return (d.src_sh + d.o + (uint64_t)d.v_hi - 1u) & ~15ull; }
+
+// Window e of one lane: V bytes, valid-byte mask, and (host source) the
+// in-range bytes whose A bit is 0.
 template <bool NT>
-__device__ __forceinline__ void src_chunk(const DV &d, const Region &R, int64_t c, u32x4 &v,
-                                          uint32_t &ok, uint32_t &unaddr)
+__device__ __forceinline__ void src_window(const DV &d, const Region &R, int64_t e, u32x4 &v, uint32_t &ok,
+                                           uint32_t &unaddr)
 {
-    const int64_t i0 = 16 * c - (int64_t)d.phi;
+    const int64_t i0 = 16 * e - (int64_t)d.o;
     const uint32_t m = rmask(d.v_lo - i0, d.v_hi - i0);
     v = u32x4{0u, 0u, 0u, 0u};
     ok = 0u;
     unaddr = 0u;
     if (m) {
-        v = ld16<NT>(d.src_sh + (uint64_t)(16 * c));
+        const uint64_t p = d.src_sh + (uint64_t)(16 * e), lo = src_first(d), hi = src_last(d);
+        const uint64_t q = p < lo ? lo : (p > hi ? hi : p);
+        v = ld16<NT>(q);
+        if (p != q) v = byte_shift(v, (int32_t)(int64_t)(p - q));
         if (d.ctl & CTL_SRC_HOST) {
-            const uint32_t a = ld_u16((uint64_t)R.a16 + (uint64_t)((d.a_src + 16 * c) >> 3));
+            const uint32_t a = ld_a16((uint64_t)R.a16, a_bytes(R), d.a_src + 16 * e);
             ok = m & a;
             unaddr = m & ~a;
         } else {
@@ -292,21 +367,42 @@ __device__ __forceinline__ void acc_reset(Acc &a) { a.first = NONE; a.undef = 0;
 
 __device__ __forceinline__ void acc_min(Acc &a, int64_t i) { a.first = (uint64_t)i < a.first ? (uint64_t)i : a.first; }
 
-// Findings of source chunk c (checking only).
+// one 0x80 per non-zero byte of w
+__device__ __forceinline__ uint32_t nz80(uint32_t w) { return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u; }
+
+// Findings of a window whose byte 0 is the record's byte i0 (checking only).
+// A lane's windows ascend, so once it has a first fault below i0 only the
+// count is left to take (dense shadow: 4 words of 4 operations).
 __device__ __forceinline__ void src_findings(Acc &a, int64_t i0, u32x4 v, uint32_t ok, uint32_t unaddr)
 {
-    const uint32_t any = v.x | v.y | v.z | v.w;
     if (unaddr) {
+        stay_branched();
         a.flags |= CG_SRC_UNADDR;
         acc_min(a, i0 + __builtin_ctz(unaddr));
     }
-    if (any) {
+    if (v.x | v.y | v.z | v.w) {
+        stay_branched();
+        if (ok == 0xFFFFu && i0 >= 0 && a.first < (uint64_t)i0) {
+            a.flags |= CG_SRC_UNDEF;
+            a.undef += (uint64_t)(uint32_t)(__builtin_popcount(nz80(v.x)) + __builtin_popcount(nz80(v.y)) +
+                                            __builtin_popcount(nz80(v.z)) + __builtin_popcount(nz80(v.w)));
+            return;
+        }
         const uint32_t und = nz16(v) & ok;
         if (und) {
             a.flags |= CG_SRC_UNDEF;
             a.undef += (uint64_t)__builtin_popcount(und);
             acc_min(a, i0 + __builtin_ctz(und));
         }
+    }
+}
+
+__device__ __forceinline__ void dst_findings(Acc &a, int64_t i0, uint32_t unaddr)
+{
+    if (unaddr) {
+        stay_branched();
+        a.flags |= CG_DST_UNADDR;
+        acc_min(a, i0 + __builtin_ctz(unaddr));
     }
 }
 
@@ -330,180 +426,197 @@ __device__ __forceinline__ void flush_wave(Acc &a, cg_verdict *out, uint64_t t)
 // uniform mode: the whole wave works on units [k_begin, k_end) of one record
 // ---------------------------------------------------------------------------
 
-// Chunks 64 j + lane (j < U) of an interior iteration: V from vbase, source A
-// words from abase (SA), destination A words from dbase (DA); true when every
-// V byte of the wave's chunks is 0 and every A bit 1.
+// Windows 64 j + lane (j < U) of an interior iteration: V from vbase, A words
+// of the source (SA) and of the destination (DA) at byte 2 * window of abase /
+// dbase, their bits starting at bit ss / ds of the word.
 template <int U, bool NT, bool SA, bool DA>
-__device__ __forceinline__ bool clean_interior(uint64_t vbase, uint64_t abase, uint64_t dbase)
-{
-    const gcptr<u32x4> vp = reinterpret_cast<gcptr<u32x4>>(vbase);
-    const gcptr<uint16_t> ap = reinterpret_cast<gcptr<uint16_t>>(abase);
-    const gcptr<uint16_t> dp = reinterpret_cast<gcptr<uint16_t>>(dbase);
-    const uint32_t lane = lane_id();
-    u32x4 w[U];
-    uint32_t sa[U], da[U];
+struct Interior {
+    u32x4 v[U];
+    uint32_t a[U], da[U];
+    __device__ __forceinline__ Interior(uint64_t vbase, uint64_t abase, uint32_t ss, uint64_t dbase, uint32_t ds)
+    {
+        const uint32_t lane = lane_id();
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-        const uint32_t cr = 64u * j + lane;
-        if constexpr (NT) w[j] = __builtin_nontemporal_load(vp + cr);
-        else w[j] = vp[cr];
-        if constexpr (SA) sa[j] = ap[cr];
-        if constexpr (DA) da[j] = dp[cr];
-    }
-    uint32_t bad = 0;
+        for (int j = 0; j < U; ++j) {
+            const uint32_t w = 64u * j + lane;
+            v[j] = ld16<NT>(vbase + 16u * w);
+            if constexpr (SA) a[j] = *reinterpret_cast<gcptr<u32u>>(abase + 2u * w);
+            if constexpr (DA) da[j] = *reinterpret_cast<gcptr<u32u>>(dbase + 2u * w);
+        }
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-        bad |= w[j].x | w[j].y | w[j].z | w[j].w;
-        if constexpr (SA) bad |= sa[j] ^ 0xFFFFu;
-        if constexpr (DA) bad |= da[j] ^ 0xFFFFu;
+        for (int j = 0; j < U; ++j) {
+            a[j] = SA ? (a[j] >> ss) & 0xFFFFu : 0xFFFFu;
+            da[j] = DA ? (da[j] >> ds) & 0xFFFFu : 0xFFFFu;
+        }
     }
-    return __ballot(bad != 0u) == 0;
-}
-template <int U, bool NT, bool PROP>
-__device__ __forceinline__ void run_uniform(const DV &d, const Region &R, uint64_t k_begin, uint64_t k_end,
-                                            Acc &acc)
+    // findings: none when every V byte of the wave's windows is 0 and every A
+    // bit 1, which one test over all windows tells
+    __device__ __forceinline__ void check(int64_t i0, Acc &acc) const
+    {
+        uint32_t bad = 0;
+#pragma unroll
+        for (int j = 0; j < U; ++j) bad |= v[j].x | v[j].y | v[j].z | v[j].w | (a[j] ^ 0xFFFFu) | (da[j] ^ 0xFFFFu);
+        if (__ballot(bad != 0u) == 0) return;
+        const uint32_t lane = lane_id();
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint32_t w = 64u * j + lane;
+            src_findings(acc, i0 + 16 * w, v[j], a[j], a[j] ^ 0xFFFFu);
+            if constexpr (DA) dst_findings(acc, i0 + 16 * w, da[j] ^ 0xFFFFu);
+        }
+    }
+    // findings and stores, window 0's first byte being record byte i0 and
+    // going to address dst
+    __device__ __forceinline__ void carry(bool check, int64_t i0, uint64_t dst, Acc &acc) const
+    {
+        const uint32_t lane = lane_id();
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint32_t w = 64u * j + lane;
+            if (check) {
+                src_findings(acc, i0 + 16 * w, v[j], a[j], a[j] ^ 0xFFFFu);
+                if constexpr (DA) dst_findings(acc, i0 + 16 * w, da[j] ^ 0xFFFFu);
+            }
+            const u32x4 x = SA ? prop_val(v[j], a[j]) : v[j];
+            if (!DA || da[j] == 0xFFFFu) st16(dst + 16u * w, x);
+            else store_masked(dst + 16u * w, x, da[j]);
+        }
+    }
+};
+
+// Units [kb, kb + 64 G) of a record below k_end, by the whole wave, at its
+// edges: windows that are only partly valid, or not at all, are masked, and
+// loaded from clamped addresses (lanes without a valid byte read some valid
+// chunk and ignore it), so that all G loads go out back to back.
+template <int G, bool NT, bool PROP>
+__device__ __forceinline__ void run_edge(const DV &d, const Region &R, uint64_t kb, uint64_t k_end, Acc &acc)
 {
-    // Lane l of sub-iteration j handles unit kb + 64 j + l: destination chunk
-    // e = e0 + kb + 64 j + l and source chunk c = e - delta.  Per iteration all
-    // offsets are taken relative to the first unit, in 32 bits.  Loads are
-    // issued for every lane with the chunk index clamped into the range of
-    // chunks that hold valid bytes, so that all U loads go out back to back
-    // without branches; lanes whose own chunk has no valid byte ignore the data.
     const int32_t lane = (int32_t)lane_id();
     const bool check = (d.ctl & CTL_CHECK) != 0;
     const bool prop = PROP && (d.ctl & CTL_PROP) != 0;
     const bool dsta = (d.ctl & CTL_DST_A) != 0;
     const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
     const bool dst_host = (d.ctl & CTL_DST_HOST) != 0;
+    constexpr int32_t W = 16 * 64 * G;   // bytes worked
+    const int64_t eb = (int64_t)(d.e0 + kb);
+    const int64_t i0b = 16 * eb - (int64_t)d.o;
+    const int32_t vlo = clamp32(d.v_lo - i0b), vhi = clamp32(d.v_hi - i0b);
+    const int32_t dlo = clamp32(d.d_lo - i0b), dhi = clamp32(d.d_hi - i0b);
+    const int32_t kend = clamp32((int64_t)(k_end - kb));
+    u32x4 v[G];
+    uint32_t ok[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        v[j] = u32x4{0u, 0u, 0u, 0u};
+        ok[j] = 0u;
+    }
+    if (vlo < W && vhi > 0 && vhi > vlo) {   // some window holds a valid byte
+        const uint64_t vbase = d.src_sh + (uint64_t)(16 * eb);
+        const int32_t lo = clamp32((int64_t)(src_first(d) - vbase)), hi = clamp32((int64_t)(src_last(d) - vbase));
+        bool moved = false;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t p = 16 * (64 * j + lane);
+            const int32_t q = p < lo ? lo : (p > hi ? hi : p);
+            v[j] = ld16<NT>(vbase - 16u + (uint32_t)(q + 16));   // q >= -15
+            moved |= p != q;
+        }
+        if (src_host) {
+            const AWords A(R, d.a_src + 16 * eb);
+#pragma unroll
+            for (int j = 0; j < G; ++j) ok[j] = A.at(64 * j + lane);
+        } else {
+#pragma unroll
+            for (int j = 0; j < G; ++j) ok[j] = 0xFFFFu;
+        }
+        if (__ballot(moved)) {
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int32_t p = 16 * (64 * j + lane);
+                const int32_t q = p < lo ? lo : (p > hi ? hi : p);
+                if (p != q && p - q < 16 && q - p < 16) v[j] = byte_shift(v[j], p - q);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        const int32_t cr = 64 * j + lane;
+        const uint32_t m = cr < kend ? rmask32(vlo - 16 * cr, vhi - 16 * cr) : 0u;
+        const uint32_t un = m & ~ok[j];
+        ok[j] &= m;
+        if (check) src_findings(acc, i0b + 16 * cr, v[j], ok[j], un);
+    }
+    if ((dsta || prop) && dlo < W && dhi > 0) {
+        const uint64_t dbase = d.dst_sh + (uint64_t)(16 * eb);
+        const AWords A(R, d.a_dst + 16 * eb);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t cr = 64 * j + lane;
+            const uint32_t md = cr < kend ? rmask32(dlo - 16 * cr, dhi - 16 * cr) : 0u;
+            uint32_t wm = md;
+            if (dst_host) {
+                wm = md & A.at(cr);
+                if (check) dst_findings(acc, i0b + 16 * cr, md & ~wm);
+            }
+            if (prop && wm) store_masked(dbase + (uint64_t)(uint32_t)(16 * cr), prop_val(v[j], ok[j]), wm);
+        }
+    }
+}
+
+// The wave's iterations start at k_begin and are `step` units apart.  Lane l
+// of sub-iteration j handles unit kb + 64 j + l: window e = e0 + kb + 64 j + l
+// of both sides.  Per iteration all offsets are taken relative to the first
+// unit, in 32 bits.
+template <int U, bool NT, bool PROP>
+__device__ __forceinline__ void run_uniform(const DV &d, const Region &R, uint64_t k_begin, uint64_t k_end,
+                                            Acc &acc, uint64_t step = 64u * U)
+{
+    const bool check = (d.ctl & CTL_CHECK) != 0;
+    const bool prop = PROP && (d.ctl & CTL_PROP) != 0;
+    const bool dsta = (d.ctl & CTL_DST_A) != 0;
+    const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
+    const bool dst_host = (d.ctl & CTL_DST_HOST) != 0;
     const uint64_t a16b = (uint64_t)R.a16;
+    const int64_t nab = a_bytes(R);
+    constexpr int32_t W = 16 * 64 * U;   // bytes per iteration
+    constexpr int G = U < 2 ? 1 : 2;
+    k_begin = ufl64(k_begin);   // (in scalar registers, so that all the offsets below are)
+    k_end = ufl64(k_end);
+    step = ufl64(step);
 
-    for (uint64_t kb = k_begin; kb < k_end; kb += 64u * U) {
-        const int64_t cb = (int64_t)(d.e0 + kb) - (int64_t)d.delta;
-        const int64_t i0b = 16 * cb - (int64_t)d.phi;
-        const int32_t vlo = clamp32(d.v_lo - i0b), vhi = clamp32(d.v_hi - i0b);
-        const int32_t kend = clamp32((int64_t)(k_end - kb));
-        const int32_t clo = (vlo >> 4) > 0 ? (vlo >> 4) : 0;
-        const int32_t chi = ((vhi + 15) >> 4) < 64 * U ? ((vhi + 15) >> 4) : 64 * U;
-        const uint64_t vbase = d.src_sh + (uint64_t)(16 * cb);
-        const uint64_t abase = a16b + (uint64_t)((d.a_src + 16 * cb) >> 3);
-
-        // Interior iteration of a check (kernels built without propagation,
-        // whose register budget allows three waves per SIMD): every lane's U
-        // source chunks lie wholly inside the valid source range (and, for a
-        // host destination, its chunks inside the valid destination range), so
-        // no byte mask or index clamp is needed.  When every V byte is 0 and
-        // every A bit 1, the code below would find nothing and the iteration
-        // ends here; otherwise (rare) that code runs the iteration again and
-        // reports exactly.
-        if (!PROP && check && vlo <= 0 && vhi >= 16 * 64 * U && kend >= 64 * U) {
-            bool dfull = true;
-            uint64_t dbase = 0;
-            if (dsta) {
-                const int64_t eb = (int64_t)(d.e0 + kb);
-                const int64_t i0db = 16 * eb - (int64_t)d.psi;
-                dfull = clamp32(d.d_lo - i0db) <= 0 && clamp32(d.d_hi - i0db) >= 16 * 64 * U;
-                dbase = a16b + (uint64_t)((d.a_dst + 16 * eb) >> 3);
+    for (uint64_t kb = k_begin; kb < k_end; kb += step) {
+        const int64_t eb = (int64_t)(d.e0 + kb);
+        const int64_t i0b = 16 * eb - (int64_t)d.o;
+        // Interior iteration: every window lies wholly inside the valid source
+        // range and, where the destination is worked, inside its valid range
+        // (and the A words inside the bitmap), so no byte mask or clamp is
+        // needed.
+        const int64_t sbit = d.a_src + 16 * eb, dbit = d.a_dst + 16 * eb;
+        bool in = d.v_lo <= i0b && d.v_hi >= i0b + W && k_end - kb >= 64u * U;
+        if (src_host) in &= sbit >= 0 && ((sbit + W) >> 3) + 4 <= nab;
+        if (dsta || prop) in &= d.d_lo <= i0b && d.d_hi >= i0b + W;
+        if (dst_host && (dsta || prop)) in &= dbit >= 0 && ((dbit + W) >> 3) + 4 <= nab;
+        if (in && (PROP ? prop : check)) {
+            // (a host destination has a device source, a host source a device destination)
+            const uint64_t vbase = d.src_sh + (uint64_t)(16 * eb), dbase = d.dst_sh + (uint64_t)(16 * eb);
+            const uint64_t sab = a16b + (uint64_t)(sbit >> 3), dab = a16b + (uint64_t)(dbit >> 3);
+            const uint32_t ss = (uint32_t)sbit & 7u, ds = (uint32_t)dbit & 7u;
+            if constexpr (PROP) {
+                if (src_host) Interior<U, NT, true, false>(vbase, sab, ss, 0, 0).carry(check, i0b, dbase, acc);
+                else if (dst_host) Interior<U, NT, false, true>(vbase, 0, 0, dab, ds).carry(check, i0b, dbase, acc);
+                else Interior<U, NT, false, false>(vbase, 0, 0, 0, 0).carry(check, i0b, dbase, acc);
+            } else {
+                if (dsta) Interior<U, NT, false, true>(vbase, 0, 0, dab, ds).check(i0b, acc);
+                else if (src_host) Interior<U, NT, true, false>(vbase, sab, ss, 0, 0).check(i0b, acc);
+                else Interior<U, NT, false, false>(vbase, 0, 0, 0, 0).check(i0b, acc);
             }
-            if (dfull) {
-                // a host destination (D2H) has a device source; a host source
-                // (H2D) has a device destination
-                const bool clean = dsta ? clean_interior<U, NT, false, true>(vbase, abase, dbase)
-                                 : src_host ? clean_interior<U, NT, true, false>(vbase, abase, dbase)
-                                            : clean_interior<U, NT, false, false>(vbase, abase, dbase);
-                if (clean) continue;
-            }
+            continue;
         }
-
-        u32x4 v[U];
-        uint32_t ok[U], un[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            v[j] = u32x4{0u, 0u, 0u, 0u};
-            ok[j] = 0u;
-            un[j] = 0u;
-        }
-        if (chi > clo) {
-            uint32_t av[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int32_t cr = 64 * j + lane;
-                const int32_t cc = cr < clo ? clo : (cr >= chi ? chi - 1 : cr);
-                v[j] = ld16<NT>(vbase + (uint32_t)(16 * cc));
-                if (src_host) av[j] = ld_u16(abase + (uint32_t)(2 * cc));
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int32_t cr = 64 * j + lane;
-                const uint32_t m = cr < kend ? rmask32(vlo - 16 * cr, vhi - 16 * cr) : 0u;
-                if (src_host) {
-                    ok[j] = m & av[j];
-                    un[j] = m & ~av[j];
-                } else {
-                    ok[j] = m;
-                }
-            }
-        }
-        if (check) {
-#pragma unroll
-            for (int j = 0; j < U; ++j) src_findings(acc, i0b + 16 * (64 * j + lane), v[j], ok[j], un[j]);
-        }
-        if (dsta || prop) {
-            const int64_t eb = (int64_t)(d.e0 + kb);
-            const int64_t i0db = 16 * eb - (int64_t)d.psi;
-            const int32_t dlo = clamp32(d.d_lo - i0db), dhi = clamp32(d.d_hi - i0db);
-            const int32_t dclo = (dlo >> 4) > 0 ? (dlo >> 4) : 0;
-            const int32_t dchi = ((dhi + 15) >> 4) < 64 * U ? ((dhi + 15) >> 4) : 64 * U;
-            uint32_t ad[U];
-            if (dst_host && dchi > dclo) {
-                const uint64_t dbase = a16b + (uint64_t)((d.a_dst + 16 * eb) >> 3);
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    const int32_t cr = 64 * j + lane;
-                    const int32_t cc = cr < dclo ? dclo : (cr >= dchi ? dchi - 1 : cr);
-                    ad[j] = ld_u16(dbase + (uint32_t)(2 * cc));
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int32_t cr = 64 * j + lane;
-                const uint32_t md = (cr < kend && dchi > dclo) ? rmask32(dlo - 16 * cr, dhi - 16 * cr) : 0u;
-                uint32_t wm = md;
-                if (dst_host) {
-                    wm = md & ad[j];
-                    const uint32_t ud = md & ~ad[j];
-                    if (check && ud) {
-                        acc.flags |= CG_DST_UNADDR;
-                        acc_min(acc, i0db + 16 * cr + __builtin_ctz(ud));
-                    }
-                }
-                if (prop && d.s == 0) {
-                    // source and destination chunks coincide (equal phases)
-                    if (wm) store_masked(d.dst_sh + (uint64_t)(16 * eb) + (uint32_t)(16 * cr), prop_val(v[j], ok[j]), wm);
-                } else if (prop) {
-                    const u32x4 own = prop_val(v[j], ok[j]);
-                    u32x4 nxt;
-                    nxt.x = __shfl_down(own.x, 1);
-                    nxt.y = __shfl_down(own.y, 1);
-                    nxt.z = __shfl_down(own.z, 1);
-                    nxt.w = __shfl_down(own.w, 1);
-                    if (j + 1 < U) {
-                        const int jn = j + 1 < U ? j + 1 : j;
-                        const u32x4 g = prop_val(v[jn], ok[jn]);
-                        const uint32_t gx = __shfl(g.x, 0), gy = __shfl(g.y, 0), gz = __shfl(g.z, 0),
-                                       gw = __shfl(g.w, 0);
-                        if (lane == 63) nxt = u32x4{gx, gy, gz, gw};
-                    }
-                    const bool self = cr < kend && ((lane == 63 && j == U - 1) || cr + 1 >= kend);
-                    if (self) {
-                        u32x4 vn;
-                        uint32_t okn, unn;
-                        src_chunk<NT>(d, R, cb + cr + 1, vn, okn, unn);
-                        nxt = prop_val(vn, okn);
-                    }
-                    if (wm) store_masked(d.dst_sh + (uint64_t)(16 * eb) + (uint32_t)(16 * cr), window(own, nxt, d.s), wm);
-                }
-            }
-        }
+        // (two windows per lane at a time: four would cost the registers that
+        // let twice the waves run)
+#pragma nounroll
+        for (uint64_t k = kb; k < kb + 64u * U && k < k_end; k += 64u * G)
+            run_edge<G, NT, PROP>(d, R, k, k_end < kb + 64u * U ? k_end : kb + 64u * U, acc);
     }
 }
 
@@ -515,30 +628,19 @@ __device__ __forceinline__ void run_unit(const DV &d, const Region &R, uint64_t 
 {
     const bool check = (d.ctl & CTL_CHECK) != 0;
     const int64_t e = (int64_t)(d.e0 + k);
-    const int64_t c = e - (int64_t)d.delta;
+    const int64_t i0 = 16 * e - (int64_t)d.o;
     u32x4 v;
     uint32_t ok, un;
-    src_chunk<NT>(d, R, c, v, ok, un);
-    if (check) src_findings(acc, 16 * c - (int64_t)d.phi, v, ok, un);
+    src_window<NT>(d, R, e, v, ok, un);
+    if (check) src_findings(acc, i0, v, ok, un);
     if (d.ctl & (CTL_DST_A | CTL_PROP)) {
-        const int64_t i0d = 16 * e - (int64_t)d.psi;
-        const uint32_t md = rmask(d.d_lo - i0d, d.d_hi - i0d);
+        const uint32_t md = rmask(d.d_lo - i0, d.d_hi - i0);
         uint32_t wm = md;
         if ((d.ctl & CTL_DST_HOST) && md) {
-            const uint32_t a = ld_u16((uint64_t)R.a16 + (uint64_t)((d.a_dst + 16 * e) >> 3));
-            wm = md & a;
-            const uint32_t ud = md & ~a;
-            if (check && ud) {
-                acc.flags |= CG_DST_UNADDR;
-                acc_min(acc, i0d + __builtin_ctz(ud));
-            }
+            wm = md & ld_a16((uint64_t)R.a16, a_bytes(R), d.a_dst + 16 * e);
+            if (check) dst_findings(acc, i0, md & ~wm);
         }
-        if (PROP && (d.ctl & CTL_PROP) && wm) {
-            u32x4 vn;
-            uint32_t okn, unn;
-            src_chunk<NT>(d, R, c + 1, vn, okn, unn);
-            store_masked(d.dst_sh + (uint64_t)(16 * e), window(prop_val(v, ok), prop_val(vn, okn), d.s), wm);
-        }
+        if (PROP && (d.ctl & CTL_PROP) && wm) store_masked(d.dst_sh + (uint64_t)(16 * e), prop_val(v, ok), wm);
     }
 }
 
@@ -608,7 +710,7 @@ __device__ __forceinline__ uint32_t wave_add32(uint32_t x)
 // compared 64 entries at a time, so two rounds of independent loads take the
 // place of a chain of dependent ones.  Entries are sorted by base, so the
 // number of them at or below p is one past the last of them.
-__device__ int64_t table_lookup_wave(const TableView &tb, uint64_t p)
+__device__ __forceinline__ int64_t table_lookup_wave(const TableView &tb, uint64_t p)
 {
     if (tb.n == 0) return -1;
     const uint32_t lane = lane_id();
@@ -653,9 +755,10 @@ __device__ __forceinline__ bool dev_dst(const cg_transfer &r) { return r.kind <=
 // Decode record r, given the table entries holding its device source and
 // destination pointers (js, jd: -1 when none, or when the side is on the
 // host): its descriptor, its verdict's range-derived fields, and its number
-// of units (returned).
-__device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevState &st, int64_t js, int64_t jd,
-                                 Desc &ds, cg_verdict &v)
+// of units (returned).  With `row`, the record is a row that others follow at
+// any pitch: its windows start at its first byte (o = 0).
+__device__ __forceinline__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevState &st, int64_t js, int64_t jd,
+                                 Desc &ds, cg_verdict &v, bool row = false)
 {
     const uint64_t n = r.n;
     ds = Desc{};
@@ -671,7 +774,6 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
         const bool dst_host = r.kind == CG_D2H;
         const Region &R = st.region;
         uint64_t vlo = 0, vhi = 0, dlo = 0, dhi = 0, avail_s = 0, avail_d = 0;
-        uint32_t phi = 0, psi = 0;
         uint64_t src0 = 0, dst0 = 0;   // shadow address of byte 0 (when valid)
         bool src_ok = false, dst_ok = false;
         if (src_host) {
@@ -680,8 +782,7 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
             else if (vhi < n) { flags |= CG_SRC_UNADDR; first = first < vhi ? first : vhi; }
             src_ok = vhi > vlo;
             src0 = (uint64_t)R.v + (r.src - R.hb);
-            phi = (uint32_t)((r.src - R.hb) & 15u);
-            ds.a_src = (int64_t)((r.src - R.hb) - phi);
+            ds.a_src = (int64_t)(r.src - R.hb);
         } else {
             const int64_t j = js;
             if (j < 0) { flags |= CG_SRC_UNALLOC; first = 0; }
@@ -691,7 +792,6 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
                 vlo = 0;
                 vhi = n < avail_s ? n : avail_s;
                 src0 = st.pool + st.table.off[j] + (r.src - st.table.base[j]);
-                phi = (uint32_t)(src0 & 15u);
                 src_ok = true;
             }
         }
@@ -701,8 +801,7 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
             else if (dhi < n) { flags |= CG_DST_UNADDR; first = first < dhi ? first : dhi; }
             dst_ok = dhi > dlo;
             dst0 = (uint64_t)R.v + (r.dst - R.hb);
-            psi = (uint32_t)((r.dst - R.hb) & 15u);
-            ds.a_dst = (int64_t)((r.dst - R.hb) - psi);
+            ds.a_dst = (int64_t)(r.dst - R.hb);
         } else {
             const int64_t j = jd;
             if (j < 0) { flags |= CG_DST_UNALLOC; first = 0; }
@@ -712,7 +811,6 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
                 dlo = 0;
                 dhi = n < avail_d ? n : avail_d;
                 dst0 = st.pool + st.table.off[j] + (r.dst - st.table.base[j]);
-                psi = (uint32_t)(dst0 & 15u);
                 dst_ok = true;
             }
         }
@@ -728,31 +826,32 @@ __device__ uint64_t classify_rec(const cg_transfer &r, uint32_t mode, const DevS
         const bool dstwork = (prop || dsta) && dst_ok;
         vlo = clamp_scan(vlo); vhi = clamp_scan(vhi);
         dlo = clamp_scan(dlo); dhi = clamp_scan(dhi);
-        const uint32_t delta = (dstwork && phi < psi) ? 1u : 0u;
-        // unit ranges of the source and destination sides
+        // the windows align the destination when it is written, else the source
+        const uint32_t o = row ? 0u : (uint32_t)((prop && dst_ok) || !src_ok ? dst0 : src0) & 15u;
+        // windows of the source's and of the destination's valid bytes
         uint64_t e_lo = ~0ull, e_hi = 0;
         if (src_ok && vhi > vlo) {
-            const uint64_t c_lo = (vlo + phi) >> 4, c_hi = ((vhi - 1 + phi) >> 4) + 1;
-            e_lo = c_lo + delta;
-            e_hi = c_hi + delta;
-            // propagation needs every destination chunk, including those whose
+            e_lo = (vlo + o) >> 4;
+            e_hi = ((vhi - 1 + o) >> 4) + 1;
+            // propagation needs every destination window, including those whose
             // bytes come only from invalid source bytes (written as 0xFF)
         }
         if (dstwork && dhi > dlo) {
-            const uint64_t f_lo = (dlo + psi) >> 4, f_hi = ((dhi - 1 + psi) >> 4) + 1;
+            const uint64_t f_lo = (dlo + o) >> 4, f_hi = ((dhi - 1 + o) >> 4) + 1;
             e_lo = f_lo < e_lo ? f_lo : e_lo;
             e_hi = f_hi > e_hi ? f_hi : e_hi;
         }
         if (e_hi > e_lo) units = e_hi - e_lo; else e_lo = 0;
-        ds.src_sh = src0 - phi;
-        ds.dst_sh = dst0 - psi;
+        ds.src_sh = src0 - o;
+        ds.dst_sh = dst0 - o;
+        ds.a_src -= (int64_t)o;
+        ds.a_dst -= (int64_t)o;
         ds.v_lo = (int64_t)vlo; ds.v_hi = (int64_t)vhi;
         ds.d_lo = (int64_t)dlo; ds.d_hi = (int64_t)dhi;
         ds.e0 = e_lo;
         ds.units = units;
         ds.ctl = (src_host ? CTL_SRC_HOST : 0u) | (dst_host ? CTL_DST_HOST : 0u) | (check ? CTL_CHECK : 0u) |
-                 (prop && dst_ok ? CTL_PROP : 0u) | (dsta && dst_ok ? CTL_DST_A : 0u) |
-                 (phi << CTL_PHI_SHIFT) | (psi << CTL_PSI_SHIFT) | (delta ? CTL_DELTA : 0u);
+                 (prop && dst_ok ? CTL_PROP : 0u) | (dsta && dst_ok ? CTL_DST_A : 0u) | (o << CTL_O_SHIFT);
         if (!src_ok) { ds.v_lo = 0; ds.v_hi = 0; }
     }
     v.flags = flags;
@@ -781,14 +880,10 @@ __device__ __forceinline__ void mark_steps(const BatchArgs &a, int k, uint64_t l
 // and of a host destination
 __device__ __forceinline__ uint64_t src_space_off(const Desc &ds, const DevState &st)
 {
-    const uint32_t phi = (ds.ctl >> CTL_PHI_SHIFT) & 15u;
-    return (ds.ctl & CTL_SRC_HOST) ? (uint64_t)(ds.a_src + (int64_t)phi) : ds.src_sh + phi - st.pool;
+    return (ds.ctl & CTL_SRC_HOST) ? (uint64_t)(ds.a_src + (int64_t)desc_o(ds)) : ds.src_sh + desc_o(ds) - st.pool;
 }
 
-__device__ __forceinline__ uint64_t dst_space_off(const Desc &ds)
-{
-    return (uint64_t)(ds.a_dst + (int64_t)((ds.ctl >> CTL_PSI_SHIFT) & 15u));
-}
+__device__ __forceinline__ uint64_t dst_space_off(const Desc &ds) { return (uint64_t)(ds.a_dst + (int64_t)desc_o(ds)); }
 
 // the steps a transfer's index answer reads: its valid source bytes, and a
 // host destination's valid bytes
@@ -1006,7 +1101,7 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
             const int64_t js = dev_src(r0) ? table_lookup(st.table, top, r0.src) : -1;
             const int64_t jd = dev_dst(r0) ? table_lookup(st.table, top, r0.dst) : -1;
             cg_verdict v0;
-            const uint64_t u0 = classify_rec(r0, a.mode, st, js, jd, ds, v0);
+            classify_rec(r0, a.mode, st, js, jd, ds, v0, true);
             const Region &R = st.region;
             auto side_ok = [&](bool host, int64_t j, uint64_t p, uint64_t q) {
                 if (host) return R.hl > 0 && p >= R.hb && rows_inside(p, q, P.width, rows, R.hb, R.hb + R.hl);
@@ -1021,14 +1116,13 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
                 const uint64_t b = row_extent_bound(P, rows, st);
                 ext = b < ext ? b : ext;
             }
-            // rows that follow row 0 at pitches that keep the 16-byte phases
-            // all have row 0's units: no padding between rows
-            const bool step = uniform && ((P.spitch | P.dpitch) & 15u) == 0 && u0 > 0;
-            P.upr = step ? u0 : (ext + 14) / 16 + 2;
-            P.uniform = uniform ? (step ? kRowsStep : kRowsUniform) : 0u;
+            // rows that follow row 0 all have its units; any other row at most
+            // (ext + 14) / 16 + 2, the most any alignment gives
+            P.upr = uniform ? ds.units : (ext + 14) / 16 + 2;
+            P.uniform = uniform ? kRowsUniform : 0u;
             // rows back to back on every side the check reads: one transfer
             // (in the rows' allocations, so its lookups are row 0's)
-            if (step && !(a.mode & CG_PROPAGATE) && R2.spitch == R2.width &&
+            if (uniform && !(a.mode & CG_PROPAGATE) && R2.spitch == R2.width &&
                 (R2.kind != CG_D2H || R2.dpitch == R2.width)) {
                 const cg_transfer rc{P.src, P.dst, rows * P.width, P.kind, 0u};
                 cg_verdict vc;
@@ -1083,35 +1177,14 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
         }
 }
 
-// Row r's descriptor when the rows are uniform: row 0's shifted by the
-// pitches; the phases, and so the realignment and the unit range, are row r's.
-__device__ Desc row_desc(const Desc &d0, const Pitch &P, uint64_t r)
+// Row r's descriptor when the rows are uniform: row 0's moved by the pitches.
+__device__ __forceinline__ Desc row_desc(const Desc &d0, const Pitch &P, uint64_t r)
 {
-    const uint32_t phi0 = (d0.ctl >> CTL_PHI_SHIFT) & 15u, psi0 = (d0.ctl >> CTL_PSI_SHIFT) & 15u;
-    const uint64_t src0 = d0.src_sh + phi0 + r * P.spitch, dst0 = d0.dst_sh + psi0 + r * P.dpitch;
-    const uint32_t phi = (uint32_t)(src0 & 15u), psi = (uint32_t)(dst0 & 15u);
-    const bool dstwork = (d0.ctl & (CTL_PROP | CTL_DST_A)) != 0;
-    const uint32_t delta = (dstwork && phi < psi) ? 1u : 0u;
-    const uint64_t w = P.width;
-    uint64_t e_lo = delta, e_hi = ((w - 1 + phi) >> 4) + 1 + delta;
-    if (dstwork) {
-        const uint64_t f_hi = ((w - 1 + psi) >> 4) + 1;
-        e_lo = 0;
-        e_hi = f_hi > e_hi ? f_hi : e_hi;
-    }
     Desc x = d0;
-    x.src_sh = src0 - phi;
-    x.dst_sh = dst0 - psi;
-    x.v_lo = 0;
-    x.v_hi = (int64_t)w;
-    x.d_lo = 0;
-    x.d_hi = (int64_t)w;
-    x.a_src = d0.a_src + (int64_t)phi0 + (int64_t)(r * P.spitch) - (int64_t)phi;
-    x.a_dst = d0.a_dst + (int64_t)psi0 + (int64_t)(r * P.dpitch) - (int64_t)psi;
-    x.e0 = e_lo;
-    x.units = e_hi - e_lo;
-    x.ctl = (d0.ctl & ~((15u << CTL_PHI_SHIFT) | (15u << CTL_PSI_SHIFT) | CTL_DELTA)) | (phi << CTL_PHI_SHIFT) |
-            (psi << CTL_PSI_SHIFT) | (delta ? CTL_DELTA : 0u);
+    x.src_sh += r * P.spitch;
+    x.dst_sh += r * P.dpitch;
+    x.a_src += (int64_t)(r * P.spitch);
+    x.a_dst += (int64_t)(r * P.dpitch);
     return x;
 }
 
@@ -1248,10 +1321,16 @@ __global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_u
     }
     if (tid == 1023) {
         const uint64_t total = off + x;
-        // tiles of at most tile_units, small enough that every wave of the
-        // persistent grid gets a few of them, and few enough to fit tile_start
+        // tiles of tile_units while every wave of the persistent grid gets a
+        // few of them; otherwise one equal tile per wave, which the waves take
+        // by their index (354 MB in 2,000 requests: 20,000 tiles of the least
+        // size, taken one by one from a counter, 216 us; one per wave, 90 us);
+        // and few enough to fit tile_start
         uint64_t tu = tile_units;
-        while (tu > kMinTile && (total + tu - 1) / tu < 4ull * waves) tu >>= 1;
+        if ((total + tu - 1) / tu < waves) {
+            tu = ((total + waves - 1) / waves + 63) & ~63ull;
+            if (tu < kMinTile) tu = kMinTile;
+        }
         while ((total + tu - 1) / tu > a.tiles_cap) tu <<= 1;
         a.ctl->total_units = total;
         a.ctl->tile_units = tu;
@@ -1297,118 +1376,140 @@ __global__ void __launch_bounds__(256) k_tile_starts(BatchArgs a)
 // k_batched: persistent kernel over the tiles of the flattened unit space
 // ---------------------------------------------------------------------------
 
-// Units [k0, k1) of a pitched record whose rows step by the pitches with row
-// 0's phases (kRowsStep), checked without propagation, by the whole wave:
-// the rows' units follow each other with no gap (upr is a row's units), and
-// each lane works its own unit of an iteration in whichever row it falls, so
-// that short rows and row ends share iterations.  d is row 0's descriptor;
-// row r's source and destination lie r * spitch and r * dpitch further on.
-template <int U, bool NT>
-__device__ void run_rows_flat(const DV &d, const Pitch &P, const Region &R, uint64_t k0, uint64_t k1, Acc &acc)
+// Units [k0, k1) of a pitched record whose rows follow row 0 and have fewer
+// than kFlatUnits units each, by the whole wave: the rows' units follow each
+// other with no gap (upr is a row's units), and each lane works its own unit
+// of an iteration in whichever row it falls, so that short rows and row ends
+// share iterations.  d is row 0's descriptor (o = 0); row r's source and
+// destination lie r * spitch and r * dpitch further on, at any alignment.
+// Every byte of a row is valid; only a row's last window may pass its end.
+// Offsets are taken from the iteration's first row, in 32 bits (24-bit
+// products run at full rate), so the pitches are below kFlatPitch; rows
+// further apart are worked row by row, or one unit per lane when they are
+// short: each of them is in pages of its own, and their loads' latency bounds
+// either way.  333-byte rows at 512 bytes carried: 482 us one unit per lane
+// with its row's descriptor, 140 us flat.
+constexpr uint64_t kFlatUnits = 4096, kFlatPitch = 1u << 20;
+
+__device__ __forceinline__ bool rows_flat(const Pitch &P)
+{
+    return P.uniform == kRowsUniform && P.upr < kFlatUnits && (P.spitch | P.dpitch) < kFlatPitch;
+}
+
+template <int U, bool NT, bool PROP>
+__device__ __forceinline__ void run_rows_flat(const DV &d, const Pitch &P, const Region &R, uint64_t k0, uint64_t k1,
+                                              Acc &acc)
 {
     const uint32_t lane = lane_id();
-    const uint64_t ur = P.upr;
+    const uint32_t ur = (uint32_t)P.upr;
+    const uint32_t inv = ufl32((uint32_t)(0xFFFFFFFFu / ur) + 1u);   // n * inv >> 32 = n / ur for n < 2^13 (ur > 1)
+    const uint32_t width = (uint32_t)P.width, sp = (uint32_t)P.spitch, dp = (uint32_t)P.dpitch;
+    const bool check = (d.ctl & CTL_CHECK) != 0;
+    const bool prop = PROP && (d.ctl & CTL_PROP) != 0;
     const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
-    const bool dsta = (d.ctl & CTL_DST_A) != 0;
-    const uint64_t a16b = (uint64_t)R.a16;
-    uint64_t rb = k0 / ur, jb = k0 - rb * ur;   // row and unit of the iteration's first unit
+    const bool dst_host = (d.ctl & CTL_DST_HOST) != 0;
+    const bool dwork = prop || (d.ctl & CTL_DST_A) != 0;
+    // the last row's last chunk: no load passes it
+    const uint64_t last = (d.src_sh + (P.rows - 1) * P.spitch + P.width - 1) & ~15ull;
+    k0 = ufl64(k0);
+    k1 = ufl64(k1);
+    uint64_t rb = ufl64(k0 / ur);
+    uint32_t jb = ufl32((uint32_t)(k0 - rb * ur));   // row and unit of the iteration's first unit
     for (uint64_t kb = k0; kb < k1; kb += 64u * U) {
+        const uint64_t sb = d.src_sh + rb * sp, db = d.dst_sh + rb * dp;
+        const uint32_t left = k1 - kb < 64u * U ? (uint32_t)(k1 - kb) : 64u * U;
+        const int32_t lrel = clamp32((int64_t)(last - sb));   // at least -15
         u32x4 v[U];
-        uint32_t ms[U], as[U], md[U], ad[U];
-        int64_t fs[U], fd[U] = {};   // record byte index of byte 0 of the source / destination chunk
+        uint32_t ok[U], m[U], x[U], q[U];
+        bool moved = false;
 #pragma unroll
         for (int j = 0; j < U; ++j) {
+            // (lanes past the end work the last unit again and keep nothing)
             const uint32_t c = 64u * j + lane;
-            uint64_t r = rb, q = jb + c;
-            if (q >= ur) {
-                // ur >= 64 U: q < 2 ur; else q < ur + 64 U, small
-                const uint64_t x = ur >= 64u * U ? 1u : (uint64_t)((uint32_t)q / (uint32_t)ur);
-                r += x;
-                q -= x * ur;
-            }
-            const bool live = kb + c < k1;
-            const int64_t cs = (int64_t)(d.e0 + q) - (int64_t)d.delta;
-            const int64_t i0 = 16 * cs - (int64_t)d.phi;
-            const int64_t base = (int64_t)(r * P.width);
-            fs[j] = base + i0;
-            ms[j] = live ? rmask(d.v_lo - i0, d.v_hi - i0) : 0u;
-            v[j] = u32x4{0u, 0u, 0u, 0u};
-            as[j] = 0xFFFFu;
-            if (ms[j]) {
-                v[j] = ld16<NT>(d.src_sh + r * P.spitch + (uint64_t)(16 * cs));
-                if (src_host) as[j] = ld_u16(a16b + (((uint64_t)(d.a_src + 16 * cs) + r * P.spitch) >> 3));
-            }
-            md[j] = 0u;
-            ad[j] = 0xFFFFu;
-            if (dsta) {
-                const int64_t e = (int64_t)(d.e0 + q);
-                const int64_t i0d = 16 * e - (int64_t)d.psi;
-                fd[j] = base + i0d;
-                md[j] = live ? rmask(d.d_lo - i0d, d.d_hi - i0d) : 0u;
-                if (md[j]) ad[j] = ld_u16(a16b + (((uint64_t)(d.a_dst + 16 * e) + r * P.dpitch) >> 3));
+            const uint32_t n = jb + (c < left ? c : left - 1);
+            x[j] = ur > 1 ? __umulhi(n, inv) : n;   // rows past rb
+            q[j] = n - __umul24(x[j], ur);
+            const int32_t rel = (int32_t)(__umul24(x[j], sp) + 16u * q[j]);
+            const int32_t y = rel < lrel ? rel : lrel;
+            v[j] = ld16<NT>(sb - 16u + (uint32_t)(y + 16));
+            moved |= y != rel;
+        }
+        if (src_host) {
+            const AWords A(R, d.a_src + (int64_t)(rb * sp));
+#pragma unroll
+            for (int j = 0; j < U; ++j) ok[j] = A.bits((int32_t)(__umul24(x[j], sp) + 16u * q[j]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) ok[j] = 0xFFFFu;
+        }
+        if (__ballot(moved)) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int32_t s = (int32_t)(__umul24(x[j], sp) + 16u * q[j]) - lrel;
+                if (s > 0 && s < 16) v[j] = byte_shift(v[j], s);
             }
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            src_findings(acc, fs[j], v[j], ms[j] & as[j], ms[j] & ~as[j]);
-            const uint32_t ud = md[j] & ~ad[j];
-            if (dsta && ud) {
-                acc.flags |= CG_DST_UNADDR;
-                acc_min(acc, fd[j] + __builtin_ctz(ud));
+            const uint32_t rest = width - 16u * q[j];   // bytes of the row from this window on
+            m[j] = 64u * j + lane < left ? (rest >= 16u ? 0xFFFFu : (1u << rest) - 1u) : 0u;
+            const uint32_t un = m[j] & ~ok[j];
+            ok[j] &= m[j];
+            if (check && ((v[j].x | v[j].y | v[j].z | v[j].w) || un))
+                src_findings(acc, (int64_t)((rb + x[j]) * width + 16u * q[j]), v[j], ok[j], un);
+        }
+        if (dwork) {
+            const AWords A(R, d.a_dst + (int64_t)(rb * dp));
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const uint32_t rel = __umul24(x[j], dp) + 16u * q[j];
+                uint32_t wm = m[j];
+                if (dst_host) {
+                    wm &= A.bits((int32_t)rel);
+                    if (check) dst_findings(acc, (int64_t)((rb + x[j]) * width + 16u * q[j]), m[j] & ~wm);
+                }
+                if (prop && wm) store_masked(db + rel, prop_val(v[j], ok[j]), wm);
             }
         }
-        jb += 64u * U;
-        if (jb >= ur) {
-            const uint64_t x = ur >= 64u * U ? 1u : (uint64_t)((uint32_t)jb / (uint32_t)ur);
-            rb += x;
-            jb -= x * ur;
-        }
+        const uint32_t n = jb + 64u * U, dx = ur > 1 ? __umulhi(n, inv) : n;
+        rb += ufl32(dx);
+        jb = ufl32(n - dx * ur);
     }
 }
 
-// Units [k0, k1) of pitched position t, by the whole wave: row by row, each
-// row's own units through the wave-uniform loop; rows that do not follow row
-// 0 are looked up (64 table entries per step) and classified here, and their
-// range-derived flags join the record's (OR and min: a row worked in parts by
-// several waves adds them more than once to the same effect).
+// Units [k0, k1) of pitched position t, by the whole wave: rows that follow
+// row 0 flat, or, when they are long, row by row through the wave-uniform
+// loop; rows that do not follow row 0 are looked up (64 table entries per
+// step) and classified here, and their range-derived flags join the record's
+// (OR and min: a row worked in parts by several waves adds them more than
+// once to the same effect).
 template <int U, bool NT, bool PROP>
-__device__ void run_pitched(const BatchArgs &a, const DevState *st, uint64_t t, uint64_t k0, uint64_t k1, Acc &acc)
+__device__ __forceinline__ void run_pitched(const BatchArgs &a, const Region &R, uint64_t t, uint64_t k0, uint64_t k1, Acc &acc)
 {
-    const Pitch &Pg = a.pitch[t];
-    Pitch P;
-    P.src = ufl64(Pg.src); P.dst = ufl64(Pg.dst); P.width = ufl64(Pg.width); P.rows = ufl64(Pg.rows);
-    P.spitch = ufl64(Pg.spitch); P.dpitch = ufl64(Pg.dpitch); P.upr = ufl64(Pg.upr);
-    P.kind = ufl32(Pg.kind); P.uniform = ufl32(Pg.uniform);
-    const Desc d0 = a.desc[t];
-    if (!PROP && P.uniform == kRowsContig) {   // (made only for checks without propagation)
-        run_uniform<U, NT, false>(dv_uniform(d0), st->region, k0, k1, acc);
+    const Pitch P = ld_uniform(a.pitch + t);
+    const DV d0 = load_desc_uniform(a.desc, t);
+    if (rows_flat(P)) {
+        // (two windows per lane at most: each has a row's worth of indices)
+        run_rows_flat<(U > 2 ? 2 : U), NT, PROP>(d0, P, R, k0, k1, acc);
         return;
     }
-    // rows shorter than 64 units share iterations (at most 4 chunks per
-    // lane: every lane keeps a row's worth of indices for each); longer rows
-    // go row by row, their interiors through the unmasked loads
-    constexpr int UF = U > 4 ? 4 : U;
-    if (!PROP && P.uniform == kRowsStep && P.upr < 64u) {
-        run_rows_flat<UF, NT>(dv_uniform(d0), P, st->region, k0, k1, acc);
+    if (P.uniform == kRowsContig) {   // (made only for checks without propagation)
+        run_uniform<U, NT, PROP>(d0, R, k0, k1, acc);
         return;
     }
+    const DevState *st = a.st;
     const uint64_t r0 = k0 / P.upr;
-    // kRowsStep: each next row's descriptor is the last one's moved by the pitches
-    DV ds = dv_uniform(row_desc(d0, P, r0));
     for (uint64_t r = r0; r * P.upr < k1; ++r) {
         const uint64_t j0 = (k0 > r * P.upr ? k0 : r * P.upr) - r * P.upr;
         const uint64_t j1 = (k1 < (r + 1) * P.upr ? k1 : (r + 1) * P.upr) - r * P.upr;
         uint32_t rflags = 0;
         uint64_t rfirst = NONE;
-        DV d;
-        if (P.uniform == kRowsStep) {
-            d = ds;
-            ds.src_sh += P.spitch;
-            ds.dst_sh += P.dpitch;
-            ds.a_src += (int64_t)P.spitch;
-            ds.a_dst += (int64_t)P.dpitch;
-        } else if (P.uniform) {
-            d = dv_uniform(row_desc(d0, P, r));
+        DV d = d0;
+        if (P.uniform) {
+            d.src_sh += r * P.spitch;
+            d.dst_sh += r * P.dpitch;
+            d.a_src += (int64_t)(r * P.spitch);
+            d.a_dst += (int64_t)(r * P.dpitch);
         } else {
             const cg_transfer row = row_record(P, r);
             const int64_t js = dev_src(row) ? table_lookup_wave(st->table, row.src) : -1;
@@ -1423,23 +1524,24 @@ __device__ void run_pitched(const BatchArgs &a, const DevState *st, uint64_t t, 
         Acc ra;
         acc_reset(ra);
         const uint64_t e = j1 < d.units ? j1 : d.units;
-        if (e > j0) run_uniform<U, NT, PROP>(d, st->region, j0, e, ra);
+        if (e > j0) run_uniform<U, NT, PROP>(d, R, j0, e, ra);
         acc_add_row(acc, ra, rflags, rfirst, r * P.width);
     }
 }
 
 // Unit k of pitched position t, by one lane (short rows, tile ends).
 template <bool NT, bool PROP>
-__device__ void run_unit_pitched(const BatchArgs &a, const DevState *st, uint64_t t, uint64_t k, Acc &acc)
+__device__ __forceinline__ void run_unit_pitched(const BatchArgs &a, const Region &R, uint64_t t, uint64_t k, Acc &acc)
 {
+    const DevState *st = a.st;
     const Pitch P = a.pitch[t];
     if (P.upr == 0) return;   // no rows, or a bad kind: nothing to work
     if (!PROP && P.uniform == kRowsContig) {
         const DV d = load_desc(a.desc, t);
-        if (k < d.units) run_unit<NT, false>(d, st->region, k, acc);
+        if (k < d.units) run_unit<NT, false>(d, R, k, acc);
         return;
     }
-    const uint64_t r = k / P.upr, j = k - r * P.upr;
+    const uint64_t r = (k | P.upr) >> 32 ? k / P.upr : (uint32_t)k / (uint32_t)P.upr, j = k - r * P.upr;
     uint32_t rflags = 0;
     uint64_t rfirst = NONE;
     Desc x;
@@ -1457,7 +1559,7 @@ __device__ void run_unit_pitched(const BatchArgs &a, const DevState *st, uint64_
     const DV d = make_dv(x);
     Acc ra;
     acc_reset(ra);
-    if (j < d.units) run_unit<NT, PROP>(d, st->region, j, ra);
+    if (j < d.units) run_unit<NT, PROP>(d, R, j, ra);
     acc_add_row(acc, ra, rflags, rfirst, r * P.width);
 }
 
@@ -1488,7 +1590,7 @@ __device__ void batched_loop(const BatchArgs &a)
     const uint64_t tu = ufl64(a.ctl->tile_units);
     const uint64_t total = ufl64(a.ctl->total_units);
     const uint64_t T = a.count;
-    const Region R = a.st->region;
+    const Region R = ld_uniform(&a.st->region);
     Acc acc;
     acc_reset(acc);
     // Tiles are split into kXcds contiguous chunks, chunk x worked by the
@@ -1536,52 +1638,28 @@ __device__ void batched_loop(const BatchArgs &a)
         uint64_t u = (uint64_t)j * tu;
         const uint64_t u_end = (u + tu < total) ? u + tu : total;
         uint64_t t = ufl32(a.tile_start[j]);
-        // record t's units [pt, pt1) and, once loaded, its descriptor d; when a
-        // record is finished by the wave-uniform loop, the next record's
-        // metadata is loaded together with this record's data, so that
-        // mid-size records do not pay two round trips each
-        uint64_t pt = ufl64(a.prefix[t]), pt1 = ufl64(a.prefix[t + 1]);
-        bool have_d = false;
-        DV d = make_dv(Desc{});
+        uint64_t pt = ld_uniform(a.prefix + t), pt1 = ld_uniform(a.prefix + t + 1);   // record t's units
         while (u < u_end) {
             // a run of 64 units or more goes through the wave-uniform loop whole
             // (its last iteration may be partial); shorter runs, which may hold
             // several records, go one unit per lane
             const uint64_t seg_end = pt1 < u_end ? pt1 : u_end;
             uint64_t nfull = seg_end - u >= 64 ? seg_end - u : 0;
-            // pitched positions of short rows go one unit per lane (many rows
-            // per wave), unless their rows share the wave's iterations
+            // short rows that are not worked flat go one unit per lane (many
+            // rows per wave); all others share the wave's iterations
             if constexpr (PITCH) {
-                const uint32_t un = ufl32(a.pitch[t].uniform);
-                if (nfull && ufl64(a.pitch[t].upr) < 64 && un != kRowsContig && (PROP || un != kRowsStep))
-                    nfull = 0;
+                const Pitch P = ld_uniform(a.pitch + t);
+                if (nfull && P.upr < 64 && P.uniform != kRowsContig && !rows_flat(P)) nfull = 0;
             }
             if (nfull) {
-                if (!have_d) d = load_desc_uniform(a.desc, t);
-                const bool ahead = u + nfull == pt1 && u + nfull < u_end && t + 1 < T;
-                uint64_t npt1 = pt1;
-                DV nd = d;
-                if (ahead) {
-                    npt1 = ufl64(a.prefix[t + 2]);
-                    nd = load_desc_uniform(a.desc, t + 1);
-                }
-                if constexpr (PITCH) run_pitched<U, NT, PROP>(a, a.st, t, u - pt, u - pt + nfull, acc);
-                else run_uniform<U, NT, PROP>(d, R, u - pt, u - pt + nfull, acc);
-                if (a.out) flush_wave(acc, a.out, a.perm ? ufl32(a.perm[t]) : t);
+                if constexpr (PITCH) run_pitched<U, NT, PROP>(a, R, t, u - pt, u - pt + nfull, acc);
+                else run_uniform<U, NT, PROP>(load_desc_uniform(a.desc, t), R, u - pt, u - pt + nfull, acc);
+                if (a.out) flush_wave(acc, a.out, a.perm ? ld_uniform(a.perm + t) : t);
                 u += nfull;
-                if (u == pt1) {
+                if (u == pt1 && u < u_end) {
                     ++t;
                     pt = pt1;
-                    if (ahead) {
-                        pt1 = npt1;
-                        d = nd;
-                        have_d = true;
-                    } else {
-                        if (u < u_end) pt1 = ufl64(a.prefix[t + 1]);
-                        have_d = false;
-                    }
-                } else {
-                    have_d = true;
+                    pt1 = ld_uniform(a.prefix + t + 1);
                 }
                 continue;
             }
@@ -1589,17 +1667,21 @@ __device__ void batched_loop(const BatchArgs &a)
             const uint64_t g_end = (u + 64 < u_end) ? u + 64 : u_end;
             const uint64_t ul = u + lane;
             const bool act = ul < g_end;
-            uint64_t lo = t, hi = (t + 64 < T - 1) ? t + 64 : T - 1;
-            while (lo < hi) {
-                const uint64_t mid = (lo + hi + 1) >> 1;
-                if (a.prefix[mid] <= ul) lo = mid; else hi = mid - 1;
-            }
-            const uint64_t tl = lo;
+            // each lane's record: lane l looks at where record t + l starts; the
+            // starts inside the group, as bits, count the records before a unit
+            // (weights are at least 1, so at most 64 records meet the group)
+            const uint64_t mine = a.prefix[t + lane < T ? t + lane : T];
+            const uint64_t rel = mine - u;   // (wraps for t itself, which starts at or before u)
+            const uint64_t starts = wave_or64(lane > 0 && rel < 64 ? 1ull << rel : 0ull);
+            const uint32_t before = (uint32_t)__builtin_popcountll(starts & ((2ull << lane) - 1ull));
+            const uint64_t tl = t + before;
+            const uint64_t pl = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(mine >> 32), (int)before) << 32) |
+                                (uint32_t)__shfl((int)(uint32_t)mine, (int)before);
             if (PITCH && act) {
-                run_unit_pitched<NT, PROP>(a, a.st, tl, ul - a.prefix[tl], acc);
+                run_unit_pitched<NT, PROP>(a, R, tl, ul - pl, acc);
             } else if (act) {
                 const DV d = load_desc(a.desc, tl);
-                const uint64_t k = ul - a.prefix[tl];
+                const uint64_t k = ul - pl;
                 if (k < d.units) run_unit<NT, PROP>(d, R, k, acc);
             }
             if (a.out && __ballot(acc.flags != 0u))
@@ -1607,10 +1689,9 @@ __device__ void batched_loop(const BatchArgs &a)
             else acc_reset(acc);
             if (g_end < u_end) {
                 const uint64_t t63 = ufl64(__shfl(tl, 63));
-                t = (ufl64(a.prefix[t63 + 1]) <= g_end) ? t63 + 1 : t63;
-                pt = ufl64(a.prefix[t]);
-                pt1 = ufl64(a.prefix[t + 1]);
-                have_d = false;
+                t = (ld_uniform(a.prefix + t63 + 1) <= g_end) ? t63 + 1 : t63;
+                pt = ld_uniform(a.prefix + t);
+                pt1 = ld_uniform(a.prefix + t + 1);
             }
             u = g_end;
         }
@@ -1751,12 +1832,11 @@ __device__ void host_loop(const BatchArgs &a, const uint64_t *meta, int claim, u
         const uint32_t np = (uint32_t)(p_end - q0 < tp ? p_end - q0 : tp);
         for (uint32_t t = threadIdx.x; t < np; t += blockDim.x) {
             const Desc d = a.desc[q0 + t];
-            const uint32_t phi = (d.ctl >> CTL_PHI_SHIFT) & 15u;
-            const int64_t e = (int64_t)d.e0 - ((d.ctl & CTL_DELTA) ? 1 : 0);
+            const int64_t e = (int64_t)d.e0;   // (a check's windows are aligned source chunks)
             HostPos h;
             h.c_lo = (int64_t)(d.src_sh >> 4) + e;
             h.c_hi = h.c_lo + (int64_t)d.units;
-            h.i0 = 16 * e - (int64_t)phi;
+            h.i0 = 16 * e - (int64_t)desc_o(d);
             h.v_lo = d.v_lo;
             h.v_hi = d.v_hi;
             h.blk = (uint64_t)h.c_lo >> (lb - 4);
@@ -1869,7 +1949,7 @@ __global__ void __launch_bounds__(512) k_plain(BatchArgs a, uint64_t t, uint64_t
     const DV d = load_desc_uniform(a.desc, t);
     Acc acc;
     acc_reset(acc);
-    run_uniform<U, NT, PROP>(d, a.st->region, k0, k1, acc);
+    run_uniform<U, NT, PROP>(d, ld_uniform(&a.st->region), k0, k1, acc);
     if (a.out) flush_wave(acc, a.out, t);
 }
 
@@ -1893,14 +1973,14 @@ __global__ void __launch_bounds__(512) k_plain(BatchArgs a, uint64_t t, uint64_t
 // call needs no clearing.
 
 template <int U, bool NT, bool PROP>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PROP ? 1 : 3)))
+__global__ void __launch_bounds__(1024)
 k_small(BatchArgs a, SmallAcc *acc, uint32_t bpr)
 {
     __shared__ Desc sd;
     __shared__ cg_verdict sv;
     __shared__ uint64_t su;
-    __shared__ uint64_t wfirst[8], wund[8];
-    __shared__ uint32_t wfl[8];
+    __shared__ uint64_t wfirst[16], wund[16];
+    __shared__ uint32_t wfl[16];
     __shared__ int64_t sj[2];   // the source's and the destination's allocation (-1: none)
     const uint32_t lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const uint64_t t = blockIdx.x / bpr;
@@ -1929,18 +2009,15 @@ k_small(BatchArgs a, SmallAcc *acc, uint32_t bpr)
     }
     __syncthreads();
     const uint64_t units = su;
-    // this block's units, then this wave's, in whole iterations of 64 units
-    const uint64_t per_b = ((units + nb - 1) / nb + 63) & ~63ull;
-    const uint64_t b0 = (uint64_t)b * per_b < units ? (uint64_t)b * per_b : units;
-    const uint64_t b1 = b0 + per_b < units ? b0 + per_b : units;
-    const uint64_t per_w = ((b1 - b0 + nw - 1) / nw + 63) & ~63ull;
-    const uint64_t k0 = b0 + wid * per_w < b1 ? b0 + wid * per_w : b1;
-    const uint64_t k1 = k0 + per_w < b1 ? k0 + per_w : b1;
+    // the record's iterations dealt out to its blocks' waves in turn, so that
+    // all of them work side by side on one stretch of the shadow (2 GiB carried
+    // by one stretch per wave: 850 us in a plain copy, 780 dealt out)
+    const uint64_t k0 = ((uint64_t)b * nw + wid) * 64u * U;
     Acc ac;
     acc_reset(ac);
-    if (k1 > k0) {
-        const DV d = load_desc_uniform(&sd, 0);
-        run_uniform<U, NT, PROP>(d, st->region, k0, k1, ac);
+    if (k0 < units) {
+        const DV d = dv_uniform(sd);
+        run_uniform<U, NT, PROP>(d, ld_uniform(&st->region), k0, units, ac, (uint64_t)nb * nw * 64u * U);
     }
     if (!a.out) return;   // propagation only: no verdict (uniform over the grid)
     uint64_t f = NONE, u = 0;
@@ -2109,6 +2186,15 @@ hipError_t launch_classify_2d(const BatchArgs &a, const cg_transfer2d *recs2d, P
     return hipGetLastError();
 }
 
+// Workgroups of the scan kernel: four times the persistent grid the launch
+// shape asks for (at most 16 of 256 threads per CU), so that a batch worked as
+// one tile per wave is levelled out by the hardware's own dispatch.
+uint32_t scan_grid(const LaunchShape &sh)
+{
+    const uint32_t most = sh.cus * 16u * 256u / sh.block;
+    return sh.grid >= most ? sh.grid : std::min(4u * sh.grid, most);
+}
+
 hipError_t launch_scan_sums(const BatchArgs &a, uint32_t tile_units, uint32_t waves, hipStream_t s)
 {
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, a, tile_units, waves);
@@ -2139,9 +2225,9 @@ template <int U, bool NT>
 static void launch_batched_t(const BatchArgs &a, const LaunchShape &sh, hipStream_t s)
 {
     if (a.pitch && (a.mode & CG_PROPAGATE)) {
-        hipLaunchKernelGGL((k_batched_2d<U, NT, true>), dim3(sh.grid), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched_2d<U, NT, true>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     } else if (a.pitch) {
-        hipLaunchKernelGGL((k_batched_2d<U, NT, false>), dim3(sh.grid), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched_2d<U, NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     } else if (a.lds_meta && sh.lds_after) {
         BatchArgs d = a;
         d.lds_meta = nullptr;
@@ -2150,9 +2236,9 @@ static void launch_batched_t(const BatchArgs &a, const LaunchShape &sh, hipStrea
     } else if (a.lds_meta)
         hipLaunchKernelGGL((k_batched_lds<U, NT>), dim3(sh.grid), dim3(sh.block), 0, s, a);
     else if (a.mode & CG_PROPAGATE)
-        hipLaunchKernelGGL((k_batched<U, NT, true>), dim3(sh.grid), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched<U, NT, true>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     else
-        hipLaunchKernelGGL((k_batched<U, NT, false>), dim3(sh.grid), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched<U, NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
 }
 
 template <int U, bool NT>
@@ -2195,7 +2281,7 @@ static void launch_small_t(const BatchArgs &a, SmallAcc *acc, uint32_t bpr, uint
 
 hipError_t launch_small(const BatchArgs &a, SmallAcc *acc, uint32_t bpr, const LaunchShape &sh, hipStream_t s)
 {
-    if (a.count == 0 || bpr == 0 || a.count * bpr > 0x7FFFFFFFull || sh.block > 512 || sh.block % 64)
+    if (a.count == 0 || bpr == 0 || a.count * bpr > 0x7FFFFFFFull || sh.block > 1024 || sh.block % 64)
         return hipErrorInvalidValue;
     XC_DISPATCH(launch_small_t, a, acc, bpr, sh.block, s);
     return hipGetLastError();

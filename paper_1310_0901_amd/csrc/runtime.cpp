@@ -593,7 +593,7 @@ hipError_t prepare_stage(const BatchArgs &a, const LaunchShape &sh, hipStream_t 
     }
     if (sp && sp->seg && (e = launch_segments(sp->g, *sp->sort, a, const_cast<uint32_t *>(a.perm), s)) != hipSuccess)
         return e;
-    if ((e = launch_scan_sums(a, sh.tile_units, sh.grid * (sh.block / 64), s)) != hipSuccess) return e;
+    if ((e = launch_scan_sums(a, sh.tile_units, (a.lds_meta ? sh.grid : scan_grid(sh)) * (sh.block / 64), s)) != hipSuccess) return e;
     return launch_prefix_tiles(a, s);
 }
 
@@ -763,11 +763,14 @@ int debug_conflicts(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, hipS
 
 int note_use(cg_ctx *c, hipStream_t s);
 
-// Batches of at least reorder_min records and at most kSegMaxRecords are
-// worked as source-block segments unless the caller keeps the given order.
+// Checks without propagation of at least reorder_min records and at most
+// kSegMaxRecords are worked as source-block segments unless the caller keeps
+// the given order.  (A batch that propagates writes as many bytes as it reads,
+// so re-reads saved are worth little: 65,536 pieces of 16 B to 64 KiB took
+// 880 us as segments, 460 us in their order.)
 bool segmented(const cg_ctx *c, uint64_t count, uint32_t mode)
 {
-    return !(mode & (CG_PLAIN | CG_KEEP_ORDER)) && count >= 1 && count >= c->reorder_min && count <= kSegMaxRecords;
+    return !(mode & (CG_PLAIN | CG_KEEP_ORDER | CG_PROPAGATE)) && count >= 1 && count >= c->reorder_min && count <= kSegMaxRecords;
 }
 
 // Segment buffers for `count` records; the positions (w->cap) are already
@@ -844,6 +847,18 @@ void set_index_args(BatchArgs &a, const Workspace *w)
         a.index_mark[k] = xs[k]->smark;
         a.mark_cap[k] = xs[k]->steps_cap;
     }
+}
+
+// Launch shape of a one-launch batch: blocks of 1,024 threads, so that one
+// block works a 64 KiB record in one iteration of its waves (64 such records:
+// 29.8 us per call with 256 threads, 26.1 with 1,024; 2 GiB carried in one
+// record: 966 and 822 us), and loads as a check's, since few records share
+// their sources.
+LaunchShape small_shape(const cg_ctx *c, LaunchShape sh)
+{
+    sh.block = 1024;
+    sh.nontemporal = c->tuning.nontemporal;
+    return sh;
 }
 
 // Blocks per record of a small batch, at most: `hint`, or else about 8
@@ -931,7 +946,8 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
         // few records: one launch, no preparation kernels
         TimingPair *tp = c->timing ? next_pair(c) : nullptr;
         if (tp) HIPTRY(c, hipEventRecord(tp->a, s));
-        HIPTRY(c, launch_small(a, w->small, small_bpr(c, count, sh, bpr), sh, s));
+        const LaunchShape sm = small_shape(c, sh);
+        HIPTRY(c, launch_small(a, w->small, small_bpr(c, count, sm, bpr), sm, s));
         if (tp) HIPTRY(c, hipEventRecord(tp->b, s));
         if (after) HIPTRY(c, hipEventRecord(after, s));
     } else if (mode & CG_PLAIN) {
@@ -1172,8 +1188,13 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
     if (const char *e = getenv("XC_SIDX_BLOCKS")) c->sidx_blocks_per_cu = std::min(std::max(atoi(e), 1), 64);
     if (c->seg_min_log2 < 4 || c->seg_min_log2 > 40) return bail(CG_EINVAL);
     if (!valid_tuning(c->tuning)) return bail(CG_EINVAL);
+    // propagating: four windows per lane leave room for half the waves only,
+    // and a batch's records often share their sources (65,536 pieces read from
+    // 32 MiB of host region and 256 MiB of device shadow: 337 us with
+    // non-temporal loads, 243 us with cached ones)
     c->tuning_prop = c->tuning;
     c->tuning_prop.unroll = 2;
+    c->tuning_prop.nontemporal = 0;
     // events that check_transfers_noalloc records, made here so that it makes none
     for (auto &v : c->ver)
         if (hipEventCreateWithFlags(&v.fixed_use, hipEventDisableTiming) != hipSuccess) return bail(CG_EHIP);
@@ -1406,7 +1427,7 @@ int check_transfers_noalloc(cg_ctx *c, const cg_transfer *recs_dev, uint64_t cou
     a.out = (mode & CG_CHECK) ? out_dev : nullptr;
     a.mode = mode & (CG_CHECK | CG_PROPAGATE);
     a.st = c->ver[c->cur].st;
-    const LaunchShape sh = shape_of(c, (mode & CG_PROPAGATE) ? c->tuning_prop : c->tuning);
+    const LaunchShape sh = small_shape(c, shape_of(c, (mode & CG_PROPAGATE) ? c->tuning_prop : c->tuning));
     HIPTRY(c, launch_small(a, acc, small_bpr(c, count, sh, 0), sh, s));
     return note_use_fixed(c, s);
 }
@@ -1475,7 +1496,7 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
         HIPTRY(c, launch_sidx_query(a, w->hidx, w->pidx, a.bsum, s, w->pitch));
         HIPTRY(c, launch_reweigh(a, s));
     }
-    HIPTRY(c, launch_scan_sums(a, sh.tile_units, sh.grid * (sh.block / 64), s));
+    HIPTRY(c, launch_scan_sums(a, sh.tile_units, (a.lds_meta ? sh.grid : scan_grid(sh)) * (sh.block / 64), s));
     HIPTRY(c, launch_prefix_tiles(a, s));
     if (capturing) {
         HIPTRY(c, launch_batched(a, sh, s));

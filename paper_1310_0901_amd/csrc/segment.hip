@@ -48,11 +48,11 @@ static_assert(kT == kSortKeyBlock, "one part of the key mask per block of k_seg_
 // the record reads source bytes through its units
 __device__ __forceinline__ bool seg_split(const Desc &d) { return d.units > 0 && d.v_hi > d.v_lo; }
 
-// shadow address of the source chunk of the record's first unit
+// shadow address of the source chunk of the record's first unit (the windows
+// of a check without propagation are aligned source chunks)
 __device__ __forceinline__ uint64_t seg_a0(const Desc &d)
 {
-    const uint64_t delta = (d.ctl & CTL_DELTA) ? 1u : 0u;
-    return d.src_sh + 16u * (d.e0 - delta);
+    return d.src_sh + 16u * d.e0;
 }
 
 __device__ __forceinline__ uint64_t seg_count(const Desc &d, uint32_t lb)

@@ -578,10 +578,9 @@ __global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, S
             cg_verdict v = a.out[t];
             uint64_t first = v.first_bad;
             if (has_src) {
-                const uint32_t phi = (d.ctl >> CTL_PHI_SHIFT) & 15u;
                 // space offset of the record's byte 0: host region offset, or pool offset
-                const int64_t off0 = src_host ? d.a_src + (int64_t)phi
-                                              : (int64_t)(d.src_sh + phi - a.st->pool);
+                const int64_t off0 = src_host ? d.a_src + (int64_t)desc_o(d)
+                                              : (int64_t)(d.src_sh + desc_o(d) - a.st->pool);
                 const Range g((uint64_t)(off0 + d.v_lo), (uint64_t)(off0 + d.v_hi));
                 uint64_t fu;
                 const uint64_t undef = src_host ? undef_in(h, hu, g, &fu) : undef_in(p, pu, g, &fu);
@@ -599,8 +598,7 @@ __global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, S
                 }
             }
             if (dsta) {
-                const uint32_t psi = (d.ctl >> CTL_PSI_SHIFT) & 15u;
-                const int64_t off0 = d.a_dst + (int64_t)psi;   // host region offset of the destination's byte 0
+                const int64_t off0 = d.a_dst + (int64_t)desc_o(d);   // host region offset of the destination's byte 0
                 const Range g((uint64_t)(off0 + d.d_lo), (uint64_t)(off0 + d.d_hi));
                 const uint64_t fn = unaddr_in(h, hn, g);
                 if (fn != ~0ull) {
@@ -715,7 +713,7 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v)
     return v;
 }
 
-// Pitched positions whose rows follow row 0 (kRowsUniform, kRowsStep: every
+// Pitched positions whose rows follow row 0 (kRowsUniform: every
 // row whole inside row 0's allocation or the host region) in a check without
 // propagation, one wave per position.  The list entries between the first
 // row's start and the last row's end are mapped onto the rows: undefined
@@ -729,7 +727,7 @@ __global__ void __launch_bounds__(kT) k_sidx_rows(BatchArgs a, ShadowIndex h, Sh
     const uint64_t t = (uint64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
     if (!a.out || t >= a.count) return;
     const Pitch P = pitch[t];
-    if (P.uniform != kRowsUniform && P.uniform != kRowsStep) return;
+    if (P.uniform != kRowsUniform) return;
     const Desc d = a.desc[t];
     const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
     const bool dsta = (d.ctl & CTL_DST_A) != 0 && d.d_hi > d.d_lo;
@@ -740,10 +738,10 @@ __global__ void __launch_bounds__(kT) k_sidx_rows(BatchArgs a, ShadowIndex h, Sh
                     (src_host ? h.state[1] : p.state[1]) && (!dsta || h.state[1]);
     if (!ok) return;
     const ShadowIndex &xs = src_host ? h : p;
-    const uint32_t phi = (d.ctl >> CTL_PHI_SHIFT) & 15u, psi = (d.ctl >> CTL_PSI_SHIFT) & 15u;
-    const RowSide rs{src_host ? (uint64_t)(d.a_src + (int64_t)phi) : d.src_sh + phi - a.st->pool, P.rows, P.spitch,
+    const uint32_t o = desc_o(d);
+    const RowSide rs{src_host ? (uint64_t)(d.a_src + (int64_t)o) : d.src_sh + o - a.st->pool, P.rows, P.spitch,
                      P.width};
-    const RowSide rd{(uint64_t)(d.a_dst + (int64_t)psi), P.rows, P.dpitch, P.width};
+    const RowSide rd{(uint64_t)(d.a_dst + (int64_t)o), P.rows, P.dpitch, P.width};
     // the chunks of each side's span, first row to last
     const uint64_t sa = rs.S >> 4, sb = (rs.S + (rs.R - 1) * rs.q + rs.w - 1) >> 4;
     const uint64_t da = rd.S >> 4, db = (rd.S + (rd.R - 1) * rd.q + rd.w - 1) >> 4;

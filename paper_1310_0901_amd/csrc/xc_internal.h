@@ -11,23 +11,21 @@ namespace xc {
 
 // Per-record scan descriptor written by the classify kernel.
 //
-// A record's byte index i runs over [0, n).  The source side is read in
-// 16-byte "chunks" aligned in shadow memory: source chunk c covers byte
-// indices [16c - phi, 16c - phi + 16), destination chunk e covers
-// [16e - psi, 16e - psi + 16).  One unit of work handles destination chunk
-// e = e0 + k together with source chunk c = e - delta; delta is 1 when the
-// source phase is behind the destination phase, so that destination chunk e
-// is byte window [s, s + 16) of source chunks c and c + 1, s = (phi - psi) mod 16.
+// A record's byte index i runs over [0, n).  Its work is cut into windows of
+// 16 bytes: window e covers byte indices [16e - o, 16e - o + 16) of the source
+// and of the destination alike, o < 16 being the offset that aligns one of
+// the two in shadow memory (the destination when its shadow is written, else
+// the source).  Unit k of the record is window e0 + k.
 struct alignas(16) Desc {
-    uint64_t src_sh;   // device address of source chunk 0 (16-byte aligned)
-    uint64_t dst_sh;   // device address of destination chunk 0 (16-byte aligned)
+    uint64_t src_sh;   // device address of the source shadow at window 0's first byte
+    uint64_t dst_sh;   // device address of the destination shadow there
     int64_t v_lo, v_hi;  // source bytes that are valid to read: [v_lo, v_hi)
     int64_t d_lo, d_hi;  // destination bytes inside the region / allocation
-    int64_t a_src;     // A-bit index of source chunk 0 (host source only)
-    int64_t a_dst;     // A-bit index of destination chunk 0 (host destination only)
-    uint64_t e0;       // first unit's destination-chunk index
+    int64_t a_src;     // A-bit index of window 0's first source byte (host source only)
+    int64_t a_dst;     // A-bit index of its first destination byte (host destination only)
+    uint64_t e0;       // first unit's window
     uint64_t units;    // number of units
-    uint32_t ctl;      // CTL_* bits, phase fields
+    uint32_t ctl;      // CTL_* bits and o
     uint32_t pad[3];
 };
 static_assert(sizeof(Desc) == 96, "descriptor layout");
@@ -38,10 +36,11 @@ enum : uint32_t {
     CTL_CHECK = 1u << 2,      // accumulate findings
     CTL_PROP = 1u << 3,       // write destination shadow
     CTL_DST_A = 1u << 4,      // scan destination A bits (host destination, checking)
-    CTL_PHI_SHIFT = 8,        // 4 bits
-    CTL_PSI_SHIFT = 12,       // 4 bits
-    CTL_DELTA = 1u << 16,
+    CTL_O_SHIFT = 8,          // o, 4 bits
 };
+
+// o of a descriptor
+__host__ __device__ inline uint32_t desc_o(const Desc &d) { return (d.ctl >> CTL_O_SHIFT) & 15u; }
 
 // Device-resident control block of one batched check.
 struct alignas(64) Ctl {
@@ -91,7 +90,7 @@ struct FillRange {
 constexpr int kMaxTop = 1024;        // LDS-staged top level of the table
 constexpr int kMaxMid = 8192;        // entries of its middle level (64 KiB of LDS where a kernel stages it)
 constexpr uint32_t kFineShift = 4;   // 16 bases: one 128-byte line
-constexpr uint64_t kMinTile = 1024;  // smallest work tile, in 16-byte units
+constexpr uint64_t kMinTile = 256;   // smallest work tile, in 16-byte units
 constexpr int kClassifyBlock = 256;  // records per classify block
 constexpr uint64_t kScanLimit = 1ull << 62;  // byte indices scanned per record
 constexpr uint64_t kSmallUnits = 8192;       // units per block of a record in a one-launch batch (k_small)
@@ -101,22 +100,20 @@ constexpr uint64_t kSmallUnits = 8192;       // units per block of a record in a
 // [r*upr, (r+1)*upr) of the position (upr bounds the units of any row; the
 // units past a row's own are empty), and the position's Desc is row 0's.
 // When `uniform` is non-zero, every row lies in row 0's allocation or in the
-// host region on each side, fully valid, so row r's descriptor follows from
-// row 0's by the pitches (with pitches that keep the 16-byte phases, every
-// row has exactly upr units); otherwise each row is looked up and classified
-// where it is worked.
+// host region on each side, fully valid, so row r's descriptor is row 0's
+// moved by the pitches, with o = 0 and exactly upr units; otherwise each row
+// is looked up and classified where it is worked.
 struct Pitch {
     uint64_t src, dst, width, rows, spitch, dpitch, upr;
     uint32_t kind, uniform;
 };
 
-// Pitch::uniform: rows follow row 0 (kRowsUniform), and also keep its 16-byte
-// phases, so that every row has row 0's units and upr is that number
-// (kRowsStep); or, in a check without propagation, the rows' sources (and a
-// host destination) lie back to back, so that the record is worked as one
-// transfer of rows * width bytes, whose descriptor is the position's and whose
-// units are upr (kRowsContig): its byte indices are the record's own.
-constexpr uint32_t kRowsUniform = 1u, kRowsStep = 3u, kRowsContig = 7u;
+// Pitch::uniform: rows follow row 0 (kRowsUniform); or, in a check without
+// propagation, the rows' sources (and a host destination) lie back to back, so
+// that the record is worked as one transfer of rows * width bytes, whose
+// descriptor is the position's and whose units are upr (kRowsContig): its byte
+// indices are the record's own.
+constexpr uint32_t kRowsUniform = 1u, kRowsContig = 7u;
 static_assert(sizeof(Pitch) == 64, "pitched record layout");
 
 struct BatchArgs {
@@ -278,6 +275,8 @@ hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const Sh
 // shadow indexes have answered records of a batch in its given order
 hipError_t launch_reweigh(const BatchArgs &a, hipStream_t s);
 hipError_t launch_classify_2d(const BatchArgs &a, const cg_transfer2d *recs2d, Pitch *pitch, hipStream_t s);
+uint32_t scan_grid(const LaunchShape &sh);   // workgroups of the scan kernel
+// waves: of the scan kernel's grid (its tiles)
 hipError_t launch_scan_sums(const BatchArgs &a, uint32_t tile_units, uint32_t waves, hipStream_t s);
 hipError_t launch_prefix_tiles(const BatchArgs &a, hipStream_t s);
 // the persistent scan kernel, then (a.lds_meta) the host-source positions in LDS

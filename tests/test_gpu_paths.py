@@ -118,3 +118,99 @@ def test_pointers_at_table_edges(X, nalloc):
                 assert np.array_equal(got[ok][f], want[f]), (count, f)
     finally:
         X.cg_destroy(ctx)
+
+
+def edge_world(rng, hl, sizes, dens=0.003):
+    """A host region and allocations with faults everywhere, 4,096 bytes apart."""
+    from tests import util
+    hv = np.where(rng.random(hl) < dens, rng.integers(1, 256, hl), 0).astype(np.uint8)
+    a = (rng.random(hl) > 0.0005).astype(np.uint8)
+    a[-1] = a[0] = 1
+    base = W.DEV_BASE + 4096 * np.arange(1, len(sizes) + 1) + np.concatenate([[0], np.cumsum(sizes)[:-1]]) + 5
+    vs = [np.where(rng.random(int(s)) < dens, rng.integers(1, 256, int(s)), 0).astype(np.uint8) for s in sizes]
+    return util.workload_from_arrays(W.HOST_BASE, hv, a, base, sizes, vs, np.zeros(0, W.RECORD_DTYPE)), base
+
+
+def compare_state(H, w, base, sizes, o, call, want):
+    from tests import util
+    dw = H.DeviceWorld(w)
+    try:
+        util.assert_verdicts_equal(call(dw), want)
+        for j in range(len(sizes)):
+            assert np.array_equal(dw.alloc_shadow(base[j], sizes[j]), o.vs[j]), f"allocation {j}"
+        assert np.array_equal(dw.host_shadow(), o.hv), "host region shadow"
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_windows_at_edges(X, seed):
+    """Transfers at every pair of source and destination alignments and at
+    lengths around a window, a wave's windows and a wave's iterations, some
+    reaching past the region or their allocation on either side: checks and
+    propagation, as one launch of 200 records and as a batch of 600."""
+    from paper_1310_0901_amd import harness as H
+    from tests import util
+    rng = np.random.default_rng(9000 + seed)
+    read, T = 300_001, 600
+    lens = [1, 2, 15, 16, 17, 31, 33, 1007, 1023, 1024, 1025, 2047, 2049, 4095, 4096, 4097, 8191, 8193, 16_400, 33_000]
+    n = rng.choice(lens, T)
+    kind = rng.choice(3, T, p=[0.4, 0.3, 0.3])
+    gap = rng.integers(1, 40, T)
+    pos = np.cumsum(n + gap) - n
+    sizes = np.array([200_003, int(pos[-1] + n[-1]) + 100])
+    hl = read + int(pos[-1] + n[-1]) + 7
+    w, base = edge_world(rng, hl, sizes)
+    src = np.where(kind == 0, W.HOST_BASE + rng.integers(0, read - 33_000, T), base[0] + rng.integers(0, 200_003 - 33_000, T))
+    dst = np.where(kind == 1, W.HOST_BASE + read + pos, base[1] + pos)
+    edge = rng.random(T)
+    # sources before and past the region, and past the allocation's end
+    src = np.where((kind == 0) & (edge < 0.1), W.HOST_BASE - rng.integers(0, 40, T), src)
+    src = np.where((kind != 0) & (edge < 0.1), base[0] + 200_003 - rng.integers(1, 40, T), src)
+    rec = W.make_records(kind, src.astype(np.uint64), dst.astype(np.uint64), n.astype(np.uint64))
+    for part in (rec[:200], rec):
+        want = util.oracle_for(w).run(part)
+        dw = H.DeviceWorld(w)
+        try:
+            for mode in (X.CG_CHECK, X.CG_CHECK | X.CG_KEEP_ORDER, X.CG_CHECK | X.CG_PLAIN):
+                util.assert_verdicts_equal(dw.check(part, mode), want, f"mode {mode}")
+        finally:
+            dw.close()
+        o = util.oracle_for(w)
+        want = o.run(part, propagate=True)
+        for mode in (X.CG_CHECK | X.CG_PROPAGATE, X.CG_CHECK | X.CG_PROPAGATE | X.CG_PLAIN):
+            compare_state(H, w, base, sizes, o, lambda dw: dw.check(part, mode), want)
+
+
+@pytest.mark.parametrize("width,pitch", [(1, 1), (1, 7), (15, 16), (16, 16), (17, 40), (333, 512), (1008, 1024),
+                                         (1023, 1023), (1025, 1100), (4030, 4096), (65_519, 65_520), (65_520, 65_536),
+                                         (65_521, 65_600), (65_537, 65_537), (100, (1 << 20) - 1), (100, 1 << 20),
+                                         (2000, (1 << 20) + 5)])
+def test_rows_at_edges(X, width, pitch):
+    """Pitched copies around the sizes where rows change how they are worked:
+    a window, a wave, 4,096 units a row, pitches of 1 MiB; tight rows on one
+    side and pitched rows on the other, at odd alignments."""
+    from paper_1310_0901_amd import harness as H
+    from tests import util
+    from tests.test_gpu_2d import check2d
+    rng = np.random.default_rng(width + pitch)
+    rows = 5 if pitch >= 65_000 else 77
+    span, tight = (rows - 1) * pitch + width, rows * width
+    sizes = np.array([span + 3, 2 * (span + 64)])
+    read = max(tight, 64) + 50
+    w, base = edge_world(rng, read + tight + 40, sizes, dens=0.001)
+    rec = np.zeros(3, W.RECORD2D_DTYPE)
+    rec["width"], rec["rows"], rec["kind"] = width, rows, [0, 1, 2]
+    rec["src"] = [W.HOST_BASE + 3, base[0] + 1, base[0] + 2]
+    rec["dst"] = [base[1] + 7, W.HOST_BASE + read + 5, base[1] + span + 64]
+    rec["spitch"] = [width, pitch, pitch]
+    rec["dpitch"] = [pitch, width, pitch]
+    want = util.oracle_for(w).run2d(rec)
+    dw = H.DeviceWorld(w)
+    try:
+        util.assert_verdicts_equal(check2d(X, dw, rec, X.CG_CHECK), want, "check")
+    finally:
+        dw.close()
+    o = util.oracle_for(w)
+    want = o.run2d(rec, propagate=True)
+    compare_state(H, w, base, sizes, o, lambda dw: check2d(X, dw, rec, X.CG_CHECK | X.CG_PROPAGATE), want)
