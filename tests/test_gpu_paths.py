@@ -88,7 +88,7 @@ def test_pointers_at_table_edges(X, nalloc):
     entries) stops holding every base, its stride doubles, and the fine level
     (every 16th base, from 131,073 entries on) joins in: pointers one
     below, at, inside, at the end of and one past the end of allocations, some
-    of them adjacent, at 1 pointer and at 70,000 (both workgroup sizes)."""
+    of them adjacent, at 1, 300 and 300,000 pointers (both staged levels)."""
     from oracle import oracle
     rng = np.random.default_rng(nalloc)
     sizes = rng.integers(1, 700, nalloc)
@@ -100,7 +100,7 @@ def test_pointers_at_table_edges(X, nalloc):
             X.shadow_alloc_batch(ctx, base, sizes)
         ends = np.concatenate([base - 1, base, base + sizes // 2, base + sizes - 1, base + sizes, base + sizes + 1,
                                [0, 1, (1 << 63) - 1]])
-        for count in (1, 70_000):
+        for count in (1, 300, 300_000):
             p = rng.choice(ends, count).astype(np.uint64)
             t = torch.from_numpy(p.view(np.int64)).cuda()
             out = torch.zeros((count, 3), dtype=torch.int64, device="cuda")
