@@ -127,7 +127,7 @@ def roofline(tun, config, k_avg_ms, i_avg_ms, pass_bytes, bytes_step, l2_probe_G
     """The dominant kernel's roofline.  When the shadow indexes answer the
     check-only records, that is the indexes' counting pass (k_sidx_count, one
     launch over both spaces): it reads once each V byte (and the host
-    region's A bits) of the 64 KiB steps the batch's records read (its
+    region's A bits) of the 4 KiB granules the batch's records read (its
     algorithmic bytes: `pass_bytes`, as the library counted them for the
     timed passes), so HBM bounds it; achieved = those bytes over its live
     duration, traffic from its committed counters.  Otherwise it is the scan
@@ -141,7 +141,7 @@ def roofline(tun, config, k_avg_ms, i_avg_ms, pass_bytes, bytes_step, l2_probe_G
                "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                "algorithmic_bytes_per_launch": int(pass_bytes), "scan_kernel_avg_ms": round(k_avg_ms, 3),
-               "note": "the shadow indexes' counting pass reads once each V byte of the 64 KiB steps of the host "
+               "note": "the shadow indexes' counting pass reads once each V byte of the 4 KiB granules of the host "
                        "region and of the pool that the batch's records read, and the host region's A bits of "
                        "them (16-byte V loads, 2-byte A loads); achieved = those bytes (counted by the library, "
                        "cg_index_ms) over the pass's live duration (HIP events around it on the check's stream); "
@@ -670,8 +670,8 @@ def main():
         "config": {"workload": f"{w.name} (configuration {args.config}): {w.note}",
                    "records": T, "live_allocations": int(w.dev.live_idx.size),
                    "host_region_bytes": int(w.host.length), "transfer_bytes": int(w.records["n"].sum()),
-                   "mode": "check", "path": "batched: classify (marking the 64 KiB shadow steps the records read); "
-                           "indexes of the faulty chunks of those steps of the host region and of the shadow pool, "
+                   "mode": "check", "path": "batched: classify (marking the 4 KiB shadow granules the records read); "
+                           "indexes of the faulty chunks of those granules of the host region and of the shadow pool, "
                            "read once each, answering the check-only records; source-block segments and the "
                            "persistent scan kernel for any record left; hipGraph replay",
                    "tuning": tun},

@@ -185,17 +185,17 @@ int shadow_ptr(cg_ctx *ctx, uint64_t dev_addr, uint8_t **v_dev);
  *   CG_KEEP_ORDER.  A batched check of 16,384 to 2^27 records without
  *   propagation is worked as source-block segments: each record's bytes are cut at blocks of source
  *   memory (a power of two of at least 1 MiB) and the pieces are worked in
- *   block order, so that copies reading the same bytes run close together.
+ *   block order, so that copies reading the same bytes run close together
+ *   (a batch that reads few bytes again keeps its order).
  *   Verdicts are the same and are written at the records' own positions
  *   either way; CG_KEEP_ORDER works the batch in the given order.
  *   A check without propagation of more than 256 records (not CG_PLAIN or
- *   CG_KEEP_ORDER) that reads its shadow spaces heavily (at least 4 bytes of
- *   the host region, or of the shadow pool, per byte of it) reads the 64 KiB
- *   steps of each such space that its records read, once, into an index of
- *   their faulty 16-byte chunks and answers its records from it, with the
- *   same verdicts (the first such call on a stream allocates the index
- *   space: about 180 MB plus 9 bytes per 64 KiB of the pool).  A host region
- *   above 64 GiB is not indexed.
+ *   CG_KEEP_ORDER) reads the 4 KiB granules of each shadow space (the host
+ *   region, the shadow pool) that its records read, once, into an index of
+ *   their faulty 16-byte chunks, where that costs less than the scan it saves,
+ *   and answers its records from it, with the same verdicts (the first such
+ *   call on a stream allocates the index space: about 280 MB plus 90 bytes per
+ *   64 KiB of the pool).  A host region above 64 GiB is not indexed.
  * With CG_PROPAGATE every valid destination byte receives the source's V
  * byte, or 0xFF where the source byte is not valid; overlapping D2D records
  * are not propagated.  All records read the shadow as it was before the
@@ -426,8 +426,8 @@ int cg_kernel_ms(cg_ctx *ctx, double *ms, uint64_t *launches);
  * When bytes is not NULL (2 entries), it
  * receives the shadow bytes the counting passes of the indexes read since the
  * last such call, timed or not: [0] of the host region (V and A bits), [1] of
- * the shadow pool (V); that count then restarts.  A pass reads the 64 KiB
- * steps of V that the batch's records read, not the whole space.  With bytes,
+ * the shadow pool (V); that count then restarts.  A pass reads the 4 KiB
+ * granules of V that the batch's records read, not the whole space.  With bytes,
  * the call waits for the device.  Errors: CG_EINVAL, CG_EHIP.
  */
 int cg_index_ms(cg_ctx *ctx, double *ms, uint64_t *launches, uint64_t *bytes);

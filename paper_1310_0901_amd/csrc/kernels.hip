@@ -13,7 +13,7 @@
 //                  range-derived verdict fields, scan descriptor, work weight,
 //                  block-local exclusive scan of the weights; for a check the
 //                  shadow indexes may answer, the valid bytes per shadow space
-//                  and the marks of the 64 KiB shadow steps they fall in;
+//                  and the marks of the 4 KiB shadow granules they fall in;
 //   (shadowindex.hip) large check-only batches: indexes of the faulty chunks
 //                  of those steps, which answer the records whose spaces they
 //                  cover (their units leave the scan);
@@ -862,14 +862,44 @@ __device__ __forceinline__ uint64_t classify_rec(const cg_transfer &r, uint32_t 
     return units;
 }
 
-// Marks the steps (2^16 bytes of V) of shadow space k that hold its bytes
-// [lo, hi), for that index's counting pass: bytes before the first 16-aligned
-// step, then 16 marks per store.
+// Marks the granules (2^12 bytes of V) of shadow space k that hold its bytes
+// [lo, hi), for that index's counting pass: a byte per granule of the steps
+// (2^16 bytes) at the range's ends, a byte for every step it covers whole, 16
+// per store.  Plain byte-masked stores merge in memory whichever XCD's L2 they
+// leave from; granule bits set by atomics, which all meet in one place, took
+// 310 us for 1M records.
 __device__ __forceinline__ void mark_steps(const BatchArgs &a, int k, uint64_t lo, uint64_t hi)
 {
     uint8_t *m = a.index_mark[k];
     if (!m || hi <= lo) return;
-    uint64_t s = lo >> kIdxStepShift, e = ((hi - 1) >> kIdxStepShift) + 1;
+    constexpr uint32_t sh = kIdxStepShift - kIdxGranShift;
+    const uint64_t g0 = lo >> kIdxGranShift, g1 = ((hi - 1) >> kIdxGranShift) + 1;   // granules [g0, g1)
+    uint64_t s = g0 >> sh, e = g1 >> sh;                                             // steps [s, e) start to end
+    // granules [x, x + n) of one step, n < 16, by at most two stores
+    auto part = [&](uint64_t x, uint32_t n) {
+        if (n == 0 || (x >> sh) >= a.mark_cap[k]) return;
+        uint8_t *f = a.index_fine[k] + x;
+        typedef uint64_t u64u __attribute__((aligned(1)));
+        typedef uint16_t u16u __attribute__((aligned(1)));
+        if (n >= 8) {
+            *reinterpret_cast<u64u *>(f) = *reinterpret_cast<u64u *>(f + n - 8) = 0x0101010101010101ull;
+        } else if (n >= 4) {
+            *reinterpret_cast<u32u *>(f) = *reinterpret_cast<u32u *>(f + n - 4) = 0x01010101u;
+        } else if (n >= 2) {
+            *reinterpret_cast<u16u *>(f) = *reinterpret_cast<u16u *>(f + n - 2) = (uint16_t)0x0101u;
+        } else {
+            f[0] = 1;
+        }
+    };
+    if (s == e) {
+        part(g0, (uint32_t)(g1 - g0));
+        return;
+    }
+    if (g0 & 15u) {
+        part(g0, 16u - (uint32_t)(g0 & 15u));
+        ++s;
+    }
+    part(g1 & ~15ull, (uint32_t)(g1 & 15u));
     if (e > a.mark_cap[k]) e = a.mark_cap[k];
     for (; s < e && (s & 15u); ++s) m[s] = 1;
     for (; s + 16 <= e; s += 16) *reinterpret_cast<uint4 *>(m + s) = make_uint4(0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u);
@@ -969,19 +999,20 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify(BatchArgs a)
         }
 }
 
-// After the shadow indexes have answered positions (their weight set to 0)
-// of a batch in its given order: each position's weight max(units, 1) again,
-// with the block-local prefix and block sums that k_classify leaves.
+// After the shadow indexes have answered pitched positions (their weight set
+// to 0): each position's weight max(units, 1) again, with the block-local
+// prefix and block sums that k_classify leaves, and the units left to scan.
 __global__ void __launch_bounds__(kClassifyBlock) k_reweigh(BatchArgs a)
 {
     __shared__ uint64_t wsum[kClassifyBlock / 64];
     const uint32_t tid = threadIdx.x;
     const uint64_t t = (uint64_t)blockIdx.x * kClassifyBlock + tid;
-    uint64_t w = 0;
+    uint64_t w = 0, u = 0;
     if (t < a.count) {
-        const uint64_t u = a.weight[t];
+        u = a.weight[t];
         w = u ? u : 1;
     }
+    if (__syncthreads_or(u != 0) && tid == 0) atomicOr((unsigned long long *)&a.index_bytes[0][kIdxLeft], 1ull);
     const uint32_t lane = lane_id(), wid = tid >> 6;
     uint64_t x = w;
     for (uint32_t d = 1; d < 64u; d <<= 1) {
@@ -1298,13 +1329,38 @@ __global__ void __launch_bounds__(1024) k_pointers(const DevState *stp, const ui
 constexpr uint32_t kXcds = 8;
 constexpr uint64_t kNoTile = ~0ull;
 
+// A batch worked as segments (lds_meta not null) is worked by k_batched_lds,
+// unless it was left in its order: then by k_batched, as one chunk.  Both are
+// launched, and one of them leaves at once.
+__device__ __forceinline__ bool lds_works(const BatchArgs &a) { return a.lds_meta && a.lds_meta[3] == 0; }
+
 // ---------------------------------------------------------------------------
 // k_scan_sums: one block, exclusive scan of the classify-block sums
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_units, uint32_t waves)
+// (waves: of the scan kernel's grid, or of k_batched_lds's for a batch that it works)
+__global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_units, uint32_t waves, uint32_t lds_waves)
 {
+    if (lds_works(a)) waves = lds_waves;
     __shared__ uint64_t wsum[16];
     const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
+    if (a.index_bytes[0]) {
+        // the shadow indexes' states back to 0 for the next batch; when they
+        // answered every record, the scan has no tile
+        const bool none = a.index_bytes[0][kIdxLeft] == 0;
+        __syncthreads();
+        if (tid < 2 * kIdxState) a.index_bytes[tid / kIdxState][tid % kIdxState] = 0;
+        if (none) {
+            if (tid == 0) {
+                a.ctl->total_units = a.ctl->ntiles = 0;
+                a.ctl->tile_units = kMinTile;
+            }
+            if (tid < kXcds) {
+                a.ctl->counter[tid] = 0;
+                a.ctl->lds_counter[tid] = 0;
+            }
+            return;
+        }
+    }
     const uint64_t nb = (a.count + kClassifyBlock - 1) / kClassifyBlock;
     const uint64_t per = (nb + 1023) / 1024;
     const uint64_t b0 = tid * per, b1 = (b0 + per < nb) ? b0 + per : nb;
@@ -1354,7 +1410,7 @@ __global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_u
 __global__ void __launch_bounds__(256) k_prefix_tiles(BatchArgs a)
 {
     const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= a.count) return;
+    if (t >= a.count || a.ctl->ntiles == 0) return;
     a.prefix[t] = a.local[t] + a.boff[t / kClassifyBlock];
 }
 
@@ -1607,7 +1663,7 @@ __device__ void batched_loop(const BatchArgs &a)
     // counter; a wave whose chunk is used up takes tiles from the others'.
     // Only a batch worked as segments has that locality to keep; any
     // other batch is one chunk for all waves (tiles interleaved over XCDs).
-    const uint32_t nch = a.perm ? kXcds : 1u;
+    const uint32_t nch = a.perm && (!a.lds_meta || lds_works(a)) ? kXcds : 1u;
     const uint32_t wpb = blockDim.x >> 6;
     const uint32_t xcd = blockIdx.x % nch;
     auto chunk_lo = [&](uint32_t x) { return ntiles * x / nch; };
@@ -1706,6 +1762,7 @@ __device__ void batched_loop(const BatchArgs &a)
 template <int U, bool NT, bool PROP>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PROP ? 1 : 3))) k_batched(BatchArgs a)
 {
+    if (lds_works(a)) return;
     batched_loop<U, NT, PROP, false, 0>(a);
 }
 
@@ -1927,6 +1984,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
     __shared__ uint64_t s_task;
     __shared__ uint32_t s_next[2];
     __shared__ uint16_t s_list[kTaskPos];
+    if (!lds_works(a)) return;
     if (((blockIdx.x / kXcds) & 1u) != 0) {
         host_loop<4>(a, a.lds_meta, 2, sv, sa, sp, &s_task, s_next, s_list);
         __syncthreads();
@@ -2180,6 +2238,7 @@ hipError_t launch_classify(const BatchArgs &a, hipStream_t s)
 hipError_t launch_reweigh(const BatchArgs &a, hipStream_t s)
 {
     const uint64_t blocks = (a.count + kClassifyBlock - 1) / kClassifyBlock;
+    if (!a.index_bytes[0]) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_reweigh, dim3((uint32_t)blocks), dim3(kClassifyBlock), 0, s, a);
     return hipGetLastError();
 }
@@ -2194,15 +2253,16 @@ hipError_t launch_classify_2d(const BatchArgs &a, const cg_transfer2d *recs2d, P
 // Workgroups of the scan kernel: four times the persistent grid the launch
 // shape asks for (at most 16 of 256 threads per CU), so that a batch worked as
 // one tile per wave is levelled out by the hardware's own dispatch.
-uint32_t scan_grid(const LaunchShape &sh)
+static uint32_t scan_grid(const LaunchShape &sh)
 {
     const uint32_t most = sh.cus * 16u * 256u / sh.block;
     return sh.grid >= most ? sh.grid : std::min(4u * sh.grid, most);
 }
 
-hipError_t launch_scan_sums(const BatchArgs &a, uint32_t tile_units, uint32_t waves, hipStream_t s)
+hipError_t launch_scan_sums(const BatchArgs &a, const LaunchShape &sh, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, a, tile_units, waves);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, a, sh.tile_units, scan_grid(sh) * (sh.block / 64),
+                       sh.grid * (sh.block / 64));
     return hipGetLastError();
 }
 
@@ -2238,9 +2298,10 @@ static void launch_batched_t(const BatchArgs &a, const LaunchShape &sh, hipStrea
         d.lds_meta = nullptr;
         hipLaunchKernelGGL((k_batched<U, NT, false>), dim3(sh.grid), dim3(sh.block), 0, s, d);
         hipLaunchKernelGGL(k_host_lds, dim3(sh.cus * 3), dim3(256), 0, s, a);
-    } else if (a.lds_meta)
+    } else if (a.lds_meta) {
         hipLaunchKernelGGL((k_batched_lds<U, NT>), dim3(sh.grid), dim3(sh.block), 0, s, a);
-    else if (a.mode & CG_PROPAGATE)
+        hipLaunchKernelGGL((k_batched<U, NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
+    } else if (a.mode & CG_PROPAGATE)
         hipLaunchKernelGGL((k_batched<U, NT, true>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     else
         hipLaunchKernelGGL((k_batched<U, NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);

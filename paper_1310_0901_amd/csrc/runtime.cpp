@@ -196,7 +196,6 @@ struct cg_ctx {
     uint32_t task_pos = 0;                   // positions per host-source task (0: the kernel's default)
     bool pitched_2d = true;                  // 2D records as pitched positions (else rows expanded, one wait)
     int shadow_index = 1;                    // shadow indexes of check-only segmented batches: 0 off, 1 when they pay, 2 always
-    uint32_t sidx_ratio = 4;                 // one pays from this many of the batch's bytes per byte of its space
     uint64_t sidx_cap = 1ull << 22;          // entries per list of a shadow index
     uint32_t sidx_blocks_per_cu = 8;         // grid of the index passes
     int host_lds = 1;                        // check-only segments of host sources worked from LDS: 1 in the
@@ -448,7 +447,7 @@ void free_seg(Workspace *w)
     w->seg_cap = 0;
     for (ShadowIndex *x : {&w->hidx, &w->pidx}) {
         void *hs[] = {x->uchunk, x->umask, x->ucum, x->nchunk, x->nmask, x->bcnt, x->sflag, x->state,
-                      x->smark, x->slist, x->mcnt};
+                      x->smark, x->fmark, x->slist, x->mcnt};
         for (void *p : hs)
             if (p) (void)hipFree(p);
         *x = ShadowIndex{};
@@ -577,23 +576,17 @@ hipError_t prepare_stage(const BatchArgs &a, const LaunchShape &sh, hipStream_t 
     const bool idx = sp && sp->hidx;
     if (stage == 0) {
         if (!sp) return launch_classify(a, s);
-        if (idx && (e = launch_sidx_reset(*sp->hidx, *sp->pidx, s)) != hipSuccess) return e;
         if ((e = launch_classify(sp->ar, s)) != hipSuccess) return e;
-        if (idx && (e = launch_sidx_marks(*sp->hidx, sp->ar.st, s)) != hipSuccess) return e;
-        if (idx && (e = launch_sidx_marks(*sp->pidx, sp->ar.st, s)) != hipSuccess) return e;
-        return hipSuccess;
+        return idx ? launch_sidx_marks(*sp->hidx, *sp->pidx, sp->ar.st, s) : hipSuccess;
     }
     if (stage == 1) return idx ? launch_sidx_count(*sp->hidx, *sp->pidx, sp->ar.st, s) : hipSuccess;
     if (idx) {
-        if ((e = launch_sidx_finish(*sp->hidx, sp->ar.st, s)) != hipSuccess) return e;
-        if ((e = launch_sidx_finish(*sp->pidx, sp->ar.st, s)) != hipSuccess) return e;
-        if ((e = launch_sidx_query(sp->ar, *sp->hidx, *sp->pidx, sp->ar.bsum, s)) != hipSuccess) return e;
-        // a batch in its given order: the prefix inputs again, from the units left
-        if (!sp->seg && (e = launch_reweigh(a, s)) != hipSuccess) return e;
+        if ((e = launch_sidx_finish(*sp->hidx, *sp->pidx, sp->ar.st, s)) != hipSuccess) return e;
+        if ((e = launch_sidx_query(sp->ar, *sp->hidx, *sp->pidx, s)) != hipSuccess) return e;
     }
     if (sp && sp->seg && (e = launch_segments(sp->g, *sp->sort, a, const_cast<uint32_t *>(a.perm), s)) != hipSuccess)
         return e;
-    if ((e = launch_scan_sums(a, sh.tile_units, (a.lds_meta ? sh.grid : scan_grid(sh)) * (sh.block / 64), s)) != hipSuccess) return e;
+    if ((e = launch_scan_sums(a, sh, s)) != hipSuccess) return e;
     return launch_prefix_tiles(a, s);
 }
 
@@ -822,19 +815,25 @@ int reserve_sidx(cg_ctx *c, Workspace *w)
         HIPTRY(c, hipMalloc(&x.nchunk, x.cap_n * 8));
         HIPTRY(c, hipMalloc(&x.nmask, x.cap_n * 4));
         HIPTRY(c, hipMalloc(&x.bcnt, 6ull * x.grid * 8));
-        // a mark, a list entry and 4 flags per step of 4,096 chunks (64 KiB) of
-        // the pool, or of a host region of up to 64 GiB; a larger one is not indexed
+        // per step of 64 KiB of the pool, or of a host region of up to 64 GiB (a
+        // larger one is not indexed): 17 mark bytes, 16 list
+        // entries, and flags
         const uint64_t len = space ? c->palloc->capacity() : std::max<uint64_t>(c->region.hl, 64ull << 30);
         x.steps_cap = (len >> kIdxStepShift) + 1;
-        x.mark_grid = (uint32_t)((x.steps_cap + 16383) / 16384);
-        HIPTRY(c, hipMalloc(&x.sflag, 4 * x.steps_cap));
-        HIPTRY(c, hipMalloc(&x.slist, 4 * x.steps_cap));
-        HIPTRY(c, hipMalloc(&x.smark, 16384ull * x.mark_grid));
-        HIPTRY(c, hipMemset(x.smark, 0, 16384ull * x.mark_grid));   // the marking kernels clear what they read
+        x.mark_grid = (uint32_t)((x.steps_cap + 4095) / 4096);
+        HIPTRY(c, hipMalloc(&x.sflag, 8 * (x.steps_cap + 1)));
+        HIPTRY(c, hipMalloc(&x.slist, 64 * x.steps_cap));
+        // (the marking kernels clear the marks they read)
+        HIPTRY(c, hipMalloc(&x.smark, 4096ull * x.mark_grid));
+        HIPTRY(c, hipMemset(x.smark, 0, 4096ull * x.mark_grid));
+        HIPTRY(c, hipMalloc(&x.fmark, 65536ull * x.mark_grid));
+        HIPTRY(c, hipMemset(x.fmark, 0, 65536ull * x.mark_grid));
         HIPTRY(c, hipMalloc(&x.mcnt, 8ull * x.mark_grid));
-        HIPTRY(c, hipMalloc(&x.state, 8 * 8));
+        HIPTRY(c, hipMalloc(&x.state, kIdxState * 8));
+        HIPTRY(c, hipMemset(x.state, 0, kIdxState * 8));
         x.read = c->idx_read + space;
     }
+    HIPTRY(c, hipStreamSynchronize(nullptr));   // the cleared buffers, before any stream uses them
     return CG_OK;
 }
 
@@ -845,6 +844,7 @@ void set_index_args(BatchArgs &a, const Workspace *w)
     for (int k = 0; k < 2; ++k) {
         a.index_bytes[k] = xs[k]->state;
         a.index_mark[k] = xs[k]->smark;
+        a.index_fine[k] = xs[k]->fmark;
         a.mark_cap[k] = xs[k]->steps_cap;
     }
 }
@@ -916,7 +916,7 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
                                                 (uint64_t)c->region.v + c->region.hl);
         const uint32_t key_bytes = (top >> c->seg_min_log2) < (1ull << 31) ? 4u : 8u;
         plan.g = SegArgs{w->rdesc, count, npos, w->rbsum, w->sfirst, w->sbsum, w->srec, w->meta, c->seg_min_log2,
-                         host_last ? 1u : 0u, key_bytes};
+                         host_last ? 1u : 0u, {nullptr, nullptr}, key_bytes};
         plan.sort = &w->sort;
         plan.seg = true;
         a.perm = w->perm;
@@ -930,7 +930,7 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
         count > c->small_max) {
         rc = reserve_sidx(c, w);
         if (rc) return rc;
-        w->hidx.ratio = w->pidx.ratio = c->shadow_index == 2 ? 0u : c->sidx_ratio;
+        w->hidx.always = w->pidx.always = c->shadow_index == 2 ? 1u : 0u;
         if (!seg) {
             plan.seg = false;
             plan.ar = a;
@@ -938,7 +938,9 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
         plan.hidx = &w->hidx;
         plan.pidx = &w->pidx;
         set_index_args(plan.ar, w);
-        if (!seg) a = plan.ar;
+        set_index_args(a, w);
+        plan.g.idx[0] = w->hidx.state;
+        plan.g.idx[1] = w->pidx.state;
         sp = &plan;
     }
     const LaunchShape sh = shape_of(c, tun);
@@ -1486,17 +1488,16 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
             return fail(c, CG_ESTATE, "check_transfers_2d under capture: make one call on this stream first");
         rc = reserve_sidx(c, w);
         if (rc) return rc;
-        w->hidx.ratio = w->pidx.ratio = c->shadow_index == 2 ? 0u : c->sidx_ratio;
+        w->hidx.always = w->pidx.always = c->shadow_index == 2 ? 1u : 0u;
         set_index_args(a, w);
-        HIPTRY(c, launch_sidx_reset(w->hidx, w->pidx, s));
     }
     HIPTRY(c, launch_classify_2d(a, recs_dev, w->pitch, s));
     if (idx) {
         HIPTRY(c, launch_sidx_build(w->hidx, w->pidx, a.st, s));
-        HIPTRY(c, launch_sidx_query(a, w->hidx, w->pidx, a.bsum, s, w->pitch));
+        HIPTRY(c, launch_sidx_query(a, w->hidx, w->pidx, s, w->pitch));
         HIPTRY(c, launch_reweigh(a, s));
     }
-    HIPTRY(c, launch_scan_sums(a, sh.tile_units, (a.lds_meta ? sh.grid : scan_grid(sh)) * (sh.block / 64), s));
+    HIPTRY(c, launch_scan_sums(a, sh, s));
     HIPTRY(c, launch_prefix_tiles(a, s));
     if (capturing) {
         HIPTRY(c, launch_batched(a, sh, s));

@@ -8,34 +8,34 @@
 // unaddressable one (A = 0, host sources only); for the valid bytes of a host
 // destination, the first unaddressable one.  The ranges themselves were
 // judged by k_classify's lookups.  Here the parts of each shadow space the
-// batch reads heavily (its steps of 4,096 chunks that some record reads) are
-// read once into two sorted lists: the chunks holding an undefined byte, with
-// its mask and the undefined bytes of all chunks before it, and the chunks
-// holding an unaddressable byte, with its mask.  A record's facts then come
-// from two binary searches per list and the masks of its edge chunks: its
-// range lies inside listed steps, so the entries between its searches are
-// all of its faulty chunks.  The spaces are the host region (V and A bits) and the shadow pool
-// (V only; addressability there is the allocation table's).  An index is
-// built when the batch's valid bytes in its space reach `ratio` times the
-// space's length, and is valid when both lists fit their capacity; a record
+// batch reads (its granules of 256 chunks, 4 KiB of V, that some record reads)
+// are read once into two sorted lists: the chunks holding an undefined byte,
+// with its mask and the undefined bytes of all chunks before it, and the
+// chunks holding an unaddressable byte, with its mask.  A record's facts then
+// come from two binary searches per list and the masks of its edge chunks: its
+// range lies inside listed granules, so the entries between its searches are
+// all of its faulty chunks.  The spaces are the host region (V and A bits) and
+// the shadow pool (V only; addressability there is the allocation table's).
+// An index is built when reading the listed granules costs less than the scan
+// it saves (worth), and is valid when both lists fit their capacity; a record
 // whose spaces all have a valid index is answered and leaves the scan, any
 // other is scanned as before.  The facts are exact, so verdicts do not depend
-// on the choice.
+// on the choice.  Each kernel works both spaces in one launch.
 //
-//   k_sidx_reset   one lane: both states = {0, ...}
 //   (k_classify adds the batch's valid bytes per space to state[0], and
-//   marks the steps of 4,096 chunks that its records read)
+//   marks the granules that its records read)
 //   k_sidx_mark_count, k_sidx_mark_list
-//                  the marked steps as an ascending list (marks cleared)
-//   k_sidx_count   block b over its contiguous slice of the listed steps of
+//                  the marked granules as an ascending list (marks cleared)
+//   k_sidx_count   block b over its contiguous slice of the listed granules of
 //                  the host region, then of the pool: list entries and
-//                  undefined bytes
-//   k_sidx_scan    one block: the blocks' offsets, the totals, validity
+//                  undefined bytes; every block stops once the lists overflow
+//   k_sidx_scan    a block per space: the blocks' offsets, the totals, validity
 //   k_sidx_fill    block b writes its entries in chunk order (a block with
 //                  none returns at once)
 //   k_sidx_query   one lane per record: answers the records of a check
-//                  without propagation whose spaces are indexed, and takes
-//                  their units out of the scan
+//                  without propagation whose spaces are indexed, takes their
+//                  units out of the scan, and redoes the scan's block-local
+//                  prefix
 //   k_sidx_rows    one wave per pitched 2D record whose rows follow row 0:
 //                  the same, with the list entries of its span mapped onto
 //                  its rows
@@ -47,14 +47,18 @@ namespace xc {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4u __attribute__((aligned(4)));
 template <typename T> using gcptr = const __attribute__((address_space(1))) T *;
 
 constexpr int kT = 256;
-constexpr uint32_t kPer = 16;                          // chunks per thread per step
-constexpr uint64_t kStep = (uint64_t)kT * kPer;        // chunks per block per step
-static_assert(kStep * 16 == (1ull << kIdxStepShift), "a step is the marks' unit");
+constexpr uint32_t kPer = 16;                          // granules worked side by side
+constexpr uint64_t kGran = 1ull << (kIdxGranShift - 4);   // chunks per granule
+static_assert(kGran == kT, "a chunk of a granule per thread");
 constexpr uint32_t kMarkT = 1024;                      // threads of the marking kernels
-constexpr uint64_t kMarkBlock = 16ull * kMarkT;        // marks per block of them (16 per thread)
+constexpr uint32_t kMarkPer = 4;                       // steps per thread of them
+constexpr uint64_t kMarkBlock = (uint64_t)kMarkPer * kMarkT;   // steps per block
+constexpr uint32_t kPerStep = 1u << (kIdxStepShift - kIdxGranShift);   // granules per step
+static_assert(kPerStep == 16, "a step's granules are 16 bits");
 
 // one bit per non-zero byte of w (SWAR: no carry crosses a byte)
 __device__ __forceinline__ uint32_t nz4(uint32_t w)
@@ -82,24 +86,28 @@ __device__ __forceinline__ Space space_of(uint32_t space, const DevState *st)
     return Space{reinterpret_cast<const uint8_t *>(st->pool), nullptr, st->pool_len};
 }
 
-__device__ __forceinline__ Space space_of(const ShadowIndex &x, const DevState *st) { return space_of(x.space, st); }
-
 __device__ __forceinline__ uint64_t space_chunks(const Space &S) { return (S.len + 15) >> 4; }
 
-__device__ __forceinline__ uint64_t space_steps(const Space &S) { return (space_chunks(S) + kStep - 1) / kStep; }
+__device__ __forceinline__ uint64_t space_steps(const Space &S) { return (S.len + (1ull << kIdxStepShift) - 1) >> kIdxStepShift; }
+__device__ __forceinline__ uint64_t space_grans(const Space &S) { return (S.len + (1ull << kIdxGranShift) - 1) >> kIdxGranShift; }
 
-// the index is built for this batch: a space whose steps fit the step list,
-// and enough of the batch's bytes in it
-__device__ __forceinline__ bool worth(const ShadowIndex &x, const Space &S)
+// The index is built for this batch: a space whose steps fit the marks, and
+// less to read than the scan would.  The counting pass streams its granules at
+// 6.5-7 TB/s; the scan works a batch's bytes at 4-5 TB/s, most of it short of
+// that; and the pass, its lists and the query cost about 25 us more, the scan
+// of about 96 MiB (2,000 requests, 354 MB in 187 MB of granules: 151 us
+// scanned, 135 us indexed).
+__device__ __forceinline__ bool worth(const ShadowIndex &x, const Space &S, uint64_t grans)
 {
-    return S.len > 0 && space_steps(S) <= x.steps_cap && (x.ratio == 0 || x.state[0] / x.ratio >= S.len);
+    if (S.len == 0 || space_steps(S) > x.steps_cap || grans == 0) return false;
+    return x.always || x.state[0] >= (grans << kIdxGranShift) / 4 * 3 + (96ull << 20);
 }
 
-// positions [p0, p1) of the step list that block b works
+// positions [p0, p1) of the granule list that block b works, whole groups of kPer
 __device__ __forceinline__ void block_slice(const ShadowIndex &x, uint32_t b, uint64_t *p0, uint64_t *p1)
 {
     const uint64_t m = x.state[kIdxSteps];
-    const uint64_t per = (m + x.grid - 1) / x.grid;
+    const uint64_t per = ((m + x.grid - 1) / x.grid + kPer - 1) / kPer * kPer;
     *p0 = (uint64_t)b * per < m ? (uint64_t)b * per : m;
     *p1 = *p0 + per < m ? *p0 + per : m;
 }
@@ -143,24 +151,6 @@ __device__ void block_scan3(uint64_t x[3], uint64_t ex[3], uint64_t tot[3])
     __syncthreads();   // ws is reused by the next call
 }
 
-__global__ void k_sidx_reset(ShadowIndex h, ShadowIndex p)
-{
-    for (int k = 0; k < 8; ++k) {
-        h.state[k] = 0;
-        p.state[k] = 0;
-    }
-}
-
-// The marks of steps m0 .. m0 + 15 as bits, for a space of `steps` steps
-// (none when the index is not built; every step of the space when the batch
-// asked for all of them).
-__device__ __forceinline__ uint32_t marked16(const ShadowIndex &x, uint64_t m0, uint64_t steps, bool all, u32x4 v)
-{
-    if (m0 >= steps) return 0;
-    const uint32_t live = steps - m0 >= 16 ? 0xFFFFu : (1u << (uint32_t)(steps - m0)) - 1u;
-    return (all ? 0xFFFFu : nz16(v)) & live;
-}
-
 __device__ __forceinline__ uint64_t block_sum(uint64_t v)
 {
     __shared__ uint64_t ws[kMarkT / 64];
@@ -173,46 +163,72 @@ __device__ __forceinline__ uint64_t block_sum(uint64_t v)
     return all;
 }
 
-__device__ __forceinline__ u32x4 load_marks(const ShadowIndex &x, uint64_t m0)
+// The marked granules of steps s0 .. s0 + 3, 16 bits each, of a space of
+// `grans` granules (every one of them when the batch asked for all).
+__device__ __forceinline__ uint64_t marked(const ShadowIndex &x, uint64_t s0, uint64_t grans, bool all)
 {
-    return *reinterpret_cast<const u32x4 *>(x.smark + m0);
+    const uint32_t whole = *reinterpret_cast<const uint32_t *>(x.smark + s0);
+    const u32x4 *f = reinterpret_cast<const u32x4 *>(x.fmark + s0 * kPerStep);
+    u32x4 fine[kMarkPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kMarkPer; ++j) fine[j] = f[j];
+    uint64_t bits = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kMarkPer; ++j)
+        bits |= (uint64_t)(all || ((whole >> (8 * j)) & 0xFFu) ? 0xFFFFu : nz16(fine[j])) << (16 * j);
+    const uint64_t g0 = s0 * kPerStep;
+    if (g0 >= grans) return 0;
+    return grans - g0 >= 64 ? bits : bits & ((1ull << (grans - g0)) - 1ull);
 }
 
-// marked steps among block b's kMarkBlock marks
-__global__ void __launch_bounds__(kMarkT) k_sidx_mark_count(ShadowIndex x, const DevState *stp)
+// marked granules among block b's kMarkBlock steps
+__global__ void __launch_bounds__(kMarkT) k_sidx_mark_count(ShadowIndex h, ShadowIndex p, const DevState *stp)
 {
-    const Space S = space_of(x, stp);
-    const uint64_t steps = worth(x, S) ? space_steps(S) : 0;
-    const uint64_t m0 = (uint64_t)blockIdx.x * kMarkBlock + 16ull * threadIdx.x;
-    const bool all = x.state[kIdxAll] != 0;
-    const uint32_t bits = m0 < steps ? marked16(x, m0, steps, all, all ? u32x4{0, 0, 0, 0} : load_marks(x, m0)) : 0u;
-    const uint64_t n = block_sum((uint64_t)__builtin_popcount(bits));
+    const ShadowIndex &x = blockIdx.y ? p : h;
+    if (blockIdx.x >= x.mark_grid) return;
+    const uint64_t grans = space_grans(space_of(blockIdx.y, stp));
+    const uint64_t s0 = (uint64_t)blockIdx.x * kMarkBlock + kMarkPer * threadIdx.x;
+    const uint64_t n = block_sum(s0 * kPerStep < grans ? (uint64_t)__popcll(marked(x, s0, grans, x.state[kIdxAll] != 0)) : 0);
     if (threadIdx.x == 0) x.mcnt[blockIdx.x] = n;
 }
 
-// Block b lists its marked steps after those of the blocks before it and
-// clears its marks (all of them, listed or not); block 0 writes the list's
-// length.  Each block adds the bytes the counting pass will read for its steps.
-__global__ void __launch_bounds__(kMarkT) k_sidx_mark_list(ShadowIndex x, const DevState *stp)
+// Block b lists its marked granules after those of the blocks before it, when
+// the index is worth its cost, and clears its marks; block 0 writes the list's
+// length (0: not built).  Each block adds the bytes the counting pass will
+// read for its granules.
+__global__ void __launch_bounds__(kMarkT) k_sidx_mark_list(ShadowIndex h, ShadowIndex p, const DevState *stp)
 {
     __shared__ uint64_t ws[kMarkT / 64];
-    const Space S = space_of(x, stp);
-    const uint64_t steps = worth(x, S) ? space_steps(S) : 0;
+    const ShadowIndex &x = blockIdx.y ? p : h;
+    if (blockIdx.x >= x.mark_grid) return;
+    const Space S = space_of(blockIdx.y, stp);
+    const uint64_t grans = space_grans(S);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+    const uint64_t s0 = (uint64_t)blockIdx.x * kMarkBlock + kMarkPer * tid;
+    if (blockIdx.x > 0 && (uint64_t)blockIdx.x * kMarkBlock * kPerStep >= grans) return;   // past the space: no marks
     uint64_t before = 0, total = 0;
-    for (uint32_t k = tid; k < gridDim.x; k += kMarkT) {
+    for (uint32_t k = tid; k < x.mark_grid; k += kMarkT) {
         const uint64_t c = x.mcnt[k];
         total += c;
         before += k < blockIdx.x ? c : 0;
     }
     before = block_sum(before);
     total = block_sum(total);
-    const uint64_t m0 = (uint64_t)blockIdx.x * kMarkBlock + 16ull * tid;
-    const u32x4 v = load_marks(x, m0);
-    const uint32_t bits = marked16(x, m0, steps, x.state[kIdxAll] != 0, v);
-    if (v.x | v.y | v.z | v.w) *reinterpret_cast<u32x4 *>(x.smark + m0) = u32x4{0, 0, 0, 0};
-    // block exclusive scan of the threads' marked steps
-    const uint64_t n = (uint64_t)__builtin_popcount(bits);
+    const bool build = worth(x, S, total);
+    const uint64_t bits = s0 * kPerStep < grans ? marked(x, s0, grans, x.state[kIdxAll] != 0) : 0;
+    if (bits) {   // (marks of granules past the space's end there are none)
+        *reinterpret_cast<uint32_t *>(x.smark + s0) = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kMarkPer; ++j)
+            *reinterpret_cast<u32x4 *>(x.fmark + (s0 + j) * kPerStep) = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        x.state[kIdxSteps] = build ? total : 0;
+        x.state[kIdxMarked] = total;
+    }
+    if (!build) return;
+    // block exclusive scan of the threads' marked granules
+    const uint64_t n = (uint64_t)__popcll(bits);
     uint64_t inc = n;
     for (uint32_t d = 1; d < 64u; d <<= 1) {
         const uint64_t y = __shfl_up(inc, d);
@@ -223,89 +239,132 @@ __global__ void __launch_bounds__(kMarkT) k_sidx_mark_list(ShadowIndex x, const 
     uint64_t off = before;
     for (uint32_t q = 0; q < w; ++q) off += ws[q];
     off += inc - n;
-    // the chunks the counting pass reads for these steps (the space's last step may be short)
+    // the chunks the counting pass reads for them (the space's last granule may be short)
     const uint64_t nch = space_chunks(S);
-    uint64_t chunks = 0;
-    for (uint32_t b = bits; b; b &= b - 1u) {
-        const uint64_t st = m0 + (uint64_t)__builtin_ctz(b);
-        x.slist[off++] = (uint32_t)st;
-        chunks += st * kStep + kStep <= nch ? kStep : nch - st * kStep;
+    uint64_t chunks = n * kGran;
+    if (bits) {
+        const uint64_t end = (s0 * kPerStep + 64u - (uint64_t)__builtin_clzll(bits)) * kGran;   // past the last one
+        if (end > nch) chunks -= end - nch;
+    }
+    for (uint32_t j = 0; j < kMarkPer; ++j) {
+        uint32_t b = (uint32_t)(bits >> (16 * j)) & 0xFFFFu;
+        const uint32_t g = (uint32_t)(s0 + j) * kPerStep;
+        if (b == 0xFFFFu) {   // a whole step: four 16-byte stores
+#pragma unroll
+            for (uint32_t q = 0; q < 16; q += 4)
+                *reinterpret_cast<u32x4u *>(x.slist + off + q) = u32x4{g + q, g + q + 1, g + q + 2, g + q + 3};
+            off += 16;
+            continue;
+        }
+        for (; b; b &= b - 1u) x.slist[off++] = g + (uint32_t)__builtin_ctz(b);
     }
     chunks = block_sum(chunks);
-    if (tid == 0) {
-        if (chunks) atomicAdd((unsigned long long *)x.read, (unsigned long long)(chunks * (x.space == 0 ? 18u : 16u)));
-        if (blockIdx.x == 0) x.state[kIdxSteps] = total;
-    }
+    if (tid == 0 && chunks)
+        atomicAdd((unsigned long long *)x.read, (unsigned long long)(chunks * (x.space == 0 ? 18u : 16u)));
 }
 
-// The counting pass of one index over block b's slice of its listed steps
-// (nothing when the index is not built).  A step's 16 chunks per thread are
-// loaded back to back (non-temporal: each byte is read once), then examined;
-// each wave flags the listed steps where it met a faulty chunk, so that the
-// fill reads only those.  The steps of the slice are read from the list 64 at
-// a time, one per lane.
+// The counting pass of one index over block b's slice of its listed granules
+// (nothing when the index is not built).  16 granules at a time, a chunk of
+// each per thread, are loaded back to back (non-temporal: each byte is read
+// once), then examined; each wave notes in which of the 16 it met a faulty
+// chunk, so that the fill reads only those.  The granules of the slice are
+// read from the list 64 at a time, one per lane.  A block that met list entries
+// adds them to the index's running count and stops when the lists are full, so
+// that a space dense with faults costs a few per cent of its bytes before the
+// scan takes over.  Bound by HBM: 48.8 GB at 6.8-7.0 TB/s, where a plain read
+// of the same shape reaches 0.87-0.89 of 8 TB/s.
 __device__ __forceinline__ void count_slice(const ShadowIndex &x, const Space &S)
 {
-    if (!worth(x, S)) return;
     const bool has_a = S.a16 != nullptr;   // the host region's A bits
     uint64_t p0, p1;
     block_slice(x, blockIdx.x, &p0, &p1);
     const uint64_t nch = space_chunks(S);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const gcptr<u32x4> vp = reinterpret_cast<gcptr<u32x4>>(reinterpret_cast<uint64_t>(S.v));
+    const gcptr<uint16_t> ap = reinterpret_cast<gcptr<uint16_t>>(reinterpret_cast<uint64_t>(S.a16));
+    const uint64_t full = S.len >> 4;   // chunks wholly inside the space
     uint64_t c3[3] = {0, 0, 0};
     for (uint64_t g = p0; g < p1; g += 64) {
-        const uint32_t mine = g + lane < p1 ? x.slist[g + lane] : 0u;
+        const uint32_t mine = x.slist[g + lane < p1 ? g + lane : p1 - 1];
         const uint32_t ng = p1 - g < 64 ? (uint32_t)(p1 - g) : 64u;
-        for (uint32_t k = 0; k < ng; ++k) {
-            const uint64_t base = (uint64_t)__builtin_amdgcn_readlane((int)mine, (int)k) * kStep;
-            const uint64_t hi = base + kStep < nch ? base + kStep : nch;
+        uint32_t found = 0;
+        for (uint32_t k = 0; k < ng; k += kPer) {
+            // the group's granules, in scalar registers; its last may be short
+            // of kPer granules, or hold the space's end
+            const uint32_t nk = ng - k < kPer ? ng - k : kPer;
+            const uint64_t top = (uint64_t)__builtin_amdgcn_readlane((int)mine, (int)(k + nk - 1)) * kGran + kGran;
             u32x4 v[kPer];
             uint32_t a[kPer];
-            if (base + kStep <= hi) {
+            const bool inside = nk == kPer && top <= full;
+            if (inside) {
 #pragma unroll
-                for (uint32_t j = 0; j < kPer; ++j) v[j] = __builtin_nontemporal_load(vp + base + (uint64_t)j * kT + threadIdx.x);
+                for (uint32_t j = 0; j < kPer; ++j) {
+                    const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(k + j)) * kGran;
+                    v[j] = __builtin_nontemporal_load(vp + c + threadIdx.x);
+                }
 #pragma unroll
-                for (uint32_t j = 0; j < kPer; ++j) a[j] = has_a ? (uint32_t)S.a16[base + (uint64_t)j * kT + threadIdx.x] : 0xFFFFu;
+                for (uint32_t j = 0; j < kPer; ++j) {
+                    const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(k + j)) * kGran;
+                    a[j] = has_a ? (uint32_t)ap[c + threadIdx.x] : 0xFFFFu;
+                }
             } else {
 #pragma unroll
                 for (uint32_t j = 0; j < kPer; ++j) {
-                    const uint64_t c = base + (uint64_t)j * kT + threadIdx.x;
                     v[j] = u32x4{0u, 0u, 0u, 0u};
                     a[j] = 0xFFFFu;
-                    if (c < hi) {
-                        v[j] = __builtin_nontemporal_load(vp + c);
-                        if (has_a) a[j] = S.a16[c];
+                    if (j < nk) {
+                        const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(k + j)) * kGran +
+                                           threadIdx.x;
+                        if (c < nch) {
+                            v[j] = __builtin_nontemporal_load(vp + c);
+                            if (has_a) a[j] = ap[c];
+                        }
                     }
                 }
             }
-            // almost every chunk is clean (V all 0, A all 1): the lane's step is
-            // examined chunk by chunk only when it is not, or when it holds the
-            // space's end (bytes past it must not count)
+            // almost every chunk is clean (V all 0, A all 1): the lane's chunks
+            // are examined one by one only when they are not
             uint32_t orv = 0, anda = 0xFFFFu;
 #pragma unroll
             for (uint32_t j = 0; j < kPer; ++j) {
                 orv |= v[j].x | v[j].y | v[j].z | v[j].w;
                 anda &= a[j];
             }
-            const bool edge = base + kStep > hi || ((S.len & 15u) && base + kStep >= nch);
-            uint32_t any = 0;
-            if (orv != 0u || anda != 0xFFFFu || edge) {
+            uint32_t any = 0;   // granules of the group where this lane met an entry
+            if (orv != 0u || anda != 0xFFFFu) {
 #pragma unroll
                 for (uint32_t j = 0; j < kPer; ++j) {
-                    const uint64_t c = base + (uint64_t)j * kT + threadIdx.x;
-                    // bytes past the space's end (its last chunk, or none) are clear
-                    const uint64_t left = c < hi ? S.len - 16 * c : 0;
-                    const uint32_t live = left < 16 ? (1u << left) - 1u : 0xFFFFu;
+                    uint32_t live = 0xFFFFu;
+                    if (!inside) {   // bytes past the space's end are clear
+                        const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, (int)((k + j) & 63u)) * kGran +
+                                           threadIdx.x;
+                        const uint64_t left = j < nk && c < nch ? S.len - 16 * c : 0;
+                        live = left < 16 ? (1u << left) - 1u : 0xFFFFu;
+                    }
                     const uint32_t und = nz16(v[j]) & a[j] & live, un = ~a[j] & live;
                     c3[0] += und ? 1u : 0u;
                     c3[1] += un ? 1u : 0u;
                     c3[2] += (uint32_t)__builtin_popcount(und);
-                    any |= und | un;
+                    found += (und ? 1u : 0u) + (un ? 1u : 0u);
+                    any |= (und | un) ? 1u << j : 0u;
                 }
             }
-            const uint64_t seen = __ballot(any != 0);
-            if (lane == 0) x.sflag[4 * (g + k) + wave] = seen ? 1u : 0u;
+            uint32_t seen = 0;
+            if (__ballot(any != 0)) {
+#pragma unroll
+                for (uint32_t j = 0; j < kPer; ++j) seen |= __ballot((any >> j) & 1u) ? 1u << j : 0u;
+            }
+            if (lane == 0) x.sflag[4 * ((g + k) / kPer) + wave] = (uint16_t)seen;
+        }
+        // entries met since the last look, and whether the lists are past full
+        // (waves of one block may leave at different granules: nothing below
+        // depends on the work skipped, since the index is then not valid)
+        if (__ballot(found != 0)) {
+            for (int d = 32; d >= 1; d >>= 1) found += (uint32_t)__shfl_xor((int)found, d);
+            uint64_t now = 0;
+            if (lane == 0) now = atomicAdd((unsigned long long *)&x.state[kIdxSeen], (unsigned long long)found) + found;
+            now = ((uint64_t)(uint32_t)__shfl((int)(now >> 32), 0) << 32) | (uint32_t)__shfl((int)(uint32_t)now, 0);
+            if (now > x.cap_u + x.cap_n) break;
         }
     }
     uint64_t ex[3], tot[3];
@@ -315,20 +374,23 @@ __device__ __forceinline__ void count_slice(const ShadowIndex &x, const Space &S
 }
 
 // Both indexes' counting passes in one launch: each block counts its slice of
-// the host region's listed steps, then its slice of the pool's, so that the
+// the host region's listed granules, then its slice of the pool's, so that the
 // shorter pass leaves no tail of its own (both indexes have the same grid).
 __global__ void __launch_bounds__(kT) k_sidx_count(ShadowIndex h, ShadowIndex p, const DevState *stp)
 {
 #pragma nounroll
-    for (uint32_t k = 0; k < 2; ++k) count_slice(k ? p : h, space_of(k, stp));
+    for (uint32_t k = 0; k < 2; ++k) {
+        const ShadowIndex &x = k ? p : h;
+        if (x.state[kIdxSteps]) count_slice(x, space_of(k, stp));
+    }
 }
 
 // offsets of the blocks' entries into [3 grid, 6 grid) of bcnt
-__global__ void __launch_bounds__(1024) k_sidx_scan(ShadowIndex x, const DevState *stp)
+__global__ void __launch_bounds__(1024) k_sidx_scan(ShadowIndex h, ShadowIndex p)
 {
     __shared__ uint64_t ws[16][3];
-    const Space S = space_of(x, stp);
-    if (!worth(x, S)) {
+    const ShadowIndex &x = blockIdx.x ? p : h;
+    if (x.state[kIdxSteps] == 0 || x.state[kIdxSeen] > x.cap_u + x.cap_n) {   // not built, or stopped half way
         if (threadIdx.x == 0) x.state[1] = 0;
         return;
     }
@@ -377,75 +439,62 @@ __global__ void __launch_bounds__(1024) k_sidx_scan(ShadowIndex x, const DevStat
     }
 }
 
-// The entries of one step of block b's range, in chunk order, at the running
-// offsets ou / on / op: here thread t takes the step's chunks 16 t .. 16 t + 15
-// (consecutive, so that one block scan of the threads' counts orders them).
-__device__ __forceinline__ void fill_step(const ShadowIndex &x, const Space &S, uint64_t base, uint64_t hi,
-                                          uint64_t &ou, uint64_t &on, uint64_t &op)
+// The entries of one granule, a chunk per thread, in chunk order at the
+// running offsets ou / on / op.
+__device__ __forceinline__ void fill_granule(const ShadowIndex &x, const Space &S, uint64_t base, uint64_t nch,
+                                             uint64_t &ou, uint64_t &on, uint64_t &op)
 {
-    const uint64_t c0 = base + (uint64_t)threadIdx.x * kPer;
-    uint32_t und[kPer], un[kPer];
-    uint64_t v[3] = {0, 0, 0};
-#pragma unroll
-    for (uint32_t j = 0; j < kPer; ++j) {
-        und[j] = un[j] = 0;
-        if (c0 + j < hi) chunk_faults(S, c0 + j, &und[j], &un[j]);
-        v[0] += und[j] ? 1u : 0u;
-        v[1] += un[j] ? 1u : 0u;
-        v[2] += (uint64_t)__builtin_popcount(und[j]);
-    }
+    const uint64_t c = base + threadIdx.x;
+    uint32_t und = 0, un = 0;
+    if (c < nch) chunk_faults(S, c, &und, &un);
+    uint64_t v[3] = {und ? 1u : 0u, un ? 1u : 0u, (uint64_t)__builtin_popcount(und)};
     uint64_t ex[3], tot[3];
     block_scan3(v, ex, tot);
-    uint64_t iu = ou + ex[0], in = on + ex[1], ip = op + ex[2];
-#pragma unroll
-    for (uint32_t j = 0; j < kPer; ++j) {
-        if (und[j]) {
-            x.uchunk[iu] = c0 + j;
-            x.umask[iu] = und[j];
-            x.ucum[iu] = ip;
-            ++iu;
-            ip += (uint64_t)__builtin_popcount(und[j]);
-        }
-        if (un[j]) {
-            x.nchunk[in] = c0 + j;
-            x.nmask[in] = un[j];
-            ++in;
-        }
+    if (und) {
+        const uint64_t i = ou + ex[0];
+        x.uchunk[i] = c;
+        x.umask[i] = und;
+        x.ucum[i] = op + ex[2];
+    }
+    if (un) {
+        const uint64_t i = on + ex[1];
+        x.nchunk[i] = c;
+        x.nmask[i] = un;
     }
     ou += tot[0];
     on += tot[1];
     op += tot[2];
 }
 
-// The block reads the flags of its slice 256 steps at a time, one per
-// thread, lists the flagged ones in order, and fills only those.
-__global__ void __launch_bounds__(kT) k_sidx_fill(ShadowIndex x, const DevState *stp)
+// The block reads its slice's flags 256 groups of granules at a time, one
+// group per thread, lists the flagged granules in order, and fills only those.
+__global__ void __launch_bounds__(kT) k_sidx_fill(ShadowIndex h, ShadowIndex p, const DevState *stp)
 {
-    __shared__ uint32_t list[kT];
-    __shared__ uint32_t nlist;
+    __shared__ uint32_t list[kT * kPer];
+    const ShadowIndex &x = blockIdx.y ? p : h;
     if (!x.state[1]) return;
-    const Space S = space_of(x, stp);
+    const Space S = space_of(blockIdx.y, stp);
     const uint32_t b = blockIdx.x;
     if (x.bcnt[3 * b] == 0 && x.bcnt[3 * b + 1] == 0) return;
     uint64_t p0, p1;
     block_slice(x, b, &p0, &p1);
     const uint64_t nch = space_chunks(S);
     uint64_t ou = x.bcnt[3 * (x.grid + b)], on = x.bcnt[3 * (x.grid + b) + 1], op = x.bcnt[3 * (x.grid + b) + 2];
-    for (uint64_t g0 = p0; g0 < p1; g0 += kT) {
-        const uint64_t g = g0 + threadIdx.x;
-        const uint32_t f = g < p1 && *reinterpret_cast<const uint32_t *>(x.sflag + 4 * g) != 0;
-        uint64_t v[3] = {f, 0, 0};
+    for (uint64_t g0 = p0; g0 < p1; g0 += kT * kPer) {
+        const uint64_t g = g0 + kPer * threadIdx.x;
+        uint32_t f = 0;
+        if (g < p1) {
+            const uint64_t q = *reinterpret_cast<const uint64_t *>(x.sflag + 4 * (g / kPer));
+            f = (uint32_t)(q | (q >> 16) | (q >> 32) | (q >> 48)) & 0xFFFFu;
+        }
+        uint64_t v[3] = {(uint64_t)__builtin_popcount(f), 0, 0};
         uint64_t ex[3], tot[3];
         block_scan3(v, ex, tot);
-        if (f) list[ex[0]] = (uint32_t)threadIdx.x;
-        if (threadIdx.x == 0) nlist = (uint32_t)tot[0];
+        for (uint32_t i = (uint32_t)ex[0]; f; f &= f - 1u) list[i++] = kPer * threadIdx.x + (uint32_t)__builtin_ctz(f);
         __syncthreads();
-        const uint32_t n = nlist;
-        for (uint32_t k = 0; k < n; ++k) {
-            const uint64_t base = (uint64_t)x.slist[g0 + list[k]] * kStep;
-            fill_step(x, S, base, base + kStep < nch ? base + kStep : nch, ou, on, op);
-        }
-        __syncthreads();   // list and nlist are rewritten next
+        const uint32_t n = (uint32_t)tot[0];
+        for (uint32_t k = 0; k < n; ++k) fill_granule(x, S, (uint64_t)x.slist[g0 + list[k]] * kGran, nch, ou, on, op);
+        __syncthreads();   // list is rewritten next
     }
 }
 
@@ -554,8 +603,7 @@ __device__ __forceinline__ void take_first(uint64_t *first, uint64_t off, int64_
 // With `pitch`, the positions are pitched 2D records: only those worked as
 // one transfer (kRowsContig, whose descriptor is that transfer's) are
 // answered, and their units per row go to 0.
-__global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, ShadowIndex p, uint64_t *wbsum,
-                                                   Pitch *pitch)
+__global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, ShadowIndex p, Pitch *pitch)
 {
     __shared__ uint64_t samp[3][kSamp];
     // the lists' samples: the host region's undefined and unaddressable
@@ -565,8 +613,10 @@ __global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, S
     const Sampled pu = sample_list(samp[2], p.uchunk, p.state[2], p.state[1] != 0);
     __syncthreads();
     const uint64_t t = (uint64_t)blockIdx.x * kT + threadIdx.x;
-    uint64_t removed = 0;
-    if (a.out && t < a.count && (!pitch || pitch[t].uniform == kRowsContig)) {
+    const bool none = h.state[1] == 0 && p.state[1] == 0;   // no index: nothing changes but the units to scan
+    if (pitch && none) return;
+    uint64_t units = !pitch && t < a.count ? a.weight[t] : 0;   // left to scan
+    if (!none && a.out && t < a.count && (!pitch || pitch[t].uniform == kRowsContig)) {
         const Desc d = a.desc[t];
         const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
         const bool has_src = d.v_hi > d.v_lo;
@@ -611,20 +661,18 @@ __global__ void __launch_bounds__(kT) k_sidx_query(BatchArgs a, ShadowIndex h, S
             a.desc[t].units = 0;
             a.weight[t] = 0;
             if (pitch) pitch[t].upr = 0;
-            removed = d.units - 1;   // its weight max(units, 1) becomes 1
+            units = 0;
         }
     }
-    // the block's weight sum as k_classify left it, for the segment plan
-    uint64_t r = removed;
-    for (int k = 32; k >= 1; k >>= 1) r += __shfl_xor(r, k);
-    __shared__ uint64_t wr[kT / 64];
-    if ((threadIdx.x & 63u) == 0) wr[threadIdx.x >> 6] = r;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t all = 0;
-        for (int k = 0; k < kT / 64; ++k) all += wr[k];
-        if (all) wbsum[blockIdx.x] -= all;
-    }
+    if (pitch) return;   // (k_reweigh follows, after the rows)
+    // the block's prefix and sum of the weights max(units, 1), as k_classify
+    // makes them, and whether a unit is left
+    if (__syncthreads_or(units != 0) && threadIdx.x == 0) atomicOr((unsigned long long *)&h.state[kIdxLeft], 1ull);
+    if (none) return;   // (k_classify's stand)
+    uint64_t v[3] = {t < a.count ? (units ? units : 1) : 0, 0, 0}, ex[3], tot[3];
+    block_scan3(v, ex, tot);
+    if (t < a.count) a.local[t] = ex[0];
+    if (threadIdx.x == 0) a.bsum[blockIdx.x] = tot[0];
 }
 
 // One side of a pitched record in a shadow space: byte c of row r (r < R,
@@ -784,46 +832,39 @@ __global__ void __launch_bounds__(kT) k_sidx_rows(BatchArgs a, ShadowIndex h, Sh
 
 }  // namespace
 
-hipError_t launch_sidx_reset(const ShadowIndex &h, const ShadowIndex &p, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_sidx_reset, dim3(1), dim3(1), 0, s, h, p);
-    return hipGetLastError();
-}
-
 hipError_t launch_sidx_count(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s)
 {
     hipLaunchKernelGGL(k_sidx_count, dim3(h.grid), dim3(kT), 0, s, h, p, st);
     return hipGetLastError();
 }
 
-hipError_t launch_sidx_finish(const ShadowIndex &x, const DevState *st, hipStream_t s)
+hipError_t launch_sidx_finish(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sidx_scan, dim3(1), dim3(1024), 0, s, x, st);
-    hipLaunchKernelGGL(k_sidx_fill, dim3(x.grid), dim3(kT), 0, s, x, st);
+    hipLaunchKernelGGL(k_sidx_scan, dim3(2), dim3(1024), 0, s, h, p);
+    hipLaunchKernelGGL(k_sidx_fill, dim3(h.grid, 2), dim3(kT), 0, s, h, p, st);
     return hipGetLastError();
 }
 
-hipError_t launch_sidx_marks(const ShadowIndex &x, const DevState *st, hipStream_t s)
+hipError_t launch_sidx_marks(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sidx_mark_count, dim3(x.mark_grid), dim3(kMarkT), 0, s, x, st);
-    hipLaunchKernelGGL(k_sidx_mark_list, dim3(x.mark_grid), dim3(kMarkT), 0, s, x, st);
+    const dim3 grid(h.mark_grid > p.mark_grid ? h.mark_grid : p.mark_grid, 2);
+    hipLaunchKernelGGL(k_sidx_mark_count, grid, dim3(kMarkT), 0, s, h, p, st);
+    hipLaunchKernelGGL(k_sidx_mark_list, grid, dim3(kMarkT), 0, s, h, p, st);
     return hipGetLastError();
 }
 
 hipError_t launch_sidx_build(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s)
 {
-    hipError_t e = launch_sidx_marks(h, st, s);
-    if (e == hipSuccess) e = launch_sidx_marks(p, st, s);
+    hipError_t e = launch_sidx_marks(h, p, st, s);
     if (e == hipSuccess) e = launch_sidx_count(h, p, st, s);
-    if (e == hipSuccess) e = launch_sidx_finish(h, st, s);
-    return e != hipSuccess ? e : launch_sidx_finish(p, st, s);
+    return e != hipSuccess ? e : launch_sidx_finish(h, p, st, s);
 }
 
-hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const ShadowIndex &p, uint64_t *wbsum,
-                             hipStream_t s, Pitch *pitch)
+hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const ShadowIndex &p, hipStream_t s,
+                             Pitch *pitch)
 {
     const uint64_t blocks = (ar.count + kT - 1) / kT;
-    hipLaunchKernelGGL(k_sidx_query, dim3((uint32_t)blocks), dim3(kT), 0, s, ar, h, p, wbsum, pitch);
+    hipLaunchKernelGGL(k_sidx_query, dim3((uint32_t)blocks), dim3(kT), 0, s, ar, h, p, pitch);
     if (pitch) {
         const uint64_t wblocks = (ar.count + kT / 64 - 1) / (kT / 64);
         hipLaunchKernelGGL(k_sidx_rows, dim3((uint32_t)wblocks), dim3(kT), 0, s, ar, h, p, pitch);

@@ -148,10 +148,12 @@ struct BatchArgs {
     // destinations of device-to-host records), [1] in the shadow pool (device
     // sources); the indexes' cost test (shadowindex.hip)
     uint64_t *index_bytes[2];
-    // with index_bytes: per space, a byte per step of 4,096 chunks (64 KiB of
-    // V bytes), set to 1 for every step the batch's valid bytes fall in
-    // (mark_cap[k] steps), so that the index's counting pass reads only those
+    // with index_bytes: per space and step of 64 KiB of V bytes (mark_cap[k]
+    // steps), a byte set to 1 where the batch's valid bytes cover the step,
+    // and 16 bytes, one per granule of 4 KiB, for those they only touch, so
+    // that the index's counting pass reads only these
     uint8_t *index_mark[2];
+    uint8_t *index_fine[2];
     uint64_t mark_cap[2];
 };
 
@@ -162,11 +164,13 @@ struct BatchArgs {
 // its mask and the undefined bytes of all chunks before it, and every chunk
 // with an unaddressable byte (A = 0), in ascending order; a record's
 // findings in that space are then two searches per list instead of a scan
-// of its bytes.  Only the steps of 4,096 chunks that the batch's records
-// read are listed (marked by the classify kernels) and read; the list is cut
-// into `grid` contiguous slices, one per block.  state = {valid bytes of the
-// batch in the space, index valid, undefined-chunk entries,
-// unaddressable-chunk entries, steps listed, every step wanted, 0, 0}.
+// of its bytes.  Only the granules of 4 KiB that the batch's records read are
+// listed (marked by the classify kernels) and read; the list is cut into
+// `grid` contiguous slices, one per block.  state = {valid bytes of the batch
+// in the space, index valid, undefined-chunk entries, unaddressable-chunk
+// entries, granules listed, every granule wanted, entries counted so far,
+// whether units are left to scan (the host region's state only), granules
+// marked}; the scan's k_scan_sums puts it back to 0.
 struct ShadowIndex {
     uint64_t *uchunk;   // [cap_u + 1]: entry n_u holds ~0
     uint32_t *umask;    // [cap_u]
@@ -174,23 +178,25 @@ struct ShadowIndex {
     uint64_t *nchunk;   // [cap_n]
     uint32_t *nmask;    // [cap_n]
     uint64_t *bcnt;     // [6 * grid]: per block entries (u, n) and undefined bytes, then their offsets
-    uint64_t *state;    // [8]
-    uint8_t *sflag;     // [4 * steps_cap]: wave w of listed step i (4,096 chunks) met list entries
-    uint8_t *smark;     // [16384 * mark_grid]: steps the batch reads (set by the classify kernels)
-    uint32_t *slist;    // [steps_cap]: the steps listed, ascending
-    uint64_t *mcnt;     // [mark_grid]: marked steps per block of the marking kernels
+    uint64_t *state;    // [kIdxState]
+    uint16_t *sflag;    // [4 * steps_cap + 4]: which of the 16 listed granules of a group wave w met entries in
+    uint8_t *smark;     // [4096 * mark_grid]: steps the batch covers (set by the classify kernels)
+    uint8_t *fmark;     // [65536 * mark_grid]: granules of the steps it touches
+    uint32_t *slist;    // [16 * steps_cap]: the granules listed, ascending
+    uint64_t *mcnt;     // [mark_grid]: marked granules per block of the marking kernels
     uint64_t *read;     // bytes the counting passes read (V, and A for the host region), accumulated
     uint64_t steps_cap; // steps of the largest space indexed (a larger one is not)
     uint64_t cap_u, cap_n;
     uint32_t grid;
     uint32_t mark_grid;
     uint32_t space;     // 0 host region, 1 shadow pool
-    uint32_t ratio;     // built when the batch's valid bytes in the space reach ratio * its length
+    uint32_t always;    // built whatever it costs (else when it costs less than the scan it saves)
 };
 
 // ShadowIndex::state slots beyond the first four
-constexpr int kIdxSteps = 4, kIdxAll = 5;
+constexpr int kIdxSteps = 4, kIdxAll = 5, kIdxSeen = 6, kIdxLeft = 7, kIdxMarked = 8, kIdxState = 16;
 constexpr uint64_t kIdxStepShift = 16;   // a step is 2^16 bytes of V (4,096 chunks)
+constexpr uint64_t kIdxGranShift = 12;   // a granule is 2^12 bytes of V (256 chunks), 16 to a step
 
 // Cutting a batch's records into source-block segments (segment.hip).
 // rdesc / wbsum come from k_classify run over the records in their given
@@ -203,9 +209,14 @@ struct SegArgs {
     uint64_t *first;        // per record: first segment
     uint64_t *sbsum;        // per record block: segment sums, then their prefix
     uint32_t *srec;         // per segment: its record
-    uint64_t *meta;         // [0] segments, [1] log2 of the block size, [2] first host-source position
+    uint64_t *meta;         // [0] segments, [1] log2 of the block size, [2] first host-source position,
+                            // [3] in order: one segment per record, all with the same key
     uint32_t min_log2;      // smallest block size, log2
     uint32_t host_last;     // host-source segments sort after the others and weigh 0: k_host_lds works them
+    // when not null, the shadow indexes' states (host region, pool): nothing is
+    // left to scan when they answered every record, and a batch that reads few
+    // of its bytes again is left in its order (meta[3])
+    const uint64_t *idx[2];
     uint32_t key_bytes;     // 4 when every block index is below 2^31 (the host bit is then bit 31), else 8
 };
 
@@ -259,25 +270,23 @@ struct FillArgs {
 hipError_t launch_classify(const BatchArgs &a, hipStream_t s);
 // one lane per pitched 2D record: row 0 classified, Pitch, weight rows * upr,
 // verdict before any row is worked (check_transfers_2d)
-// the shadow indexes of a check-only batch worked as segments: reset before
-// k_classify, build after it, then answer the records whose every space has
-// a valid index and take them out of the scan (units to 0, wbsum per
-// classify block adjusted)
-hipError_t launch_sidx_reset(const ShadowIndex &h, const ShadowIndex &p, hipStream_t s);
+// the shadow indexes of a check-only batch: build after k_classify, then
+// answer the records whose every space has a valid index and take them out of
+// the scan (units to 0; the block-local prefix and block sums redone)
 // both indexes: marks, counting pass, finish
 hipError_t launch_sidx_build(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s);
-hipError_t launch_sidx_marks(const ShadowIndex &x, const DevState *st, hipStream_t s);
+hipError_t launch_sidx_marks(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s);
 hipError_t launch_sidx_count(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s);
-hipError_t launch_sidx_finish(const ShadowIndex &x, const DevState *st, hipStream_t s);
-hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const ShadowIndex &p, uint64_t *wbsum,
-                             hipStream_t s, Pitch *pitch = nullptr);   // pitch: positions are 2D records
+hipError_t launch_sidx_finish(const ShadowIndex &h, const ShadowIndex &p, const DevState *st, hipStream_t s);
+// pitch: positions are 2D records; then launch_reweigh follows
+hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const ShadowIndex &p, hipStream_t s,
+                             Pitch *pitch = nullptr);
 // the block-local prefix and block sums of max(units, 1) again, after the
-// shadow indexes have answered records of a batch in its given order
+// shadow indexes have answered pitched records
 hipError_t launch_reweigh(const BatchArgs &a, hipStream_t s);
 hipError_t launch_classify_2d(const BatchArgs &a, const cg_transfer2d *recs2d, Pitch *pitch, hipStream_t s);
-uint32_t scan_grid(const LaunchShape &sh);   // workgroups of the scan kernel
-// waves: of the scan kernel's grid (its tiles)
-hipError_t launch_scan_sums(const BatchArgs &a, uint32_t tile_units, uint32_t waves, hipStream_t s);
+// tiles for the scan kernel's waves
+hipError_t launch_scan_sums(const BatchArgs &a, const LaunchShape &sh, hipStream_t s);
 hipError_t launch_prefix_tiles(const BatchArgs &a, hipStream_t s);
 // the persistent scan kernel, then (a.lds_meta) the host-source positions in LDS
 hipError_t launch_batched(const BatchArgs &a, const LaunchShape &sh, hipStream_t s);

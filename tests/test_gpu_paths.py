@@ -214,3 +214,41 @@ def test_rows_at_edges(X, width, pitch):
     o = util.oracle_for(w)
     want = o.run2d(rec, propagate=True)
     compare_state(H, w, base, sizes, o, lambda dw: check2d(X, dw, rec, X.CG_CHECK | X.CG_PROPAGATE), want)
+
+
+@pytest.mark.parametrize("knobs", [{}, {"XC_SHADOW_INDEX": "2"}, {"XC_SHADOW_INDEX": "2", "XC_SIDX_CAP": "40"},
+                                   {"XC_REORDER_MIN": "1"}, {"XC_REORDER_MIN": "1", "XC_SHADOW_INDEX": "2"},
+                                   {"XC_REORDER_MIN": "1", "XC_SHADOW_INDEX": "2", "XC_SIDX_CAP": "40"},
+                                   {"XC_REORDER_MIN": "1", "XC_SHADOW_INDEX": "0"}])
+def test_ranges_at_granule_edges(X, knobs, monkeypatch):
+    """Checks whose ranges start and end within a byte of the index's granules
+    (4 KiB) and steps (64 KiB), with faults on both sides of them: answered
+    from the index, left to the scan by its cost or by full lists, worked as
+    segments and in their order.  Run twice on one stream, so that the second
+    batch finds the marks and states the first left."""
+    from paper_1310_0901_amd import harness as H
+    from tests import util
+    for k, v in knobs.items():
+        monkeypatch.setenv(k, v)
+    rng = np.random.default_rng(77)
+    hl, T = 5 * 65_536 + 4096 + 3, 700
+    sizes = np.array([3 * 65_536 + 9, 4096, 200_000, 1])
+    w, base = edge_world(rng, hl, sizes, dens=0.0002)
+    cuts = np.array([c + d for c in list(range(0, hl, 4096)) + [hl] for d in (-1, 0, 1) if 0 <= c + d <= hl])
+    kind = rng.choice(3, T, p=[0.5, 0.2, 0.3])
+    pair = np.sort(rng.choice(cuts, (T, 2)), 1)
+    n = np.maximum(pair[:, 1] - pair[:, 0], 1)
+    host = W.HOST_BASE + np.minimum(pair[:, 0], hl - n)
+    j = rng.choice([0, 0, 0, 1, 2, 3], T)
+    n = np.where(kind == 0, n, np.minimum(n, sizes[j]))
+    dev = base[j] + (rng.random(T) * (sizes[j] - np.minimum(n, sizes[j]) + 1)).astype(np.int64) // 4096 * 4096
+    other = base[2] + rng.integers(0, 100, T)
+    rec = W.make_records(kind, np.where(kind == 0, host, dev).astype(np.uint64),
+                         np.where(kind == 1, host, other).astype(np.uint64), n.astype(np.uint64))
+    o = util.oracle_for(w)
+    dw = H.DeviceWorld(w)
+    try:
+        for part in (rec, rec[350:], rec[:300]):
+            util.assert_verdicts_equal(dw.check(part), o.run(part), f"{knobs} {len(part)}")
+    finally:
+        dw.close()
