@@ -74,6 +74,16 @@ void destroy_graph(GraphEntry &g)
         if (x) (void)hipGraphDestroy(x);
 }
 
+// A check issued: its completion event (one of the context's pool, recorded
+// once behind the check and shared by everything that waits for it) and its
+// number.  A finished check's event goes back to the pool and may be recorded
+// again, so an event is waited for only while its check is not known to be
+// done.
+struct Use {
+    hipEvent_t ev = nullptr;
+    uint64_t seq = 0;
+};
+
 struct Workspace {
     uint64_t cap = 0;
     Desc *desc = nullptr;
@@ -85,8 +95,7 @@ struct Workspace {
     SmallAcc *small = nullptr;      // small_max accumulators of the one-launch path (k_small)
     Pitch *pitch = nullptr;         // per position of a pitched 2D batch (allocated on first use)
     uint64_t pitch_cap = 0;
-    hipEvent_t done = nullptr;      // recorded after every check issued on this stream
-    bool used = false;
+    Use last;                       // the last check issued on this stream
     std::vector<GraphEntry> graphs;
     // large batches worked as source-block segments (allocated on first use):
     // per record the classify output and first segment, per segment its
@@ -108,15 +117,14 @@ struct TimingPair {
 };
 
 // One version of the device table: sorted base | end | off | top | mid | fine arrays and
-// the DevState that points at them.  `uses` holds, per stream, an event
-// recorded after the last check on that stream that read this version.
+// the DevState that points at them.  `uses` holds, per stream, the last check
+// on that stream that read this version.
 struct TableVersion {
     uint64_t *tab = nullptr;
     DevState *st = nullptr;
     uint64_t n = 0;
-    std::map<hipStream_t, hipEvent_t> uses;
-    hipEvent_t fixed_use = nullptr;   // after the last check_transfers_noalloc call that read this version
-    bool fixed_used = false;
+    std::map<hipStream_t, Use> uses;
+    Use fixed;   // the last check_transfers_noalloc call that read it (no entry of a map, which would allocate)
 };
 
 // Row expansion of pitched 2D copies on one stream.
@@ -178,6 +186,7 @@ struct cg_ctx {
     std::deque<InFlight> inflight;
     std::vector<hipEvent_t> ev_pool;
     uint64_t check_seq = 0, done_seq = 0;
+    Use last_fixed;                // the last check_transfers_noalloc call
     Region region{0, 0, nullptr, nullptr};
     // fills: a ring of staging buffers so that a new fill rarely waits for
     // the copy of an earlier one
@@ -186,8 +195,12 @@ struct cg_ctx {
     bool fill_busy[kFillSlots] = {};
     int fill_next = 0;
     // ordering
+    // the context stream's latest state: its event is recorded when a check
+    // first has to wait for that state, and no check waits once it is known to
+    // have happened
     hipEvent_t ev_ctx = nullptr;
-    uint64_t ctx_seq = 0;          // records of ev_ctx so far
+    bool ctx_recorded = false, ctx_done = false;
+    uint64_t ctx_seq = 0;          // states so far
     std::map<hipStream_t, Workspace *> ws;
     std::map<hipStream_t, RaceWs> race_ws;   // concurrent-access joins, per stream
     uint64_t reorder_min = 16384;            // batches this large are worked as source-block segments
@@ -233,27 +246,47 @@ int hip_fail(cg_ctx *c, const char *what, hipError_t e)
         if (e_ != hipSuccess) return hip_fail(ctx, #call, e_); \
     } while (0)
 
-// ctx stream waits for every check issued so far
-int ctx_begin(cg_ctx *c)
+// ctx stream waits for check u, unless that is known to be done
+int wait_use(cg_ctx *c, const Use &u)
 {
-    for (auto &kv : c->ws)
-        if (kv.second->used) HIPTRY(c, hipStreamWaitEvent(c->s, kv.second->done, 0));
+    if (u.seq > c->done_seq) HIPTRY(c, hipStreamWaitEvent(c->s, u.ev, 0));
     return CG_OK;
 }
 
+// ctx stream waits for every check issued so far
+int ctx_begin(cg_ctx *c)
+{
+    for (auto &kv : c->ws) {
+        int rc = wait_use(c, kv.second->last);
+        if (rc) return rc;
+    }
+    return wait_use(c, c->last_fixed);
+}
+
+// work was added to the ctx stream
 int ctx_end(cg_ctx *c)
 {
-    HIPTRY(c, hipEventRecord(c->ev_ctx, c->s));
+    c->ctx_recorded = c->ctx_done = false;
     ++c->ctx_seq;
     return CG_OK;
 }
 
-// Stream s waits for the context's latest state (a table version, fills).
-// Every check waits: a stream handle may be a destroyed stream's, reused.
-int wait_ctx(cg_ctx *c, Workspace *w, hipStream_t s)
+// Stream s waits for the context's latest state (a table version, fills),
+// unless that is known to have happened; whatever stream the handle names, it
+// then has nothing to wait for.  (A stream under capture always gets the wait,
+// which refuses the capture.)
+int wait_ctx(cg_ctx *c, hipStream_t s)
 {
+    if (!c->ctx_recorded) {
+        HIPTRY(c, hipEventRecord(c->ev_ctx, c->s));
+        c->ctx_recorded = true;
+    }
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+        if (!c->ctx_done) c->ctx_done = hipEventQuery(c->ev_ctx) == hipSuccess;
+        if (c->ctx_done) return CG_OK;
+    }
     HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
-    w->ctx_seen = c->ctx_seq;
     return CG_OK;
 }
 
@@ -267,8 +300,12 @@ int materialize(cg_ctx *c)
     if (!c->full_dirty && c->pend_del.empty() && c->pend_ins.empty()) return CG_OK;
     const int t = (c->cur + 1) % kVersions;
     TableVersion &nv = c->ver[t], &ov = c->ver[c->cur];
-    for (auto &kv : nv.uses) HIPTRY(c, hipStreamWaitEvent(c->s, kv.second, 0));
-    if (nv.fixed_used) HIPTRY(c, hipStreamWaitEvent(c->s, nv.fixed_use, 0));
+    for (auto &kv : nv.uses) {
+        int rc = wait_use(c, kv.second);
+        if (rc) return rc;
+    }
+    int rc = wait_use(c, nv.fixed);
+    if (rc) return rc;
     const uint64_t n = c->table.size();
     const uint64_t M = c->max_allocs;
     uint32_t shift = 0;
@@ -487,7 +524,6 @@ int get_ws(cg_ctx *c, hipStream_t s, uint64_t count, Workspace **out)
     auto it = c->ws.find(s);
     if (it == c->ws.end()) {
         w = new Workspace();
-        HIPTRY(c, hipEventCreateWithFlags(&w->done, hipEventDisableTiming));
         c->ws[s] = w;
     } else {
         w = it->second;
@@ -754,7 +790,7 @@ int debug_conflicts(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, hipS
     return CG_OK;
 }
 
-int note_use(cg_ctx *c, hipStream_t s);
+int note_use(cg_ctx *c, hipStream_t s, Workspace *w = nullptr);
 
 // Checks without propagation of at least reorder_min records and at most
 // kSegMaxRecords are worked as source-block segments unless the caller keeps
@@ -885,8 +921,9 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
     if (rc) return rc;
     rc = materialize(c);
     if (rc) return rc;
-    rc = wait_ctx(c, w, s);
+    rc = wait_ctx(c, s);
     if (rc) return rc;
+    w->ctx_seen = c->ctx_seq;
     if ((mode & CG_DEBUG_CONFLICTS) && (mode & CG_PROPAGATE)) {
         rc = debug_conflicts(c, recs, count, s);
         if (rc) return rc;
@@ -989,24 +1026,26 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
             HIPTRY(c, hipGraphLaunch(ge->exec, s));
         }
     }
-    HIPTRY(c, hipEventRecord(w->done, s));
-    w->used = true;
-    return note_use(c, s);
+    return note_use(c, s, w);
 }
 
 // Bookkeeping after work on stream s that reads the current table version:
 // the version's ring slot is not overwritten, and pool blocks freed later are
 // not reused, before that work has finished.
-int note_use(cg_ctx *c, hipStream_t s)
+int note_use(cg_ctx *c, hipStream_t s, Workspace *w)
 {
-    hipEvent_t &vu = c->ver[c->cur].uses[s];
-    if (!vu) HIPTRY(c, hipEventCreateWithFlags(&vu, hipEventDisableTiming));
-    HIPTRY(c, hipEventRecord(vu, s));
     hipEvent_t ev;
     if (c->ev_pool.empty()) HIPTRY(c, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     else { ev = c->ev_pool.back(); c->ev_pool.pop_back(); }
-    HIPTRY(c, hipEventRecord(ev, s));
-    c->inflight.push_back(InFlight{++c->check_seq, ev});
+    const hipError_t e = hipEventRecord(ev, s);
+    if (e != hipSuccess) {
+        c->ev_pool.push_back(ev);
+        return hip_fail(c, "hipEventRecord", e);
+    }
+    const Use u{ev, ++c->check_seq};
+    c->ver[c->cur].uses[s] = u;
+    if (w) w->last = u;
+    c->inflight.push_back(InFlight{u.seq, ev});
     if (c->inflight.size() > 256) retire(c, false);
     return CG_OK;
 }
@@ -1085,21 +1124,20 @@ SmallAcc *scratch_of(int dev)
     return dev >= 0 && dev < kMaxDevices ? g_scratch[dev] : nullptr;
 }
 
-// note_use for check_transfers_noalloc: the version's own event, and an event
-// from the pool (made by cg_create) for the pool blocks' quarantine; when the
-// pool is empty, finished checks give theirs back first
+// note_use for check_transfers_noalloc, with an event of the pool that
+// cg_create made; when the pool is empty, finished checks give theirs back
+// first
 int note_use_fixed(cg_ctx *c, hipStream_t s)
 {
-    TableVersion &v = c->ver[c->cur];
-    HIPTRY(c, hipEventRecord(v.fixed_use, s));
-    v.fixed_used = true;
     if (c->ev_pool.empty()) retire(c, false);
     if (c->ev_pool.empty()) retire(c, true);
     if (c->ev_pool.empty()) return fail(c, CG_ESTATE, "no pooled event");
     const hipEvent_t ev = c->ev_pool.back();
+    const hipError_t e = hipEventRecord(ev, s);
+    if (e != hipSuccess) return hip_fail(c, "hipEventRecord", e);
     c->ev_pool.pop_back();
-    HIPTRY(c, hipEventRecord(ev, s));
-    c->inflight.push_back(InFlight{++c->check_seq, ev});
+    c->ver[c->cur].fixed = c->last_fixed = Use{ev, ++c->check_seq};
+    c->inflight.push_back(InFlight{c->check_seq, ev});
     if (c->inflight.size() > 256) retire(c, false);
     return CG_OK;
 }
@@ -1198,8 +1236,6 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
     c->tuning_prop.unroll = 2;
     c->tuning_prop.nontemporal = 0;
     // events that check_transfers_noalloc records, made here so that it makes none
-    for (auto &v : c->ver)
-        if (hipEventCreateWithFlags(&v.fixed_use, hipEventDisableTiming) != hipSuccess) return bail(CG_EHIP);
     for (int k = 0; k < kPooledEvents; ++k) {
         hipEvent_t e;
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail(CG_EHIP);
@@ -1220,7 +1256,6 @@ int cg_destroy(cg_ctx *c)
     (void)hipDeviceSynchronize();
     for (auto &kv : c->ws) {
         free_ws(kv.second);
-        if (kv.second->done) (void)hipEventDestroy(kv.second->done);
         delete kv.second;
     }
     for (auto &kv : c->race_ws) race_release(kv.second);
@@ -1247,8 +1282,6 @@ int cg_destroy(cg_ctx *c)
     for (auto &v : c->ver) {
         (void)hipFree(v.tab);
         (void)hipFree(v.st);
-        for (auto &kv : v.uses) (void)hipEventDestroy(kv.second);
-        if (v.fixed_use) (void)hipEventDestroy(v.fixed_use);
     }
     for (auto &f : c->inflight) (void)hipEventDestroy(f.ev);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
@@ -1422,7 +1455,8 @@ int check_transfers_noalloc(cg_ctx *c, const cg_transfer *recs_dev, uint64_t cou
     const hipStream_t s = (hipStream_t)hip_stream;
     int rc = materialize(c);
     if (rc) return rc;
-    HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
+    rc = wait_ctx(c, s);
+    if (rc) return rc;
     BatchArgs a{};
     a.recs = recs_dev;
     a.count = count;
@@ -1473,8 +1507,9 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
     } else {
         rc = materialize(c);
         if (rc) return rc;
-        rc = wait_ctx(c, w, s);
+        rc = wait_ctx(c, s);
         if (rc) return rc;
+        w->ctx_seen = c->ctx_seq;
     }
     BatchArgs a = make_args(c, w, nullptr, count, out_dev, mode);
     a.pitch = w->pitch;
@@ -1507,9 +1542,7 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
     if (tp) HIPTRY(c, hipEventRecord(tp->a, s));
     HIPTRY(c, launch_batched(a, sh, s));
     if (tp) HIPTRY(c, hipEventRecord(tp->b, s));
-    HIPTRY(c, hipEventRecord(w->done, s));
-    w->used = true;
-    return note_use(c, s);
+    return note_use(c, s, w);
 }
 
 int check_transfers_2d(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, cg_verdict *out_dev, uint32_t mode,
@@ -1593,7 +1626,8 @@ int check_pointers(cg_ctx *c, const uint64_t *ptrs_dev, uint64_t count, cg_ptr_c
     const hipStream_t s = (hipStream_t)hip_stream;
     int rc = materialize(c);
     if (rc) return rc;
-    HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
+    rc = wait_ctx(c, s);
+    if (rc) return rc;
     HIPTRY(c, launch_pointers(c->ver[c->cur].st, c->state.table.nmid, (uint32_t)c->cu_count, ptrs_dev, count, out_dev, s));
     return note_use(c, s);
 }

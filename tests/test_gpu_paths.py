@@ -252,3 +252,51 @@ def test_ranges_at_granule_edges(X, knobs, monkeypatch):
             util.assert_verdicts_equal(dw.check(part), o.run(part), f"{knobs} {len(part)}")
     finally:
         dw.close()
+
+
+def test_state_order_over_many_checks(X):
+    """700 checks on four streams without a host wait, the shadow and the
+    allocations they read changed between them: each check sees exactly the
+    changes made before it (its completion event is shared by what waits for
+    it, and comes back from the pool after 256 checks)."""
+    n, K = 70_000, 700
+    hv = torch.zeros(4096, dtype=torch.uint8, device="cuda")
+    ha = torch.full((64,), -1, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    ctx = X.cg_create(0, 8 << 20, 64)
+    try:
+        X.cg_host_register(ctx, W.HOST_BASE, 4096, hv.data_ptr(), ha.data_ptr())
+        a, b = W.DEV_BASE, W.DEV_BASE + (1 << 20)
+        X.shadow_alloc(ctx, a, n)
+        X.shadow_alloc(ctx, b, n)
+        X.shadow_set(ctx, b, n, 0)
+        rec = W.make_records([2], np.array([a], np.uint64), np.array([b], np.uint64), np.array([n], np.uint64))
+        rt = torch.from_numpy(rec.view(np.uint8).copy()).cuda()
+        out = torch.zeros((K, 4), dtype=torch.int64, device="cuda")
+        streams = [torch.cuda.Stream() for _ in range(3)] + [torch.cuda.current_stream()]
+        torch.cuda.synchronize()
+        rng = np.random.default_rng(5)
+        undef, live, want = n, True, []
+        for k in range(K):
+            x = rng.random()
+            if x < 0.4 and live:
+                m = int(rng.integers(1, n))
+                X.shadow_set(ctx, a, n, 0)
+                X.shadow_set(ctx, a + n - m, m, 0xFF)
+                undef = m
+            elif x < 0.5:
+                if live:
+                    X.shadow_free(ctx, a)
+                else:
+                    X.shadow_alloc(ctx, a, n)
+                    undef = n
+                live = not live
+            call = X.check_transfers if rng.random() < 0.7 else X.check_transfers_noalloc
+            st = streams[int(rng.integers(4))] if call is X.check_transfers else streams[3]
+            call(ctx, rt.data_ptr(), 1, out[k].data_ptr(), X.CG_CHECK, st.cuda_stream)
+            want.append((X.CG_SRC_UNDEF, n - undef, undef, n) if live else (X.CG_SRC_UNALLOC, 0, 0, 0))
+        torch.cuda.synchronize()
+        bad = np.flatnonzero((out.cpu().numpy() != np.array(want, np.int64)).any(1))
+        assert bad.size == 0, (bad[:10], out.cpu().numpy()[bad[:3]], [want[i] for i in bad[:3]])
+    finally:
+        X.cg_destroy(ctx)
