@@ -16,7 +16,8 @@
 // 32-bit epoch.  When the epochs never decrease in record order, no epoch
 // spans more than 4,096 records and they average at least 256 (a program's
 // synchronisation windows), each epoch's intervals are instead sorted in LDS
-// by one block, in place, and the global passes all skip.  An interval then
+// by one block, in place, and the global passes all skip; a batch of at most
+// 4,096 records, whatever its epochs, is ordered by one block.  An interval then
 // meets an interval of another stream that starts no later exactly when the
 // furthest last byte among earlier intervals of other streams of its epoch
 // reaches its first byte, and one that starts later exactly when the smallest
@@ -72,41 +73,14 @@ __device__ __forceinline__ Iv interval_of(const cg_transfer &t, uint64_t i)
     return v;
 }
 
-// first pass keys: every interval's first byte (dead ones too, where they
-// land does not matter), its id with kDead when it touches nothing
-__global__ __launch_bounds__(kT) void k_race_keys(const cg_transfer *recs, uint64_t m, uint64_t *keys, uint32_t *vals,
-                                                  uint64_t *parts, uint32_t *flag)
-{
-    __shared__ uint64_t part[kWaves];
-    const uint64_t i = (uint64_t)blockIdx.x * kT + threadIdx.x;
-    if (i == 0) {
-        flag[0] = 0;
-        flag[1] = 0;
-    }
-    const uint64_t k0 = recs[0].src;
-    uint64_t x = 0;
-    if (i < m) {
-        const Iv v = interval_of(recs[i >> 1], i);
-        keys[i] = v.first;
-        vals[i] = (uint32_t)i | (v.live ? 0u : kDead);
-        x = v.first ^ k0;
-    }
-    for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t y = 0;
-        for (int w = 0; w < kWaves; ++w) y |= part[w];
-        parts[blockIdx.x] = y;
-    }
-}
-
 // ---- per-epoch sort --------------------------------------------------------
 
 // flag[0] becomes non-zero unless the epochs never decrease and no epoch
 // spans more than kRunMax records (equal epochs kRunMax records apart mean a
 // longer one, since they never decrease); flag[1] counts the epochs.  Without
-// epochs all records are one epoch.
+// epochs all records are one epoch.  Both start at 0 and k_race_finalize
+// leaves them there (one that a failed launch leaves set only costs the next
+// join the per-epoch path).
 __global__ __launch_bounds__(kT) void k_race_local_check(const uint32_t *epochs, uint64_t count, uint32_t *flag)
 {
     const uint64_t i = (uint64_t)blockIdx.x * kT + threadIdx.x;
@@ -129,39 +103,175 @@ __device__ __forceinline__ bool local_path(const uint32_t *flag, uint64_t count)
     return flag[0] == 0 && (uint64_t)flag[1] * kRunMean <= count;
 }
 
-// One block per chunk of kRunMax records sorts, in place, the intervals of
-// every epoch that starts in the chunk (at most kRunMax records, so at most
-// kLocalN intervals) by first byte, with a stable LSD radix sort in LDS and
-// 8-bit digits: each key travels with its index in the epoch's run, element
-// e of the run sits in wave e / 512, round (e / 64) % 8, lane e % 64, ranks
-// come from ballots as in the global sort, and a pass whose digit is the same
-// in every key is skipped.  Dead intervals sort by their address like the
-// others; the sweep skips them wherever they are.  The chunk's parts of the
-// key mask are cleared, so every pass of both global sorts skips.  The
-// write-back leaves what the sweep reads: the epoch as the key, the interval
-// id, and in the spare buffers and `first` each interval's last byte, stream
-// and first byte (k_race_gather fills them on the global path).
-__global__ __launch_bounds__(kLT) void k_race_local_sort(uint64_t *keys, uint32_t *vals, uint64_t *ends,
-                                                         uint32_t *strm, uint64_t *first, uint64_t *parts,
-                                                         uint64_t nparts, const cg_transfer *recs,
-                                                         const uint32_t *streams, const uint32_t *epochs,
-                                                         uint64_t count, const uint32_t *flag)
+// first pass keys of the global path: every interval's first byte (dead ones
+// too, where they land does not matter), its id with kDead when it touches
+// nothing.  On the per-epoch path the parts are cleared instead, so that every
+// pass of both global sorts skips.
+__global__ __launch_bounds__(kT) void k_race_keys(const cg_transfer *recs, uint64_t m, uint64_t *keys, uint32_t *vals,
+                                                  uint64_t *parts, const uint32_t *flag, uint64_t count)
 {
-    __shared__ uint64_t buf[kLocalN];
-    __shared__ uint16_t bix[kLocalN];
-    __shared__ uint32_t wrun[kLWaves][256];   // per wave and digit: running count, then prefix over waves
-    __shared__ uint32_t dstart[256];
-    __shared__ uint32_t wtot[kLWaves];
-    __shared__ uint64_t wor[kLWaves];
+    __shared__ uint64_t part[kWaves];
+    if (local_path(flag, count)) {
+        if (threadIdx.x == 0) parts[blockIdx.x] = 0;
+        return;
+    }
+    const uint64_t i = (uint64_t)blockIdx.x * kT + threadIdx.x;
+    const uint64_t k0 = recs[0].src;
+    uint64_t x = 0;
+    if (i < m) {
+        const Iv v = interval_of(recs[i >> 1], i);
+        keys[i] = v.first;
+        vals[i] = (uint32_t)i | (v.live ? 0u : kDead);
+        x = v.first ^ k0;
+    }
+    for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t y = 0;
+        for (int w = 0; w < kWaves; ++w) y |= part[w];
+        parts[blockIdx.x] = y;
+    }
+}
+
+// The block's shared memory for sorting a run of up to kLocalN keys.
+struct RunSort {
+    uint64_t buf[kLocalN];
+    uint16_t bix[kLocalN];
+    uint32_t wrun[kLWaves][256];   // per wave and digit: running count, then prefix over waves
+    uint32_t dstart[256];
+    uint32_t wtot[kLWaves];
+    uint64_t wor[kLWaves];
+    uint64_t k0;
+};
+
+// How a run of n keys lies in the block: every wave takes `per` * 64
+// consecutive elements, as few rounds as all waves together need, so that a
+// short run costs one round a pass and not eight.
+struct RunLayout {
+    uint32_t n, per, waves;
+    __device__ __forceinline__ explicit RunLayout(uint32_t n_)
+        : n(n_), per((n_ + kLT - 1) / kLT), waves((n_ + 64 * per - 1) / (64 * per))
+    {
+    }
+    __device__ __forceinline__ uint32_t elem(int i) const
+    {
+        return ((threadIdx.x >> 6) * per + (uint32_t)i) * 64 + (threadIdx.x & 63);
+    }
+    // element i of this lane exists (false from a wave-uniform round on)
+    __device__ __forceinline__ bool has(int i) const { return (uint32_t)i < per && elem(i) < n; }
+};
+
+// Stable LSD radix sort of a run's keys, 8-bit digits, with each key's index
+// ix; ranks come from ballots as in the global sort, and a pass whose digit is
+// the same in every key is skipped.
+__device__ __forceinline__ void sort_run(RunSort &S, uint64_t (&k)[kLRounds], uint32_t (&ix)[kLRounds],
+                                         const RunLayout &at)
+{
+    const uint32_t w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (threadIdx.x == 0) S.k0 = k[0];
+    __syncthreads();
+    uint64_t x = 0;
+#pragma unroll
+    for (int i = 0; i < kLRounds; ++i)
+        if (at.has(i)) x |= k[i] ^ S.k0;
+    for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d);
+    if (l == 0) S.wor[w] = x;
+    __syncthreads();
+    uint64_t live = 0;
+    for (int j = 0; j < kLWaves; ++j) live |= S.wor[j];
+    for (int sh = 0; sh < 64; sh += 8) {
+        if (((live >> sh) & 0xFFu) == 0) continue;   // the same digit everywhere: skip the pass
+        for (int j = threadIdx.x; j < kLWaves * 256; j += kLT) (&S.wrun[0][0])[j] = 0;
+        __syncthreads();
+        uint32_t pk[kLRounds];
+#pragma unroll
+        for (int i = 0; i < kLRounds; ++i) {
+            pk[i] = 0xFFFFFFFFu;
+            if ((uint32_t)i >= at.per) continue;
+            const bool valid = at.has(i);
+            const uint32_t d = (uint32_t)(k[i] >> sh) & 0xFFu;
+            const uint64_t peers = match8(d, valid);
+            const uint32_t rank = (uint32_t)__popcll(peers & lanes_below());
+            uint32_t run = 0;
+            if (valid) run = S.wrun[w][d];
+            if (valid && rank == 0) S.wrun[w][d] = run + (uint32_t)__popcll(peers);
+            pk[i] = valid ? (d << 16) | (run + rank) : 0xFFFFFFFFu;
+        }
+        __syncthreads();
+        uint32_t tot = 0;
+        if (threadIdx.x < 256)
+            for (uint32_t j = 0; j < at.waves; ++j) {
+                const uint32_t c = S.wrun[j][threadIdx.x];
+                S.wrun[j][threadIdx.x] = tot;
+                tot += c;
+            }
+        uint32_t inc = tot;
+        for (uint32_t d = 1; d < 64u; d <<= 1) {
+            const uint32_t y = __shfl_up(inc, d);
+            if (l >= d) inc += y;
+        }
+        if (threadIdx.x < 256 && l == 63) S.wtot[w] = inc;
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            uint32_t off = 0;
+            for (uint32_t j = 0; j < w; ++j) off += S.wtot[j];
+            S.dstart[threadIdx.x] = off + inc - tot;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kLRounds; ++i)
+            if (pk[i] != 0xFFFFFFFFu) {
+                const uint32_t d = pk[i] >> 16;
+                const uint32_t pos = S.dstart[d] + S.wrun[w][d] + (pk[i] & 0xFFFFu);
+                S.buf[pos] = k[i];
+                S.bix[pos] = (uint16_t)ix[i];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kLRounds; ++i) {
+            if (at.has(i)) {
+                k[i] = S.buf[at.elem(i)];
+                ix[i] = S.bix[at.elem(i)];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Where the sorted order of a join goes: the epochs and interval ids, and in
+// the spare buffers and `first` each interval's last byte, stream and first
+// byte (k_race_gather fills these on the global path).
+struct Order {
+    uint64_t *keys, *ends, *first;
+    uint32_t *vals, *strm;
+};
+
+__device__ __forceinline__ void put_interval(const Order &o, uint64_t p, uint64_t iv, uint32_t ep,
+                                             const cg_transfer *recs, const uint32_t *streams)
+{
+    const Iv v = interval_of(recs[iv >> 1], iv);
+    o.keys[p] = ep;
+    o.vals[p] = (uint32_t)iv | (v.live ? 0u : kDead);
+    o.first[p] = v.first;
+    o.ends[p] = v.last;
+    o.strm[p] = streams[iv >> 1];
+}
+
+// One block per chunk of records sorts the intervals of every epoch that
+// starts in the chunk (at most kRunMax records, so at most kLocalN intervals)
+// by first byte, in LDS.  Dead intervals sort by their address like the
+// others; the sweep skips them wherever they are.
+__global__ __launch_bounds__(kLT) void k_race_local_sort(Order o, const cg_transfer *recs, const uint32_t *streams,
+                                                         const uint32_t *epochs, uint64_t count, uint32_t chunk,
+                                                         const uint32_t *flag)
+{
+    __shared__ RunSort S;
     __shared__ uint32_t starts[kRunMax];
     __shared__ uint32_t nstarts, run_len;
     if (!local_path(flag, count)) return;   // the whole grid leaves: the global sort runs
-    const uint32_t w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const uint64_t c0 = (uint64_t)blockIdx.x * kRunMax;
-    const uint64_t c1 = c0 + kRunMax < count ? c0 + kRunMax : count;
-    // parts cover 128 records each; the chunks tile the records, so every part is cleared once
-    const uint64_t p1 = (c1 + 127) / 128 < nparts ? (c1 + 127) / 128 : nparts;
-    for (uint64_t b = c0 / 128 + threadIdx.x; b < p1; b += kLT) parts[b] = 0;
+    const uint64_t c0 = (uint64_t)blockIdx.x * chunk;
+    const uint64_t c1 = c0 + chunk < count ? c0 + chunk : count;
     if (threadIdx.x == 0) nstarts = 0;
     __syncthreads();
     for (uint64_t i = c0 + threadIdx.x; i < c1; i += kLT) {
@@ -176,99 +286,75 @@ __global__ __launch_bounds__(kLT) void k_race_local_sort(uint64_t *keys, uint32_
         const uint32_t ep = epochs ? epochs[s] : 0u;
         if (threadIdx.x == 0) run_len = most;
         __syncthreads();
-        if (epochs)
+        // the run ends at the next start of the chunk; the chunk's last one is followed
+        bool last = true;
+        for (uint32_t j = threadIdx.x; j < ns; j += kLT)
+            if (starts[j] > starts[r]) {
+                atomicMin(&run_len, starts[j] - starts[r]);
+                last = false;
+            }
+        if (__syncthreads_and(last) && epochs) {
             for (uint32_t j = 1 + threadIdx.x; j < most; j += kLT)
                 if (epochs[s + j] != ep) atomicMin(&run_len, j);
+        }
         __syncthreads();
-        const uint32_t n = 2 * run_len;   // intervals of this epoch
+        const RunLayout at(2 * run_len);   // intervals of this epoch
         const uint64_t i0 = 2 * s;
-        const uint64_t k0 = keys[i0];
         uint64_t k[kLRounds];
         uint32_t ix[kLRounds];
-        uint64_t x = 0;
 #pragma unroll
         for (int i = 0; i < kLRounds; ++i) {
-            const uint32_t e = w * 512 + i * 64 + l;
-            k[i] = e < n ? keys[i0 + e] : ~0ull;
+            const uint32_t e = at.elem(i);
             ix[i] = e;
-            if (e < n) x |= k[i] ^ k0;
+            k[i] = at.has(i) ? interval_of(recs[(i0 + e) >> 1], i0 + e).first : ~0ull;
         }
-        for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d);
-        if (l == 0) wor[w] = x;
-        __syncthreads();
-        uint64_t live = 0;
-        for (int j = 0; j < kLWaves; ++j) live |= wor[j];
-        for (int sh = 0; sh < 64; sh += 8) {
-            if (((live >> sh) & 0xFFu) == 0) continue;   // the same digit everywhere: skip the pass
-            for (int j = threadIdx.x; j < kLWaves * 256; j += kLT) (&wrun[0][0])[j] = 0;
-            __syncthreads();
-            uint32_t pk[kLRounds];
+        sort_run(S, k, ix, at);
 #pragma unroll
-            for (int i = 0; i < kLRounds; ++i) {
-                const bool valid = w * 512 + i * 64 + l < n;
-                const uint32_t d = (uint32_t)(k[i] >> sh) & 0xFFu;
-                const uint64_t peers = match8(d, valid);
-                const uint32_t rank = (uint32_t)__popcll(peers & lanes_below());
-                uint32_t run = 0;
-                if (valid) run = wrun[w][d];
-                if (valid && rank == 0) wrun[w][d] = run + (uint32_t)__popcll(peers);
-                pk[i] = valid ? (d << 16) | (run + rank) : 0xFFFFFFFFu;
-            }
-            __syncthreads();
-            uint32_t tot = 0;
-            if (threadIdx.x < 256)
-                for (int j = 0; j < kLWaves; ++j) {
-                    const uint32_t c = wrun[j][threadIdx.x];
-                    wrun[j][threadIdx.x] = tot;
-                    tot += c;
-                }
-            uint32_t inc = tot;
-            for (uint32_t d = 1; d < 64u; d <<= 1) {
-                const uint32_t y = __shfl_up(inc, d);
-                if (l >= d) inc += y;
-            }
-            if (threadIdx.x < 256 && l == 63) wtot[w] = inc;
-            __syncthreads();
-            if (threadIdx.x < 256) {
-                uint32_t off = 0;
-                for (uint32_t j = 0; j < w; ++j) off += wtot[j];
-                dstart[threadIdx.x] = off + inc - tot;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < kLRounds; ++i)
-                if (pk[i] != 0xFFFFFFFFu) {
-                    const uint32_t d = pk[i] >> 16;
-                    const uint32_t pos = dstart[d] + wrun[w][d] + (pk[i] & 0xFFFFu);
-                    buf[pos] = k[i];
-                    bix[pos] = (uint16_t)ix[i];
-                }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < kLRounds; ++i) {
-                const uint32_t e = w * 512 + i * 64 + l;
-                if (e < n) {
-                    k[i] = buf[e];
-                    ix[i] = bix[e];
-                }
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < kLRounds; ++i) {
-            const uint32_t e = w * 512 + i * 64 + l;
-            if (e < n) {
-                const uint64_t iv = i0 + ix[i];
-                const Iv v = interval_of(recs[iv >> 1], iv);
-                keys[i0 + e] = ep;
-                vals[i0 + e] = (uint32_t)iv | (v.live ? 0u : kDead);
-                first[i0 + e] = v.first;
-                ends[i0 + e] = v.last;
-                strm[i0 + e] = streams[iv >> 1];
-            }
-        }
+        for (int i = 0; i < kLRounds; ++i)
+            if (at.has(i)) put_interval(o, i0 + at.elem(i), i0 + ix[i], ep, recs, streams);
         __syncthreads();
     }
+}
+
+// Records per block of k_race_local_sort: one round of blocks over the CUs
+// (each holds most of a CU's LDS), since a block takes its epochs one after
+// another.  5,000 records in epochs of 300 took 733 us, the whole join, in two
+// blocks of 4,096 records whose waves each held 512 elements, 154 us in 20 of
+// 256 with a short run spread over the waves.
+uint32_t local_chunk(uint64_t count)
+{
+    uint32_t c = 256;
+    while (c < kRunMax && ((uint64_t)c << 8) < count) c <<= 1;
+    return c;
+}
+
+// A batch of at most kRunMax records, whatever its epochs, by one block: by
+// first byte, then, stable, by epoch.  Nothing of the global path is launched:
+// 300 records in one epoch took 160 us with its 45 launches, 58 us with five;
+// 4,000 records 390 and 110 us.
+__global__ __launch_bounds__(kLT) void k_race_one_run(Order o, const cg_transfer *recs, const uint32_t *streams,
+                                                      const uint32_t *epochs, uint64_t count, uint64_t *mask)
+{
+    __shared__ RunSort S;
+    const RunLayout at(2u * (uint32_t)count);
+    if (threadIdx.x == 0) *mask = 0;   // the order is in the first pair of buffers
+    uint64_t k[kLRounds];
+    uint32_t ix[kLRounds];
+#pragma unroll
+    for (int i = 0; i < kLRounds; ++i) {
+        const uint32_t e = at.elem(i);
+        ix[i] = e;
+        k[i] = at.has(i) ? interval_of(recs[e >> 1], e).first : ~0ull;
+    }
+    sort_run(S, k, ix, at);
+    if (epochs) {
+#pragma unroll
+        for (int i = 0; i < kLRounds; ++i) k[i] = at.has(i) ? epochs[ix[i] >> 1] : ~0ull;
+        sort_run(S, k, ix, at);
+    }
+#pragma unroll
+    for (int i = 0; i < kLRounds; ++i)
+        if (at.has(i)) put_interval(o, at.elem(i), ix[i], epochs ? (uint32_t)k[i] : 0u, recs, streams);
 }
 
 // Second pass keys (global path): the epoch of each interval, in the order of
@@ -470,13 +556,28 @@ __device__ __forceinline__ Sorted sorted_view(const uint64_t *ka, const uint64_t
     return Sorted{b ? kb : ka, b ? ka : kb, first, b ? vb : va, b ? va : vb};
 }
 
-__device__ __forceinline__ Elem load_elem(const Sorted &o, uint64_t p, uint64_t m)
-{
-    if (p >= m) return make_elem(kNoRec, 0, 0, 0, kNoStream);
-    const uint32_t raw = o.V[p];
-    if (raw & kDead) return make_elem(raw, 0, 0, 0, kNoStream);
-    return make_elem(raw, (uint32_t)o.K[p], o.F[p], o.E[p], o.S[p]);
-}
+// what the sweep reads of kSweepItems intervals, in registers
+struct Items {
+    uint64_t first[kSweepItems], last[kSweepItems];
+    uint32_t raw[kSweepItems], ep[kSweepItems], s[kSweepItems];
+
+    // elements p, p + step, ...; every load is issued before the first is used
+    __device__ __forceinline__ void load(const Sorted &o, uint64_t p, uint32_t step, uint64_t m)
+    {
+#pragma unroll
+        for (int j = 0; j < kSweepItems; ++j) {
+            const uint64_t q = p + (uint64_t)j * step;
+            const bool in = q < m;
+            const uint64_t r = in ? q : m - 1;
+            raw[j] = in ? o.V[r] : kNoRec;
+            ep[j] = (uint32_t)o.K[r];
+            first[j] = o.F[r];
+            last[j] = o.E[r];
+            s[j] = o.S[r];
+        }
+    }
+    __device__ __forceinline__ Elem at(int j) const { return make_elem(raw[j], ep[j], first[j], last[j], s[j]); }
+};
 
 // first byte, last byte and stream of every sorted interval, written into
 // `first` and the ping-pong buffers that do not hold the sorted order
@@ -495,45 +596,44 @@ __global__ __launch_bounds__(kT) void k_race_gather(uint64_t *ka, uint64_t *kb, 
     (b ? va : vb)[p] = streams[iv >> 1];
 }
 
-// the four running combines: forward (last bytes) and backward (first
-// bytes), of all intervals and of writes
-struct Sweep {
-    Top2 fa, fw, ba, bw;
-};
-
 __device__ __forceinline__ Val fwd_val(const Elem &e) { return Val{kHere | e.ep, e.last}; }
 __device__ __forceinline__ Val bwd_val(const Elem &e) { return Val{kHere | (uint32_t)~e.ep, ~e.first}; }
 
-__device__ __forceinline__ void sweep_add_fwd(Sweep &x, const Elem &e)
+// one interval into the running combines of all intervals and of writes:
+// forward (last bytes), backward (first bytes)
+__device__ __forceinline__ void sweep_add_fwd(Top2 &a, Top2 &w, const Elem &e)
 {
     if (!e.valid) return;
     const Val v = fwd_val(e);
-    x.fa = t2_add(x.fa, v, e.s, e.r);
-    if (e.w) x.fw = t2_add(x.fw, v, e.s, e.r);
+    a = t2_add(a, v, e.s, e.r);
+    if (e.w) w = t2_add(w, v, e.s, e.r);
 }
 
-__device__ __forceinline__ void sweep_add_bwd(Sweep &x, const Elem &e)
+__device__ __forceinline__ void sweep_add_bwd(Top2 &a, Top2 &w, const Elem &e)
 {
     if (!e.valid) return;
     const Val v = bwd_val(e);
-    x.ba = t2_add(x.ba, v, e.s, e.r);
-    if (e.w) x.bw = t2_add(x.bw, v, e.s, e.r);
+    a = t2_add(a, v, e.s, e.r);
+    if (e.w) w = t2_add(w, v, e.s, e.r);
 }
 
-__global__ __launch_bounds__(kT) void k_race_sweep_reduce(const uint64_t *ka, const uint64_t *kb, const uint32_t *va,
-                                                          const uint32_t *vb, const uint64_t *first,
-                                                          const uint64_t *maskp, uint64_t m, Top2 *agg)
+__global__ __launch_bounds__(kT, 4) void k_race_sweep_reduce(const uint64_t *ka, const uint64_t *kb, const uint32_t *va,
+                                                             const uint32_t *vb, const uint64_t *first,
+                                                             const uint64_t *maskp, uint64_t m, Top2 *agg)
 {
     const Sorted o = sorted_view(ka, kb, va, vb, first, *maskp);
     // the combines do not depend on order: read the tile lane-contiguously
-    const uint64_t base = (uint64_t)blockIdx.x * kSweepTile + threadIdx.x;
-    Sweep x{t2_none(), t2_none(), t2_none(), t2_none()};
-    for (int j = 0; j < kSweepItems; ++j) {
-        const Elem e = load_elem(o, base + (uint64_t)j * kT, m);
-        sweep_add_fwd(x, e);
-        sweep_add_bwd(x, e);
-    }
-    const Top2 fa = block_all(x.fa), fw = block_all(x.fw), ba = block_all(x.ba), bw = block_all(x.bw);
+    Items t;
+    t.load(o, (uint64_t)blockIdx.x * kSweepTile + threadIdx.x, kT, m);
+    Top2 fa = t2_none(), fw = t2_none(), ba = t2_none(), bw = t2_none();
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) sweep_add_fwd(fa, fw, t.at(j));
+    fa = block_all(fa);
+    fw = block_all(fw);
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) sweep_add_bwd(ba, bw, t.at(j));
+    ba = block_all(ba);
+    bw = block_all(bw);
     if (threadIdx.x == 0) {
         Top2 *o = agg + (uint64_t)blockIdx.x * 4;
         o[0] = fa;
@@ -543,124 +643,127 @@ __global__ __launch_bounds__(kT) void k_race_sweep_reduce(const uint64_t *ka, co
     }
 }
 
-// per sweep tile: combine of the tiles before it (forward) and after it (backward)
+// per sweep tile: combine of the tiles before it (forward) and after it
+// (backward), one block per running combine (977 tiles of 1M records: one block
+// for all four 39 us, four blocks 13 us)
 __global__ __launch_bounds__(kT) void k_race_sweep_scan(const Top2 *agg, uint32_t tiles, Top2 *pre)
 {
+    const uint32_t q = blockIdx.x;   // fa, fw, ba, bw
     const uint32_t per = (tiles + kT - 1) / kT;
     const uint32_t lo = min(tiles, threadIdx.x * per), hi = min(tiles, lo + per);
-    Sweep c{t2_none(), t2_none(), t2_none(), t2_none()};
-    for (uint32_t b = lo; b < hi; ++b) {
-        c.fa = t2_combine(c.fa, agg[(uint64_t)b * 4 + 0]);
-        c.fw = t2_combine(c.fw, agg[(uint64_t)b * 4 + 1]);
-        c.ba = t2_combine(c.ba, agg[(uint64_t)b * 4 + 2]);
-        c.bw = t2_combine(c.bw, agg[(uint64_t)b * 4 + 3]);
-    }
-    Top2 fa = block_excl<true>(c.fa), fw = block_excl<true>(c.fw);
-    Top2 ba = block_excl<false>(c.ba), bw = block_excl<false>(c.bw);
-    for (uint32_t b = lo; b < hi; ++b) {
-        pre[(uint64_t)b * 4 + 0] = fa;
-        pre[(uint64_t)b * 4 + 1] = fw;
-        fa = t2_combine(fa, agg[(uint64_t)b * 4 + 0]);
-        fw = t2_combine(fw, agg[(uint64_t)b * 4 + 1]);
-    }
-    for (uint32_t b = hi; b > lo; --b) {
-        pre[(uint64_t)(b - 1) * 4 + 2] = ba;
-        pre[(uint64_t)(b - 1) * 4 + 3] = bw;
-        ba = t2_combine(ba, agg[(uint64_t)(b - 1) * 4 + 2]);
-        bw = t2_combine(bw, agg[(uint64_t)(b - 1) * 4 + 3]);
+    Top2 c = t2_none();
+    for (uint32_t b = lo; b < hi; ++b) c = t2_combine(c, agg[(uint64_t)b * 4 + q]);
+    if (q < 2) {
+        Top2 x = block_excl<true>(c);
+        for (uint32_t b = lo; b < hi; ++b) {
+            pre[(uint64_t)b * 4 + q] = x;
+            x = t2_combine(x, agg[(uint64_t)b * 4 + q]);
+        }
+    } else {
+        Top2 x = block_excl<false>(c);
+        for (uint32_t b = hi; b > lo; --b) {
+            pre[(uint64_t)(b - 1) * 4 + q] = x;
+            x = t2_combine(x, agg[(uint64_t)(b - 1) * 4 + q]);
+        }
     }
 }
 
-// per interval: a record of another stream it meets (writes: any access;
-// reads: writes), or kNoRec
-// LDS slot of tile element i: one pad slot per kSweepItems elements, so that
-// threads reading their own consecutive runs spread over the banks
+// A wave's kSweepItems * 64 elements, read lane after lane (x[j] of lane l is
+// element j * 64 + l), handed round so that every lane holds its own
+// consecutive run, through the wave's part of LDS: one pad slot per
+// kSweepItems elements spreads the runs over the banks.
+constexpr int kWaveRun = kSweepItems * 64;
+constexpr int kWaveSlots = kWaveRun + kWaveRun / kSweepItems;
 __device__ __forceinline__ int pad_slot(int i) { return i + i / kSweepItems; }
-constexpr int kSweepSlots = kSweepTile + kSweepTile / kSweepItems;
 
-__global__ __launch_bounds__(kT) void k_race_sweep_apply(const uint64_t *ka, const uint64_t *kb, const uint32_t *va,
-                                                         const uint32_t *vb, const uint64_t *first,
-                                                         const uint64_t *maskp, uint64_t m, const Top2 *pre,
-                                                         uint32_t *res)
+__device__ __forceinline__ void wave_order()
 {
-    __shared__ uint64_t sf[kSweepSlots], se[kSweepSlots];
-    __shared__ uint32_t sk[kSweepSlots], sv[kSweepSlots], ss[kSweepSlots];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T>
+__device__ __forceinline__ void wave_runs(T (&x)[kSweepItems], T *lds, int l)
+{
+    wave_order();
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) lds[pad_slot(j * 64 + l)] = x[j];
+    wave_order();
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) x[j] = lds[pad_slot(l * kSweepItems + j)];
+}
+
+// per interval: a record of another stream it meets (writes: any access;
+// reads: writes), or kNoRec.  Bound by how many waves are resident: with the
+// tile's five arrays kept in LDS (65 KB) two blocks fitted a CU and the 977
+// tiles of 1M records took two rounds, 67.5 us; in registers four blocks fit,
+// 42 us.
+__global__ __launch_bounds__(kT, 4) void k_race_sweep_apply(const uint64_t *ka, const uint64_t *kb, const uint32_t *va,
+                                                            const uint32_t *vb, const uint64_t *first,
+                                                            const uint64_t *maskp, uint64_t m, const Top2 *pre,
+                                                            uint32_t *res)
+{
+    __shared__ uint64_t runs[kWaves][kWaveSlots];
     const Sorted o = sorted_view(ka, kb, va, vb, first, *maskp);
-    const uint64_t tile = (uint64_t)blockIdx.x * kSweepTile;
-    // stage the tile through LDS: read lane-contiguously, walk per thread
-    for (int j = 0; j < kSweepItems; ++j) {
-        const int i = j * kT + threadIdx.x;
-        const uint64_t p = tile + i;
-        const int q = pad_slot(i);
-        sv[q] = kNoRec;
-        if (p < m) {
-            const uint32_t raw = o.V[p];
-            sv[q] = raw;
-            if (!(raw & kDead)) {
-                sk[q] = (uint32_t)o.K[p];
-                sf[q] = o.F[p];
-                se[q] = o.E[p];
-                ss[q] = o.S[p];
-            }
-        }
-    }
-    __syncthreads();
-    const int base = threadIdx.x * kSweepItems;
-    auto elem = [&](int j) {
-        const int q = pad_slot(base + j);
-        const uint32_t raw = sv[q];
-        if (raw & kDead) return make_elem(raw, 0, 0, 0, kNoStream);
-        return make_elem(raw, sk[q], sf[q], se[q], ss[q]);
-    };
-    Sweep own{t2_none(), t2_none(), t2_none(), t2_none()};
-    for (int j = 0; j < kSweepItems; ++j) {
-        const Elem e = elem(j);
-        sweep_add_fwd(own, e);
-        sweep_add_bwd(own, e);
-    }
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    Items t;
+    t.load(o, (uint64_t)blockIdx.x * kSweepTile + (uint64_t)w * kWaveRun + l, 64, m);
+    wave_runs(t.raw, (uint32_t *)runs[w], l);
+    wave_runs(t.ep, (uint32_t *)runs[w], l);
+    wave_runs(t.s, (uint32_t *)runs[w], l);
+    wave_runs(t.first, runs[w], l);
+    wave_runs(t.last, runs[w], l);
     const Top2 *P = pre + (uint64_t)blockIdx.x * 4;
-    Sweep x;
-    x.fa = t2_combine(P[0], block_excl<true>(own.fa));
-    x.fw = t2_combine(P[1], block_excl<true>(own.fw));
-    x.ba = t2_combine(P[2], block_excl<false>(own.ba));
-    x.bw = t2_combine(P[3], block_excl<false>(own.bw));
+    Top2 a = t2_none(), wr = t2_none();   // of all intervals, of writes
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) sweep_add_fwd(a, wr, t.at(j));
+    a = t2_combine(P[0], block_excl<true>(a));
+    wr = t2_combine(P[1], block_excl<true>(wr));
     uint32_t hit[kSweepItems];
 #pragma unroll
     for (int j = 0; j < kSweepItems; ++j) {
-        const Elem e = elem(j);
+        const Elem e = t.at(j);
         hit[j] = kNoRec;
         if (e.valid) {
             // an earlier interval of another stream, in this epoch, reaching this one's first byte
             Val va, vw;
             uint32_t ra, rw;
-            t2_other(x.fa, e.s, &va, &ra);
-            t2_other(x.fw, e.s, &vw, &rw);
+            t2_other(a, e.s, &va, &ra);
+            t2_other(wr, e.s, &vw, &rw);
             const Val v = e.w ? va : vw;
             if (v.h == (kHere | e.ep) && v.l >= e.first) hit[j] = e.w ? ra : rw;
         }
-        sweep_add_fwd(x, e);
+        sweep_add_fwd(a, wr, e);
     }
+    a = t2_none();
+    wr = t2_none();
+    // the run's own combine takes its intervals in ascending order too
+#pragma unroll
+    for (int j = 0; j < kSweepItems; ++j) sweep_add_bwd(a, wr, t.at(j));
+    a = t2_combine(P[2], block_excl<false>(a));
+    wr = t2_combine(P[3], block_excl<false>(wr));
 #pragma unroll
     for (int j = kSweepItems - 1; j >= 0; --j) {
-        const Elem e = elem(j);
+        const Elem e = t.at(j);
         if (e.valid && hit[j] == kNoRec) {
             // a later interval of another stream, in this epoch, starting at or before this one's last byte
             Val va, vw;
             uint32_t ra, rw;
-            t2_other(x.ba, e.s, &va, &ra);
-            t2_other(x.bw, e.s, &vw, &rw);
+            t2_other(a, e.s, &va, &ra);
+            t2_other(wr, e.s, &vw, &rw);
             const Val v = e.w ? va : vw;
             if (v.h == (kHere | (uint32_t)~e.ep) && ~v.l <= e.last) hit[j] = e.w ? ra : rw;
         }
-        sweep_add_bwd(x, e);
+        sweep_add_bwd(a, wr, e);
         if (e.present) res[e.iv] = hit[j];
     }
 }
 
 __global__ __launch_bounds__(kT) void k_race_finalize(const cg_transfer *recs, uint64_t count, const uint32_t *res,
-                                                      cg_race *out)
+                                                      cg_race *out, uint32_t *flag)
 {
     const uint64_t r = (uint64_t)blockIdx.x * kT + threadIdx.x;
+    if (r < 2) flag[r] = 0;   // for the next join
     if (r >= count) return;
     const cg_transfer t = recs[r];
     cg_race o;
@@ -693,6 +796,8 @@ hipError_t race_reserve(RaceWs &w, uint64_t intervals)
     get((void **)&w.res, intervals * sizeof(uint32_t));
     get((void **)&w.first, intervals * sizeof(uint64_t));
     get((void **)&w.flag, 64);
+    if (e == hipSuccess) e = hipMemset(w.flag, 0, 64);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     get(&w.agg, sweeps * 4 * sizeof(Top2));
     get(&w.pre, sweeps * 4 * sizeof(Top2));
     if (e != hipSuccess) {
@@ -720,34 +825,36 @@ hipError_t race_launch(RaceWs &w, const cg_transfer *recs, const uint32_t *strea
     const uint32_t sweeps = (uint32_t)ceil_div(m, kSweepTile);
     const uint32_t blocks = (uint32_t)ceil_div(m, kT);
     SortWs &q = w.sort;
-    hipLaunchKernelGGL(k_race_keys, dim3(blocks), dim3(kT), 0, s, recs, m, q.keys[0], q.vals[0], q.parts, w.flag);
-    hipLaunchKernelGGL(k_race_local_check, dim3((uint32_t)ceil_div(count, kT)), dim3(kT), 0, s, epochs, count, w.flag);
-    hipLaunchKernelGGL(k_race_local_sort, dim3((uint32_t)ceil_div(count, kRunMax)), dim3(kLT), 0, s, q.keys[0],
-                       q.vals[0], q.keys[1], q.vals[1], w.first, q.parts, ceil_div(m, kT), recs, streams, epochs, count,
-                       w.flag);
-    // without epochs, a batch of kRunMean to kRunMax records is one epoch that
-    // the per-epoch sort takes (as the device decides too): the global passes
-    // would all return at once, so they are not launched
-    const bool one_local_epoch = !epochs && count <= kRunMax && count >= kRunMean;
-    // first sort: by first byte
-    hipError_t e = one_local_epoch ? sort_mask_only(q, m, s) : sort_pairs(q, m, s);
-    if (e != hipSuccess) return e;
-    // second sort, stable: by epoch (all 0 without epochs: only the mask is taken,
-    // which then names keys[0] / vals[0], where the rekey moved the order)
-    if (!one_local_epoch)
+    const Order o{q.keys[0], q.keys[1], w.first, q.vals[0], q.vals[1]};
+    if (count <= kRunMax) {
+        hipLaunchKernelGGL(k_race_one_run, dim3(1), dim3(kLT), 0, s, o, recs, streams, epochs, count, q.mask);
+    } else {
+        hipLaunchKernelGGL(k_race_local_check, dim3((uint32_t)ceil_div(count, kT)), dim3(kT), 0, s, epochs, count, w.flag);
+        const uint32_t chunk = local_chunk(count);
+        hipLaunchKernelGGL(k_race_local_sort, dim3((uint32_t)ceil_div(count, chunk)), dim3(kLT), 0, s, o, recs, streams,
+                           epochs, count, chunk, w.flag);
+        hipLaunchKernelGGL(k_race_keys, dim3(blocks), dim3(kT), 0, s, recs, m, q.keys[0], q.vals[0], q.parts, w.flag,
+                           count);
+        // first sort: by first byte
+        hipError_t e = sort_pairs(q, m, s);
+        if (e != hipSuccess) return e;
+        // second sort, stable: by epoch (all 0 without epochs: only the mask is taken,
+        // which then names keys[0] / vals[0], where the rekey moved the order)
         hipLaunchKernelGGL(k_race_rekey, dim3(blocks), dim3(kT), 0, s, q.keys[0], q.vals[0], q.vals[1], q.mask, epochs,
                            m, q.parts, w.flag, count);
-    e = epochs ? sort_pairs(q, m, s, nullptr, 4) : sort_mask_only(q, m, s);
-    if (e != hipSuccess) return e;
+        e = epochs ? sort_pairs(q, m, s, nullptr, 4) : sort_mask_only(q, m, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_race_gather, dim3(blocks), dim3(kT), 0, s, q.keys[0], q.keys[1], q.vals[0], q.vals[1],
+                           w.first, q.mask, recs, streams, m, w.flag, count);
+    }
     Top2 *agg = (Top2 *)w.agg, *pre = (Top2 *)w.pre;
-    hipLaunchKernelGGL(k_race_gather, dim3(blocks), dim3(kT), 0, s, q.keys[0], q.keys[1], q.vals[0], q.vals[1], w.first,
-                       q.mask, recs, streams, m, w.flag, count);
     hipLaunchKernelGGL(k_race_sweep_reduce, dim3(sweeps), dim3(kT), 0, s, q.keys[0], q.keys[1], q.vals[0], q.vals[1],
                        w.first, q.mask, m, agg);
-    hipLaunchKernelGGL(k_race_sweep_scan, dim3(1), dim3(kT), 0, s, agg, sweeps, pre);
+    hipLaunchKernelGGL(k_race_sweep_scan, dim3(4), dim3(kT), 0, s, agg, sweeps, pre);
     hipLaunchKernelGGL(k_race_sweep_apply, dim3(sweeps), dim3(kT), 0, s, q.keys[0], q.keys[1], q.vals[0], q.vals[1],
                        w.first, q.mask, m, pre, w.res);
-    hipLaunchKernelGGL(k_race_finalize, dim3((uint32_t)ceil_div(count, kT)), dim3(kT), 0, s, recs, count, w.res, out);
+    hipLaunchKernelGGL(k_race_finalize, dim3((uint32_t)ceil_div(count, kT)), dim3(kT), 0, s, recs, count, w.res, out,
+                       w.flag);
     return hipGetLastError();
 }
 

@@ -20,17 +20,18 @@ constexpr int kRounds = kWaveItems / 64;
 static_assert(kT == kSortKeyBlock, "one part per block of the key kernels");
 
 // the key bits that differ anywhere: OR of the per-block partials
-__global__ __launch_bounds__(kT) void k_sort_mask(const uint64_t *parts, uint32_t nparts, uint64_t *mask)
+constexpr int kMaskT = 1024;
+__global__ __launch_bounds__(kMaskT) void k_sort_mask(const uint64_t *parts, uint32_t nparts, uint64_t *mask)
 {
-    __shared__ uint64_t part[kWaves];
+    __shared__ uint64_t part[kMaskT / 64];
     uint64_t x = 0;
-    for (uint32_t j = threadIdx.x; j < nparts; j += kT) x |= parts[j];
+    for (uint32_t j = threadIdx.x; j < nparts; j += kMaskT) x |= parts[j];
     for (int d = 32; d >= 1; d >>= 1) x |= __shfl_xor(x, d);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint64_t y = 0;
-        for (int w = 0; w < kWaves; ++w) y |= part[w];
+        for (int w = 0; w < kMaskT / 64; ++w) y |= part[w];
         *mask = y;
     }
 }
@@ -247,7 +248,7 @@ void sort_release(SortWs &w)
 hipError_t sort_mask_only(SortWs &w, uint64_t n, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sort_mask, dim3(1), dim3(kT), 0, s, w.parts, (uint32_t)ceil_div(n, kT), w.mask);
+    hipLaunchKernelGGL(k_sort_mask, dim3(1), dim3(kMaskT), 0, s, w.parts, (uint32_t)ceil_div(n, kT), w.mask);
     return hipGetLastError();
 }
 
@@ -256,7 +257,7 @@ hipError_t sort_pairs(SortWs &w, uint64_t n, hipStream_t s, const uint64_t *n_de
     if (n == 0) return hipSuccess;
     if (bytes < 1 || bytes > 8) return hipErrorInvalidValue;
     const uint32_t tiles = (uint32_t)ceil_div(n, kSortTile);
-    hipLaunchKernelGGL(k_sort_mask, dim3(1), dim3(kT), 0, s, w.parts, (uint32_t)ceil_div(n, kT), w.mask);
+    hipLaunchKernelGGL(k_sort_mask, dim3(1), dim3(kMaskT), 0, s, w.parts, (uint32_t)ceil_div(n, kT), w.mask);
     for (int pass = 0; pass < bytes; ++pass) {
         hipLaunchKernelGGL(k_sort_count, dim3(tiles), dim3(kT), 0, s, w.keys[0], w.keys[1], n, n_dev, tiles, w.mask,
                            pass, w.counts);

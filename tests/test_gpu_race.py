@@ -273,3 +273,20 @@ def test_full_size_sampled(X, ctx):
     # the same join twice gives the same results (the choice of partner included)
     again = gpu_join(X, ctx, b.records, b.streams, b.epochs)
     assert np.array_equal(again, res)
+
+
+@pytest.mark.parametrize("count", [1, 2, 255, 256, 257, 1023, 4095, 4096, 4097, 6200])
+def test_one_run(X, ctx, count):
+    """Around the size up to which one block orders the whole batch, with
+    epochs in any order; the same context joins a larger batch in between."""
+    i = np.arange(count)
+    rng = np.random.default_rng(count)
+    b = W.small_race(count=count, streams=5, epochs=1, seed=W.SEED0 + count)
+    big = W.small_race(count=9000, streams=5, epochs=3, seed=W.SEED0 + 1)
+    for kind, epochs in {"none": None, "one": np.full(count, 0xFFFFFFFF), "runs": i // 300,
+                         "shuffled": rng.integers(0, 4, count) << 20, "descending": (count - i) // 300,
+                         "each": i}.items():
+        ep = None if epochs is None else epochs.astype(np.uint32)
+        want = oracle.race(b.records, b.streams, ep, threads=8)
+        check(gpu_join(X, ctx, b.records, b.streams, ep), b.records, b.streams, ep, want)
+        gpu_join(X, ctx, big.records, big.streams, big.epochs)
