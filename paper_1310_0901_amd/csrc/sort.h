@@ -17,8 +17,8 @@ struct SortWs {
     uint64_t cap = 0;
     uint64_t *keys[2] = {nullptr, nullptr};
     uint32_t *vals[2] = {nullptr, nullptr};
-    uint32_t *counts = nullptr;   // per-digit, per-tile counts [256][tiles]
-    uint32_t *dtot = nullptr;     // per-digit totals [256]
+    uint64_t *look = nullptr;     // per tile and digit: its look-back word [tiles][256]
+    uint32_t *hist = nullptr;     // per byte and digit: keys [8][256]; then a ticket counter per pass [8]
     uint64_t *parts = nullptr;    // per key-building block: OR of (key ^ first key)
     uint64_t *mask = nullptr;     // key bits that differ anywhere
 };

@@ -290,3 +290,13 @@ def test_one_run(X, ctx, count):
         want = oracle.race(b.records, b.streams, ep, threads=8)
         check(gpu_join(X, ctx, b.records, b.streams, ep), b.records, b.streams, ep, want)
         gpu_join(X, ctx, big.records, big.streams, big.epochs)
+
+
+@pytest.mark.parametrize("count", [6143, 6144, 6145, 16_384, 16_385, 18_433, 40_000])
+def test_sort_tiles(X, ctx, count):
+    """The global sort (epochs in no order) at the edges of its tiles of 4,096
+    intervals and of the eight tiles a look-back step reads."""
+    b = W.small_race(count=count, streams=4, epochs=5, seed=W.SEED0 + count)
+    ep = np.random.default_rng(count).permutation(b.epochs).astype(np.uint32)
+    want = oracle.race(b.records, b.streams, ep, threads=8)
+    check(gpu_join(X, ctx, b.records, b.streams, ep), b.records, b.streams, ep, want)
