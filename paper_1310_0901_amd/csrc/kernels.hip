@@ -24,7 +24,8 @@
 //                  the kernels below work by position and send findings to
 //                  each position's record;
 //   k_scan_sums    one block: exclusive scan of the per-block sums, tile size;
-//   k_prefix_tiles global prefix; k_tile_starts first record of every tile;
+//   k_prefix_tiles global prefix; k_tile_starts first record of every tile
+//                  (k_plan_tiles: these three in one, up to 262,144 records);
 //   k_batched      persistent kernel: tiles of the flattened 16-byte unit space
 //                  (one tile per wave when the batch is small), for a
 //                  segmented batch one contiguous chunk per XCD, taken from
@@ -954,12 +955,18 @@ __device__ uint64_t classify_one(const BatchArgs &a, const DevState &st, uint64_
     return units;
 }
 
+__device__ __forceinline__ void clear_left(const BatchArgs &a, uint32_t tid)
+{
+    if (a.index_bytes[0] && blockIdx.x == 0 && tid == 0) a.index_bytes[0][kIdxLeft] = 0;
+}
+
 __global__ void __launch_bounds__(kClassifyBlock) k_classify(BatchArgs a)
 {
     __shared__ uint64_t top[kMaxTop];
     __shared__ uint64_t wsum[kClassifyBlock / 64];
     __shared__ uint64_t isum[2][kClassifyBlock / 64];
     const uint32_t tid = threadIdx.x;
+    clear_left(a, tid);
     const DevState st = *a.st;
     for (uint32_t k = tid; k < st.table.ntop; k += kClassifyBlock) top[k] = st.table.top[k];
     __syncthreads();
@@ -1111,6 +1118,7 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
     __shared__ uint64_t isum[2][kClassifyBlock / 64];
     uint64_t ib[2] = {0, 0};   // this record's valid bytes per shadow space (the indexes' cost test)
     const uint32_t tid = threadIdx.x;
+    clear_left(a, tid);
     const DevState st = *a.st;
     for (uint32_t k = tid; k < st.table.ntop; k += kClassifyBlock) top[k] = st.table.top[k];
     __syncthreads();
@@ -1334,6 +1342,43 @@ constexpr uint64_t kNoTile = ~0ull;
 // launched, and one of them leaves at once.
 __device__ __forceinline__ bool lds_works(const BatchArgs &a) { return a.lds_meta && a.lds_meta[3] == 0; }
 
+// The tile size of `total` units: tile_units while every wave of the
+// persistent grid gets a few of them; otherwise one equal tile per wave, which
+// the waves take by their index (354 MB in 2,000 requests: 20,000 tiles of the
+// least size, taken one by one from a counter, 216 us; one per wave, 90 us);
+// and few enough to fit tile_start.
+__device__ __forceinline__ uint64_t tile_size(uint64_t total, uint32_t tile_units, uint32_t waves, uint64_t cap)
+{
+    uint64_t tu = tile_units;
+    if ((total + tu - 1) / tu < waves) {
+        tu = ((total + waves - 1) / waves + 63) & ~63ull;
+        if (tu < kMinTile) tu = kMinTile;
+    }
+    while ((total + tu - 1) / tu > cap) tu <<= 1;
+    return tu;
+}
+
+__device__ __forceinline__ void put_tiles(const BatchArgs &a, uint64_t total, uint64_t tu)
+{
+    a.ctl->total_units = total;
+    a.ctl->tile_units = tu;
+    a.ctl->ntiles = (total + tu - 1) / tu;
+    for (int x = 0; x < kXcds; ++x) {
+        a.ctl->counter[x] = 0;
+        a.ctl->lds_counter[x] = 0;
+    }
+    a.prefix[a.count] = total;
+}
+
+// The shadow indexes' states back to 0 for the next batch, except whether
+// units are left (kIdxLeft, which every block of k_plan_tiles reads here and
+// the next classify clears): when they answered every record, the scan has no
+// tile.
+__device__ __forceinline__ void reset_states(const BatchArgs &a, uint32_t tid)
+{
+    if (tid < 2 * kIdxState && tid != kIdxLeft) a.index_bytes[tid / kIdxState][tid % kIdxState] = 0;
+}
+
 // ---------------------------------------------------------------------------
 // k_scan_sums: one block, exclusive scan of the classify-block sums
 // ---------------------------------------------------------------------------
@@ -1344,20 +1389,9 @@ __global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_u
     __shared__ uint64_t wsum[16];
     const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
     if (a.index_bytes[0]) {
-        // the shadow indexes' states back to 0 for the next batch; when they
-        // answered every record, the scan has no tile
-        const bool none = a.index_bytes[0][kIdxLeft] == 0;
-        __syncthreads();
-        if (tid < 2 * kIdxState) a.index_bytes[tid / kIdxState][tid % kIdxState] = 0;
-        if (none) {
-            if (tid == 0) {
-                a.ctl->total_units = a.ctl->ntiles = 0;
-                a.ctl->tile_units = kMinTile;
-            }
-            if (tid < kXcds) {
-                a.ctl->counter[tid] = 0;
-                a.ctl->lds_counter[tid] = 0;
-            }
+        reset_states(a, tid);
+        if (a.index_bytes[0][kIdxLeft] == 0) {
+            if (tid == 0) put_tiles(a, 0, kMinTile);
             return;
         }
     }
@@ -1382,25 +1416,8 @@ __global__ void __launch_bounds__(1024) k_scan_sums(BatchArgs a, uint32_t tile_u
     }
     if (tid == 1023) {
         const uint64_t total = off + x;
-        // tiles of tile_units while every wave of the persistent grid gets a
-        // few of them; otherwise one equal tile per wave, which the waves take
-        // by their index (354 MB in 2,000 requests: 20,000 tiles of the least
-        // size, taken one by one from a counter, 216 us; one per wave, 90 us);
-        // and few enough to fit tile_start
-        uint64_t tu = tile_units;
-        if ((total + tu - 1) / tu < waves) {
-            tu = ((total + waves - 1) / waves + 63) & ~63ull;
-            if (tu < kMinTile) tu = kMinTile;
-        }
-        while ((total + tu - 1) / tu > a.tiles_cap) tu <<= 1;
-        a.ctl->total_units = total;
-        a.ctl->tile_units = tu;
-        a.ctl->ntiles = (total + tu - 1) / tu;
-        for (int x = 0; x < kXcds; ++x) {
-            a.ctl->counter[x] = 0;
-            a.ctl->lds_counter[x] = 0;
-        }
-        a.prefix[a.count] = total;
+        const uint64_t tu = tile_size(total, tile_units, waves, a.tiles_cap);
+        put_tiles(a, total, tu);
     }
 }
 
@@ -1430,6 +1447,78 @@ __global__ void __launch_bounds__(256) k_tile_starts(BatchArgs a)
             if (a.prefix[mid] <= u) lo = mid; else hi = mid - 1;
         }
         a.tile_start[j] = (uint32_t)lo;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_plan_tiles: the three kernels above in one, for up to kPlanSums classify
+// blocks.  Every block scans the block sums for itself, in LDS, and so needs no
+// other block's result: a tile's first record is searched among the block sums
+// in LDS and then in that block's local prefixes.  Each of the three took
+// about 4.7 us, nearly all of it the launch: 2,000 requests 135.2 -> 131.4 us,
+// 800 pitched copies of 2,000 rows 182.9 -> 178.7.  (Block 0 resets the states while the
+// others still read: they read kIdxLeft only, which stays.  With the last
+// block to finish, found by a counter, as the one to reset: no gain.)
+// ---------------------------------------------------------------------------
+constexpr uint32_t kPlanSums = 1024, kPlanGrid = 256;
+__global__ void __launch_bounds__(256) k_plan_tiles(BatchArgs a, uint32_t tile_units, uint32_t waves,
+                                                    uint32_t lds_waves)
+{
+    if (lds_works(a)) waves = lds_waves;
+    __shared__ uint64_t boff[kPlanSums], wsum[4];
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
+    if (a.index_bytes[0]) {
+        if (blockIdx.x == 0) reset_states(a, tid);
+        if (a.index_bytes[0][kIdxLeft] == 0) {
+            if (blockIdx.x == 0 && tid == 0) put_tiles(a, 0, kMinTile);
+            return;
+        }
+    }
+    const uint32_t nb = (uint32_t)((a.count + kClassifyBlock - 1) / kClassifyBlock);
+    const uint32_t per = (nb + 255) / 256, b0 = tid * per;
+    uint64_t v[kPlanSums / 256], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPlanSums / 256; ++k) {
+        v[k] = k < per && b0 + k < nb ? a.bsum[b0 + k] : 0;
+        sum += v[k];
+    }
+    uint64_t x = sum;
+    for (uint32_t d = 1; d < 64u; d <<= 1) {
+        const uint64_t y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63u) wsum[wid] = x;
+    __syncthreads();
+    uint64_t run = x - sum, total = 0;
+    for (uint32_t k = 0; k < 4; ++k) {
+        if (k < wid) run += wsum[k];
+        total += wsum[k];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPlanSums / 256; ++k) {
+        if (k < per && b0 + k < nb) boff[b0 + k] = run;
+        run += v[k];
+    }
+    __syncthreads();
+    const uint64_t tu = tile_size(total, tile_units, waves, a.tiles_cap), ntiles = (total + tu - 1) / tu;
+    if (blockIdx.x == 0 && tid == 0) put_tiles(a, total, tu);
+    const uint64_t t = (uint64_t)blockIdx.x * kClassifyBlock + tid;
+    if (t < a.count) a.prefix[t] = a.local[t] + boff[blockIdx.x];
+    for (uint64_t j = (uint64_t)blockIdx.x * 256 + tid; j < ntiles; j += (uint64_t)gridDim.x * 256) {
+        const uint64_t u = j * tu;
+        uint32_t lo = 0, hi = nb - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (boff[mid] <= u) lo = mid; else hi = mid - 1;
+        }
+        const uint64_t t0 = (uint64_t)lo * kClassifyBlock, w = u - boff[lo];
+        lo = 0;
+        hi = (uint32_t)(a.count - t0 < kClassifyBlock ? a.count - t0 : kClassifyBlock) - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (a.local[t0 + mid] <= w) lo = mid; else hi = mid - 1;
+        }
+        a.tile_start[j] = (uint32_t)t0 + lo;
     }
 }
 
@@ -2259,16 +2348,16 @@ static uint32_t scan_grid(const LaunchShape &sh)
     return sh.grid >= most ? sh.grid : std::min(4u * sh.grid, most);
 }
 
-hipError_t launch_scan_sums(const BatchArgs &a, const LaunchShape &sh, hipStream_t s)
+hipError_t launch_tiles(const BatchArgs &a, const LaunchShape &sh, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, a, sh.tile_units, scan_grid(sh) * (sh.block / 64),
-                       sh.grid * (sh.block / 64));
-    return hipGetLastError();
-}
-
-hipError_t launch_prefix_tiles(const BatchArgs &a, hipStream_t s)
-{
-    const uint64_t blocks = (a.count + 255) / 256;
+    const uint64_t blocks = (a.count + kClassifyBlock - 1) / kClassifyBlock;
+    const uint32_t waves = scan_grid(sh) * (sh.block / 64), lds_waves = sh.grid * (sh.block / 64);
+    if (blocks <= kPlanSums) {
+        hipLaunchKernelGGL(k_plan_tiles, dim3(std::max((uint32_t)blocks, kPlanGrid)), dim3(256), 0, s, a,
+                           sh.tile_units, waves, lds_waves);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, a, sh.tile_units, waves, lds_waves);
     hipLaunchKernelGGL(k_prefix_tiles, dim3((uint32_t)blocks), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_tile_starts, dim3(1024), dim3(256), 0, s, a);
     return hipGetLastError();

@@ -622,8 +622,7 @@ hipError_t prepare_stage(const BatchArgs &a, const LaunchShape &sh, hipStream_t 
     }
     if (sp && sp->seg && (e = launch_segments(sp->g, *sp->sort, a, const_cast<uint32_t *>(a.perm), s)) != hipSuccess)
         return e;
-    if ((e = launch_scan_sums(a, sh, s)) != hipSuccess) return e;
-    return launch_prefix_tiles(a, s);
+    return launch_tiles(a, sh, s);
 }
 
 hipError_t enqueue_prepare(const BatchArgs &a, const LaunchShape &sh, hipStream_t s, const SegPlan *sp)
@@ -1532,8 +1531,7 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
         HIPTRY(c, launch_sidx_query(a, w->hidx, w->pidx, s, w->pitch));
         HIPTRY(c, launch_reweigh(a, s));
     }
-    HIPTRY(c, launch_scan_sums(a, sh, s));
-    HIPTRY(c, launch_prefix_tiles(a, s));
+    HIPTRY(c, launch_tiles(a, sh, s));
     if (capturing) {
         HIPTRY(c, launch_batched(a, sh, s));
         return CG_OK;

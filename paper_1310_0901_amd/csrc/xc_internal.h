@@ -169,8 +169,9 @@ struct BatchArgs {
 // `grid` contiguous slices, one per block.  state = {valid bytes of the batch
 // in the space, index valid, undefined-chunk entries, unaddressable-chunk
 // entries, granules listed, every granule wanted, entries counted so far,
-// whether units are left to scan (the host region's state only), granules
-// marked}; the scan's k_scan_sums puts it back to 0.
+// whether units are left to scan (the host region's state only; cleared by the
+// classify kernels), granules marked}; k_plan_tiles or k_scan_sums puts the
+// rest back to 0.
 struct ShadowIndex {
     uint64_t *uchunk;   // [cap_u + 1]: entry n_u holds ~0
     uint32_t *umask;    // [cap_u]
@@ -286,8 +287,7 @@ hipError_t launch_sidx_query(const BatchArgs &ar, const ShadowIndex &h, const Sh
 hipError_t launch_reweigh(const BatchArgs &a, hipStream_t s);
 hipError_t launch_classify_2d(const BatchArgs &a, const cg_transfer2d *recs2d, Pitch *pitch, hipStream_t s);
 // tiles for the scan kernel's waves
-hipError_t launch_scan_sums(const BatchArgs &a, const LaunchShape &sh, hipStream_t s);
-hipError_t launch_prefix_tiles(const BatchArgs &a, hipStream_t s);
+hipError_t launch_tiles(const BatchArgs &a, const LaunchShape &sh, hipStream_t s);
 // the persistent scan kernel, then (a.lds_meta) the host-source positions in LDS
 hipError_t launch_batched(const BatchArgs &a, const LaunchShape &sh, hipStream_t s);
 hipError_t launch_plain(const BatchArgs &a, uint64_t rec, uint64_t units, const LaunchShape &sh,

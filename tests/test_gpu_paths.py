@@ -300,3 +300,29 @@ def test_state_order_over_many_checks(X):
         assert bad.size == 0, (bad[:10], out.cpu().numpy()[bad[:3]], [want[i] for i in bad[:3]])
     finally:
         X.cg_destroy(ctx)
+
+
+@pytest.mark.parametrize("count", [257, 511, 512, 513, 65_535, 65_537, 262_144, 262_145, 300_000])
+@pytest.mark.parametrize("long", ["none", "first", "middle", "last"])
+def test_tiles_of_many_records(X, count, long):
+    """The tiles of a batch at the edges of a classify block and of the number
+    of blocks whose sums one block holds, with one record of many tiles among
+    short and empty ones, and with the records in the order given (no
+    segments)."""
+    from paper_1310_0901_amd import harness as H
+    from tests import util
+    rng = np.random.default_rng(count)
+    w, base = edge_world(rng, 6_000_000, np.array([6_000_000]))
+    n = rng.choice([0, 1, 16, 40, 300], count)
+    if long != "none":
+        n[{"first": 0, "middle": count // 2, "last": -1}[long]] = 5_000_000
+    src = W.HOST_BASE + rng.integers(0, 900_000, count)
+    rec = W.make_records(np.zeros(count, np.int64), src.astype(np.uint64), np.full(count, base[0], np.uint64),
+                         n.astype(np.uint64))
+    want = util.oracle_for(w).run(rec)
+    dw = H.DeviceWorld(w)
+    try:
+        for mode in (X.CG_CHECK, X.CG_CHECK | X.CG_KEEP_ORDER):
+            util.assert_verdicts_equal(dw.check(rec, mode), want, f"mode {mode}")
+    finally:
+        dw.close()
