@@ -420,7 +420,7 @@ int cg_kernel_ms(cg_ctx *ctx, double *ms, uint64_t *launches);
 
 /*
  * As cg_kernel_ms, for the counting pass of the shadow indexes (one launch
- * over the host region's and the pool's listed steps per large check-only
+ * over the host region's and the pool's listed granules per large check-only
  * batch that uses the indexes, bracketed by events while timing is on): its
  * summed time in ms since the last call, and the number of timed passes.
  * When bytes is not NULL (2 entries), it

@@ -604,7 +604,7 @@ struct SegPlan {
 
 // The preparation of a batched check, in three stages around the shadow
 // indexes' counting pass (stage 1, empty without indexes: one launch over the
-// host region's and the pool's listed steps), so that timing can bracket that
+// host region's and the pool's listed granules), so that timing can bracket that
 // pass.
 hipError_t prepare_stage(const BatchArgs &a, const LaunchShape &sh, hipStream_t s, const SegPlan *sp, int stage)
 {
