@@ -654,13 +654,14 @@ int capture(cg_ctx *c, hipGraph_t *g, hipGraphExec_t *x, const BatchArgs &a, con
             const SegPlan *sp);
 
 // The cached graph of this batched check (keyed by table version, buffers,
-// count, mode and launch shape), captured on first use.
+// count, mode, launch shape and what prepares it), captured on first use.
 int find_graph(cg_ctx *c, Workspace *w, const BatchArgs &a, const SegPlan *sp, const LaunchShape &sh,
                const cg_tuning &tun, bool split, hipStream_t s, GraphEntry **out)
 {
     // (the segment keys' width follows the shadow's addresses, which a new
-    // host region may change)
-    const uint32_t mode = (a.mode & 3u) | (a.perm ? 4u : 0u) | (sp && sp->seg && sp->g.key_bytes == 8 ? 8u : 0u);
+    // host region may change; a check kept in its order builds no indexes)
+    const uint32_t mode = (a.mode & 3u) | (a.perm ? 4u : 0u) | (sp && sp->seg && sp->g.key_bytes == 8 ? 8u : 0u) |
+                          (sp && sp->pidx ? 16u : 0u);
     for (auto &g : w->graphs)
         if (g.st == a.st && g.recs == a.recs && g.count == a.count && g.mode == mode && same_tuning(g.tun, tun) &&
             g.split == split && g.out == a.out) {

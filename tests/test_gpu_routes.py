@@ -1,0 +1,66 @@
+"""Which way a call is worked: calls that differ in one argument and share
+their buffers, launch shapes, and batches around the sizes where the way
+changes."""
+import numpy as np
+import pytest
+
+from paper_1310_0901_amd import workloads as W
+from tests.test_gpu_paths import compare_state, edge_world
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def X():
+    from paper_1310_0901_amd import xfercheck
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    xfercheck.lib()
+    return xfercheck
+
+
+@pytest.fixture(scope="module")
+def H(X):
+    from paper_1310_0901_amd import harness
+    return harness
+
+
+def uploads(rng, count, read, base, n):
+    """`count` host-to-device records of n bytes (a number or one per record) from anywhere in the region."""
+    n = np.broadcast_to(np.asarray(n, np.int64), count)
+    src = W.HOST_BASE + (rng.random(count) * (read - n + 1)).astype(np.int64)
+    return W.make_records(np.zeros(count, np.int64), src.astype(np.uint64), np.full(count, base, np.uint64),
+                          n.astype(np.uint64))
+
+
+@pytest.mark.parametrize("timing", [False, True])
+@pytest.mark.parametrize("kept_first", [False, True])
+def test_kept_order_on_the_same_buffers(X, H, timing, kept_first, monkeypatch):
+    """A check and the same check with CG_KEEP_ORDER on one pair of buffers,
+    both as graph replays: the first is answered from the shadow indexes, the
+    second is not, whichever came first."""
+    from tests import util
+    monkeypatch.setenv("XC_SHADOW_INDEX", "2")
+    rng = np.random.default_rng(31)
+    w, base = edge_world(rng, 300_000, np.array([300_000]))
+    rec = uploads(rng, 600, 300_000, base[0], rng.integers(1, 9000, 600))
+    want = util.oracle_for(w).run(rec)
+    dw = H.DeviceWorld(w)
+    try:
+        X.cg_timing(dw.ctx, timing)
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(len(rec))
+        s = torch.cuda.current_stream().cuda_stream
+        X.cg_index_ms(dw.ctx)
+        modes = [X.CG_CHECK, X.CG_CHECK | X.CG_KEEP_ORDER]
+        for mode in (modes[::-1] if kept_first else modes) * 2:
+            out.zero_()
+            X.check_transfers(dw.ctx, rt.data_ptr(), len(rec), out.data_ptr(), mode, s)
+            torch.cuda.synchronize()
+            util.assert_verdicts_equal(H.verdicts_np(out, len(rec)), want, f"mode {mode}")
+            _, passes, read = X.cg_index_ms(dw.ctx)
+            indexed = mode == X.CG_CHECK
+            assert (read[0] > 0) == indexed, f"mode {mode}: index bytes {read}"
+            assert passes == (1 if indexed and timing else 0)
+    finally:
+        dw.close()
