@@ -885,14 +885,21 @@ void set_index_args(BatchArgs &a, const Workspace *w)
     }
 }
 
-// Launch shape of a one-launch batch: blocks of 1,024 threads, so that one
-// block works a 64 KiB record in one iteration of its waves (64 such records:
-// 29.8 us per call with 256 threads, 26.1 with 1,024; 2 GiB carried in one
-// record: 966 and 822 us), and loads as a check's, since few records share
-// their sources.
-LaunchShape small_shape(const cg_ctx *c, LaunchShape sh)
+// Launch shape of a one-launch batch: the largest blocks (of 256, 512 or 1,024
+// threads) of which a batch's records, a block each at least, fit the CUs'
+// 2,048 threads at once, so that one block works a 64 KiB record in one
+// iteration of its waves (64 such records: 29.8 us per call with 256 threads,
+// 26.1 with 1,024; 2 GiB carried in one record: 966 and 822 us), and no record
+// waits for a second round of blocks, each of which costs the lookups' chain
+// again.  Records of 64 bytes with 256, 512 and 1,024 threads: 512 of them 14.0,
+// 14.1 and 13.7 us, 1,024 14.1, 14.3 and 21.9, 2,048 14.1, 23.8 and 38.0, 4,096
+// 22.3, 42.7 and 70.0; of 64 KiB, checked: 512 of them 32.3, 25.6 and 21.7 us,
+// 1,024 33.3, 26.5 and 38.0, 4,096 66.6, 92.2 and 137.9.  And loads as a
+// check's, since few records share their sources.
+LaunchShape small_shape(const cg_ctx *c, uint64_t count, LaunchShape sh)
 {
-    sh.block = 1024;
+    const uint64_t cus = (uint64_t)c->cu_count;
+    sh.block = count <= 2 * cus ? 1024 : count <= 4 * cus ? 512 : 256;
     sh.nontemporal = c->tuning.nontemporal;
     return sh;
 }
@@ -985,7 +992,7 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
         // few records: one launch, no preparation kernels
         TimingPair *tp = c->timing ? next_pair(c) : nullptr;
         if (tp) HIPTRY(c, hipEventRecord(tp->a, s));
-        const LaunchShape sm = small_shape(c, sh);
+        const LaunchShape sm = small_shape(c, count, sh);
         HIPTRY(c, launch_small(a, w->small, small_bpr(c, count, sm, bpr), sm, s));
         if (tp) HIPTRY(c, hipEventRecord(tp->b, s));
         if (after) HIPTRY(c, hipEventRecord(after, s));
@@ -1463,7 +1470,7 @@ int check_transfers_noalloc(cg_ctx *c, const cg_transfer *recs_dev, uint64_t cou
     a.out = (mode & CG_CHECK) ? out_dev : nullptr;
     a.mode = mode & (CG_CHECK | CG_PROPAGATE);
     a.st = c->ver[c->cur].st;
-    const LaunchShape sh = small_shape(c, shape_of(c, (mode & CG_PROPAGATE) ? c->tuning_prop : c->tuning));
+    const LaunchShape sh = small_shape(c, count, shape_of(c, (mode & CG_PROPAGATE) ? c->tuning_prop : c->tuning));
     HIPTRY(c, launch_small(a, acc, small_bpr(c, count, sh, 0), sh, s));
     return note_use_fixed(c, s);
 }

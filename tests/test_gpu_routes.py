@@ -64,3 +64,40 @@ def test_kept_order_on_the_same_buffers(X, H, timing, kept_first, monkeypatch):
             assert passes == (1 if indexed and timing else 0)
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("propagate", [False, True])
+def test_one_launch_of_many_records(X, H, propagate):
+    """check_transfers_noalloc of 4,096 records of 64 bytes: the verdicts are
+    the oracle's, and the call, whose records are all on the device at once,
+    takes less than 3 times that of 256 of them (about 1.6 times; 5 times when
+    a compute unit holds one block)."""
+    import time
+    from tests import util
+    rng = np.random.default_rng(12)
+    T = 4096
+    w, base = edge_world(rng, 1 << 20, np.array([80 * T]))
+    rec = uploads(rng, T, 1 << 20, base[0], 64)
+    rec["dst"] += np.uint64(80) * np.arange(T, dtype=np.uint64)
+    mode = X.CG_CHECK | (X.CG_PROPAGATE if propagate else 0)
+    want = util.oracle_for(w).run(rec, propagate=propagate)
+    dw = H.DeviceWorld(w)
+    try:
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(T)
+        s = torch.cuda.current_stream().cuda_stream
+
+        def us(count):
+            best = []
+            for _ in range(7):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                for _ in range(40):
+                    X.check_transfers_noalloc(dw.ctx, rt.data_ptr(), count, out.data_ptr(), mode, s)
+                torch.cuda.synchronize()
+                best.append((time.perf_counter() - t) / 40 * 1e6)
+            return min(best)
+        few, many = us(256), us(T)
+        util.assert_verdicts_equal(H.verdicts_np(out, T), want)
+        assert many < 3 * few, f"256 records {few:.1f} us, {T} records {many:.1f} us"
+    finally:
+        dw.close()
