@@ -2380,13 +2380,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     host_loop<4>(a, a.lds_meta, 0, sv, sa, sp, &s_task, s_next, s_list);
 }
 
+// Pitched rows are worked in at most four windows a lane, two when they
+// propagate, whatever the unroll asked for: more of them do not fit the
+// registers beside the rows' own state (248 and 244 bytes of scratch a lane at
+// four, propagating).  64 copies of 2,000 rows of 4,030 bytes carried from the
+// host: 264 us with two, 520 with four; of 200,000-byte rows 239 and 334; 8 of 64
+// rows of 70,000 bytes 2 MiB apart 42 and 95.
 template <int U, bool NT>
 static void launch_batched_t(const BatchArgs &a, const LaunchShape &sh, hipStream_t s)
 {
     if (a.pitch && (a.mode & CG_PROPAGATE)) {
-        hipLaunchKernelGGL((k_batched_2d<U, NT, true>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched_2d<(U > 2 ? 2 : U), NT, true>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     } else if (a.pitch) {
-        hipLaunchKernelGGL((k_batched_2d<U, NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
+        hipLaunchKernelGGL((k_batched_2d<(U > 4 ? 4 : U), NT, false>), dim3(scan_grid(sh)), dim3(sh.block), 0, s, a);
     } else if (a.lds_meta && sh.lds_after) {
         BatchArgs d = a;
         d.lds_meta = nullptr;
@@ -2429,14 +2435,18 @@ hipError_t launch_batched(const BatchArgs &a, const LaunchShape &sh, hipStream_t
     return hipGetLastError();
 }
 
+// At most four windows a lane: a block of 1,024 threads leaves a lane 128
+// registers, which eight pass, and eight are nowhere faster (1 GiB checked in
+// one record 195 us with four, 204 with eight; 256 records of 1 MiB 83 and 92).
 template <int U, bool NT>
 static void launch_small_t(const BatchArgs &a, SmallAcc *acc, uint32_t bpr, uint32_t block, hipStream_t s)
 {
+    constexpr int V = U > 4 ? 4 : U;
     const dim3 grid((uint32_t)(a.count * bpr));
     if (a.mode & CG_PROPAGATE)
-        hipLaunchKernelGGL((k_small<U, NT, true>), grid, dim3(block), 0, s, a, acc, bpr);
+        hipLaunchKernelGGL((k_small<V, NT, true>), grid, dim3(block), 0, s, a, acc, bpr);
     else
-        hipLaunchKernelGGL((k_small<U, NT, false>), grid, dim3(block), 0, s, a, acc, bpr);
+        hipLaunchKernelGGL((k_small<V, NT, false>), grid, dim3(block), 0, s, a, acc, bpr);
 }
 
 hipError_t launch_small(const BatchArgs &a, SmallAcc *acc, uint32_t bpr, const LaunchShape &sh, hipStream_t s)

@@ -101,3 +101,35 @@ def test_one_launch_of_many_records(X, H, propagate):
         assert many < 3 * few, f"256 records {few:.1f} us, {T} records {many:.1f} us"
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("unroll", [1, 2, 4, 8])
+@pytest.mark.parametrize("width,pitch,rows", [(333, 512, 90), (70_001, 70_400, 5)])
+def test_pitched_rows_at_every_unroll(X, H, unroll, width, pitch, rows):
+    """Pitched copies, checked and carried, at each unroll that cg_set_tuning takes."""
+    from tests import util
+    from tests.test_gpu_2d import check2d
+    rng = np.random.default_rng(width)
+    span, tight = (rows - 1) * pitch + width, rows * width
+    sizes = np.array([span + 3, 2 * (span + 64)])
+    read = tight + 50
+    w, base = edge_world(rng, read + tight + 40, sizes, dens=0.001)
+    rec = np.zeros(3, W.RECORD2D_DTYPE)
+    rec["width"], rec["rows"], rec["kind"] = width, rows, [0, 1, 2]
+    rec["src"] = [W.HOST_BASE + 3, base[0] + 1, base[0] + 2]
+    rec["dst"] = [base[1] + 7, W.HOST_BASE + read + 5, base[1] + span + 64]
+    rec["spitch"] = [width, pitch, pitch]
+    rec["dpitch"] = [pitch, width, pitch]
+
+    def at_unroll(mode):
+        def call(dw):
+            t = X.cg_get_tuning(dw.ctx)
+            t.unroll = unroll
+            X.cg_set_tuning(dw.ctx, t)
+            return check2d(X, dw, rec, mode)
+        return call
+    o = util.oracle_for(w)
+    compare_state(H, w, base, sizes, o, at_unroll(X.CG_CHECK), util.oracle_for(w).run2d(rec))
+    o = util.oracle_for(w)
+    want = o.run2d(rec, propagate=True)
+    compare_state(H, w, base, sizes, o, at_unroll(X.CG_CHECK | X.CG_PROPAGATE), want)
