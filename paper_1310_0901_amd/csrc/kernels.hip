@@ -242,6 +242,8 @@ __device__ __forceinline__ void st16(uint64_t addr, u32x4 v)
     __builtin_nontemporal_store(v, reinterpret_cast<gptr<u32x4u>>(addr));
 }
 
+__device__ __forceinline__ uint32_t ld_half(uint64_t addr) { return *reinterpret_cast<gcptr<uint16_t>>(addr); }
+
 // A bits [bit, bit + 16) of the bitmap, from one unaligned word inside its nab
 // bytes; bits outside it come out as any value.
 __device__ __forceinline__ uint32_t ld_a16(uint64_t a16, int64_t nab, int64_t bit)
@@ -334,8 +336,11 @@ __device__ __forceinline__ uint64_t src_first(const DV &d) { return (d.src_sh + 
 __device__ __forceinline__ uint64_t src_last(const DV &d) { return (d.src_sh + d.o + (uint64_t)d.v_hi - 1u) & ~15ull; }
 
 // Window e of one lane: V bytes, valid-byte mask, and (host source) the
-// in-range bytes whose A bit is 0.
-template <bool NT>
+// in-range bytes whose A bit is 0.  AL: the source's windows are aligned
+// chunks, as those of a check without propagation are, pitched rows apart
+// (classify_rec); a chunk with a valid byte lies whole in the shadow, and its
+// A bits are a half word of their own.
+template <bool NT, bool AL>
 __device__ __forceinline__ void src_window(const DV &d, const Region &R, int64_t e, u32x4 &v, uint32_t &ok,
                                            uint32_t &unaddr)
 {
@@ -345,12 +350,18 @@ __device__ __forceinline__ void src_window(const DV &d, const Region &R, int64_t
     ok = 0u;
     unaddr = 0u;
     if (m) {
-        const uint64_t p = d.src_sh + (uint64_t)(16 * e), lo = src_first(d), hi = src_last(d);
-        const uint64_t q = p < lo ? lo : (p > hi ? hi : p);
-        v = ld16<NT>(q);
-        if (p != q) v = byte_shift(v, (int32_t)(int64_t)(p - q));
+        const uint64_t p = d.src_sh + (uint64_t)(16 * e);
+        if constexpr (AL) {
+            v = ld16<NT>(p);
+        } else {
+            const uint64_t lo = src_first(d), hi = src_last(d);
+            const uint64_t q = p < lo ? lo : (p > hi ? hi : p);
+            v = ld16<NT>(q);
+            if (p != q) v = byte_shift(v, (int32_t)(int64_t)(p - q));
+        }
         if (d.ctl & CTL_SRC_HOST) {
-            const uint32_t a = ld_a16((uint64_t)R.a16, a_bytes(R), d.a_src + 16 * e);
+            const uint32_t a = AL ? ld_half((uint64_t)R.a16 + (uint64_t)((d.a_src + 16 * e) >> 3))
+                                  : ld_a16((uint64_t)R.a16, a_bytes(R), d.a_src + 16 * e);
             ok = m & a;
             unaddr = m & ~a;
         } else {
@@ -429,10 +440,8 @@ __device__ __forceinline__ void flush_wave(Acc &a, cg_verdict *out, uint64_t t)
 
 // Windows 64 j + lane (j < U) of an interior iteration: V from vbase, A words
 // of the source (SA) and of the destination (DA) at byte 2 * window of abase /
-// dbase, their bits starting at bit ss / ds of the word; with HALF the source's
-// are whole aligned half words (a check's windows lie so on a host source: 1M
-// mixed records scanned without an index 80.0 ms with words, 69.0 ms so).
-template <int U, bool NT, bool SA, bool DA, bool HALF = false>
+// dbase, their bits starting at bit ss / ds of the word.
+template <int U, bool NT, bool SA, bool DA>
 struct Interior {
     u32x4 v[U];
     uint32_t a[U], da[U];
@@ -443,13 +452,12 @@ struct Interior {
         for (int j = 0; j < U; ++j) {
             const uint32_t w = 64u * j + lane;
             v[j] = ld16<NT>(vbase + 16u * w);
-            if constexpr (SA && HALF) a[j] = *reinterpret_cast<gcptr<uint16_t>>(abase + 2u * w);
-            else if constexpr (SA) a[j] = *reinterpret_cast<gcptr<u32u>>(abase + 2u * w);
+            if constexpr (SA) a[j] = *reinterpret_cast<gcptr<u32u>>(abase + 2u * w);
             if constexpr (DA) da[j] = *reinterpret_cast<gcptr<u32u>>(dbase + 2u * w);
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            a[j] = !SA ? 0xFFFFu : HALF ? a[j] : (a[j] >> ss) & 0xFFFFu;
+            a[j] = SA ? (a[j] >> ss) & 0xFFFFu : 0xFFFFu;
             da[j] = DA ? (da[j] >> ds) & 0xFFFFu : 0xFFFFu;
         }
     }
@@ -611,8 +619,6 @@ __device__ __forceinline__ void run_uniform(const DV &d, const Region &R, uint64
                 else Interior<U, NT, false, false>(vbase, 0, 0, 0, 0).carry(check, i0b, dbase, acc);
             } else {
                 if (dsta) Interior<U, NT, false, true>(vbase, 0, 0, dab, ds).check(i0b, acc);
-                else if (src_host && ((uint32_t)sbit & 15u) == 0)
-                    Interior<U, NT, true, false, true>(vbase, sab, 0, 0, 0).check(i0b, acc);
                 else if (src_host) Interior<U, NT, true, false>(vbase, sab, ss, 0, 0).check(i0b, acc);
                 else Interior<U, NT, false, false>(vbase, 0, 0, 0, 0).check(i0b, acc);
             }
@@ -626,10 +632,163 @@ __device__ __forceinline__ void run_uniform(const DV &d, const Region &R, uint64
     }
 }
 
+// run_edge for a check whose source windows are aligned chunks: the chunks of
+// lanes without a valid byte are loaded at the nearest that has one, the A
+// bits with them, and nothing is shifted, so that four windows fit a lane.
+template <int G, bool NT>
+__device__ __forceinline__ void check_edge(const DV &d, const Region &R, uint64_t kb, uint64_t k_end, Acc &acc)
+{
+    const int32_t lane = (int32_t)lane_id();
+    const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
+    constexpr int32_t W = 16 * 64 * G;   // bytes worked
+    const int64_t eb = (int64_t)(d.e0 + kb);
+    const int64_t i0b = 16 * eb - (int64_t)d.o;
+    const int32_t vlo = clamp32(d.v_lo - i0b), vhi = clamp32(d.v_hi - i0b);
+    const int32_t kend = clamp32((int64_t)(k_end - kb));
+    u32x4 v[G];
+    uint32_t ok[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        v[j] = u32x4{0u, 0u, 0u, 0u};
+        ok[j] = 0xFFFFu;
+    }
+    const int32_t clo = (vlo >> 4) > 0 ? (vlo >> 4) : 0;
+    const int32_t chi = ((vhi + 15) >> 4) < 64 * G ? ((vhi + 15) >> 4) : 64 * G;
+    // (a record without a valid source byte has no source chunk to load)
+    if (vhi > vlo && chi > clo) {   // some chunk holds a valid byte
+        const uint64_t vbase = d.src_sh + (uint64_t)(16 * eb);
+        const uint64_t abase = (uint64_t)R.a16 + (uint64_t)((d.a_src + 16 * eb) >> 3);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t c = 64 * j + lane;
+            const int32_t cc = c < clo ? clo : (c >= chi ? chi - 1 : c);
+            v[j] = ld16<NT>(vbase + (uint32_t)(16 * cc));
+            if (src_host) ok[j] = ld_half(abase + (uint32_t)(2 * cc));
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        const int32_t cr = 64 * j + lane;
+        const uint32_t m = cr < kend ? rmask32(vlo - 16 * cr, vhi - 16 * cr) : 0u;
+        src_findings(acc, i0b + 16 * cr, v[j], m & ok[j], m & ~ok[j]);
+    }
+    if (d.ctl & CTL_DST_A) {
+        const int32_t dlo = clamp32(d.d_lo - i0b), dhi = clamp32(d.d_hi - i0b);
+        if (dlo < W && dhi > 0) {
+            const AWords A(R, d.a_dst + 16 * eb);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int32_t cr = 64 * j + lane;
+                const uint32_t md = cr < kend ? rmask32(dlo - 16 * cr, dhi - 16 * cr) : 0u;
+                dst_findings(acc, i0b + 16 * cr, md & ~A.at(cr));
+            }
+        }
+    }
+}
+
+// The wave's windows 64 j + lane (j < U) of an interior iteration of a check:
+// V from vbase; the A bits of a host source are half words from abase on, those
+// of a host destination start at bit ds of the words there (a host destination
+// has a device source, a host source a device destination).
+template <int U, bool NT>
+__device__ __forceinline__ void check_interior(uint64_t vbase, uint64_t abase, bool src_host, bool dsta, uint32_t ds,
+                                               int64_t i0, Acc &acc)
+{
+    // (one address for all windows: 1,024 V bytes further is the instruction's own offset)
+    const uint32_t lane = lane_id();
+    vbase += 16u * lane;
+    abase += 2u * lane;
+    i0 += 16 * (int64_t)lane;
+    u32x4 v[U];
+    uint32_t a[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = ld16<NT>(vbase + 1024u * j);
+#pragma unroll
+    for (int j = 0; j < U; ++j) a[j] = 0xFFFFu;
+    if (src_host) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) a[j] = ld_half(abase + 128u * j);
+    } else if (dsta) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) a[j] = (*reinterpret_cast<gcptr<u32u>>(abase + 128u * j) >> ds) & 0xFFFFu;
+    }
+    // no finding when every V byte is 0 and every A bit 1, which one test over
+    // all windows tells
+    uint32_t bad = 0;
+#pragma unroll
+    for (int j = 0; j < U; ++j) bad |= v[j].x | v[j].y | v[j].z | v[j].w | (a[j] ^ 0xFFFFu);
+    if (__ballot(bad != 0u) == 0) return;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        if (dsta) dst_findings(acc, i0 + 1024 * j, a[j] ^ 0xFFFFu);
+        src_findings(acc, i0 + 1024 * j, v[j], src_host ? a[j] : 0xFFFFu, src_host ? a[j] ^ 0xFFFFu : 0u);
+    }
+}
+
+// run_uniform for the checks of check_transfers.  A batch whose records read
+// the same bytes again and again takes them from the caches at 20 TB/s, where
+// the waves' instructions count: the interior iterations follow each other, so
+// their range is found once per call, and an iteration is its loads, one test
+// and one address (with the ranges tested per iteration, by the code that
+// serves any alignment, about 100 instructions and 40 more registers).  1M mixed
+// records without an index, in segments, 64 KiB tiles, cached loads: 69.2 ms with
+// that code, 55.5 so; with the host's segments in LDS 64.2 and 52.7, and in 1 MiB
+// tiles with non-temporal loads 69.5 and 64.3.  4,096 records of 64 KiB in one
+// launch 67 and 55 us.
+template <int U, bool NT>
+__device__ __forceinline__ void run_check(const DV &d, const Region &R, uint64_t k_begin, uint64_t k_end, Acc &acc,
+                                          uint64_t step = 64u * U)
+{
+    const bool dsta = (d.ctl & CTL_DST_A) != 0;
+    const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
+    const uint64_t a16b = (uint64_t)R.a16;
+    constexpr uint64_t N = 64u * U;   // units per iteration
+    constexpr int G = U > 4 ? 4 : U;
+    k_begin = ufl64(k_begin);
+    k_end = ufl64(k_end);
+    step = ufl64(step);
+    // units [in_lo, in_hi) have interior windows
+    const int64_t o = (int64_t)d.o;
+    int64_t lo = d.v_lo, hi = d.v_hi;
+    if (dsta) {
+        const int64_t last = 8 * (a_bytes(R) - 4) - d.a_dst - o;   // the A words lie inside the bitmap up to here
+        lo = lo > d.d_lo ? lo : d.d_lo;
+        hi = hi < d.d_hi ? hi : d.d_hi;
+        hi = hi < last ? hi : last;
+    }
+    const int64_t in_lo = ((lo + o + 15) >> 4) - (int64_t)d.e0;
+    int64_t in_hi = ((hi + o) >> 4) - (int64_t)d.e0;
+    in_hi = in_hi < (int64_t)k_end ? in_hi : (int64_t)k_end;
+    uint64_t kb = k_begin;
+    while (kb < k_end) {
+        if ((int64_t)kb >= in_lo && (int64_t)(kb + N) <= in_hi) {
+            for (; (int64_t)(kb + N) <= in_hi; kb += step) {
+                const int64_t e = (int64_t)(d.e0 + kb), bit = (src_host ? d.a_src : d.a_dst) + 16 * e;
+                check_interior<U, NT>(d.src_sh + (uint64_t)(16 * e), a16b + (uint64_t)(bit >> 3), src_host, dsta,
+                                      (uint32_t)bit & 7u, 16 * e - o, acc);
+            }
+            continue;
+        }
+        const uint64_t ke = k_end < kb + N ? k_end : kb + N;
+#pragma nounroll
+        for (uint64_t k = kb; k < ke; k += 64u * G) check_edge<G, NT>(d, R, k, ke, acc);
+        kb += step;
+    }
+}
+
+// a record that is no pitched row
+template <int U, bool NT, bool PROP>
+__device__ __forceinline__ void run_units(const DV &d, const Region &R, uint64_t k_begin, uint64_t k_end, Acc &acc,
+                                          uint64_t step = 64u * U)
+{
+    if constexpr (PROP) run_uniform<U, NT, true>(d, R, k_begin, k_end, acc, step);
+    else run_check<U, NT>(d, R, k_begin, k_end, acc, step);
+}
+
 // ---------------------------------------------------------------------------
 // one unit handled by one lane (small records, tile boundaries)
 // ---------------------------------------------------------------------------
-template <bool NT, bool PROP>
+template <bool NT, bool PROP, bool AL>
 __device__ __forceinline__ void run_unit(const DV &d, const Region &R, uint64_t k, Acc &acc)
 {
     const bool check = (d.ctl & CTL_CHECK) != 0;
@@ -637,7 +796,7 @@ __device__ __forceinline__ void run_unit(const DV &d, const Region &R, uint64_t 
     const int64_t i0 = 16 * e - (int64_t)d.o;
     u32x4 v;
     uint32_t ok, un;
-    src_window<NT>(d, R, e, v, ok, un);
+    src_window<NT, AL>(d, R, e, v, ok, un);
     if (check) src_findings(acc, i0, v, ok, un);
     if (d.ctl & (CTL_DST_A | CTL_PROP)) {
         const uint32_t md = rmask(d.d_lo - i0, d.d_hi - i0);
@@ -1648,9 +1807,11 @@ __device__ __forceinline__ void run_pitched(const BatchArgs &a, const Region &R,
         run_rows_flat<(U > 2 ? 2 : U), NT, PROP>(d0, P, R, k0, k1, acc);
         return;
     }
-    if (P.uniform == kRowsContig) {   // (made only for checks without propagation)
-        run_uniform<U, NT, PROP>(d0, R, k0, k1, acc);
-        return;
+    if constexpr (!PROP) {
+        if (P.uniform == kRowsContig) {   // one transfer
+            run_check<U, NT>(d0, R, k0, k1, acc);
+            return;
+        }
     }
     const DevState *st = a.st;
     const uint64_t r0 = k0 / P.upr;
@@ -1693,7 +1854,7 @@ __device__ __forceinline__ void run_unit_pitched(const BatchArgs &a, const Regio
     if (P.upr == 0) return;   // no rows, or a bad kind: nothing to work
     if (!PROP && P.uniform == kRowsContig) {
         const DV d = load_desc(a.desc, t);
-        if (k < d.units) run_unit<NT, false>(d, R, k, acc);
+        if (k < d.units) run_unit<NT, false, true>(d, R, k, acc);
         return;
     }
     const uint64_t r = (k | P.upr) >> 32 ? k / P.upr : (uint32_t)k / (uint32_t)P.upr, j = k - r * P.upr;
@@ -1714,7 +1875,7 @@ __device__ __forceinline__ void run_unit_pitched(const BatchArgs &a, const Regio
     const DV d = make_dv(x);
     Acc ra;
     acc_reset(ra);
-    if (j < d.units) run_unit<NT, PROP>(d, R, j, ra);
+    if (j < d.units) run_unit<NT, PROP, false>(d, R, j, ra);
     acc_add_row(acc, ra, rflags, rfirst, r * P.width);
 }
 
@@ -1808,7 +1969,7 @@ __device__ void batched_loop(const BatchArgs &a)
             }
             if (nfull) {
                 if constexpr (PITCH) run_pitched<U, NT, PROP>(a, R, t, u - pt, u - pt + nfull, acc);
-                else run_uniform<U, NT, PROP>(load_desc_uniform(a.desc, t), R, u - pt, u - pt + nfull, acc);
+                else run_units<U, NT, PROP>(load_desc_uniform(a.desc, t), R, u - pt, u - pt + nfull, acc);
                 if (a.out) flush_wave(acc, a.out, a.perm ? ld_uniform(a.perm + t) : t);
                 u += nfull;
                 if (u == pt1 && u < u_end) {
@@ -1837,7 +1998,7 @@ __device__ void batched_loop(const BatchArgs &a)
             } else if (act) {
                 const DV d = load_desc(a.desc, tl);
                 const uint64_t k = ul - pl;
-                if (k < d.units) run_unit<NT, PROP>(d, R, k, acc);
+                if (k < d.units) run_unit<NT, PROP, !PROP>(d, R, k, acc);
             }
             if (a.out && __ballot(acc.flags != 0u))
                 flush_segmented(acc, act ? (a.perm ? (uint64_t)a.perm[tl] : tl) : ~0ull, a.out);
@@ -2106,7 +2267,7 @@ __global__ void __launch_bounds__(512) k_plain(BatchArgs a, uint64_t t, uint64_t
     const DV d = load_desc_uniform(a.desc, t);
     Acc acc;
     acc_reset(acc);
-    run_uniform<U, NT, PROP>(d, ld_uniform(&a.st->region), k0, k1, acc);
+    run_units<U, NT, PROP>(d, ld_uniform(&a.st->region), k0, k1, acc);
     if (a.out) flush_wave(acc, a.out, t);
 }
 
@@ -2174,7 +2335,7 @@ k_small(BatchArgs a, SmallAcc *acc, uint32_t bpr)
     acc_reset(ac);
     if (k0 < units) {
         const DV d = dv_uniform(sd);
-        run_uniform<U, NT, PROP>(d, ld_uniform(&st->region), k0, units, ac, (uint64_t)nb * nw * 64u * U);
+        run_units<U, NT, PROP>(d, ld_uniform(&st->region), k0, units, ac, (uint64_t)nb * nw * 64u * U);
     }
     if (!a.out) return;   // propagation only: no verdict (uniform over the grid)
     uint64_t f = NONE, u = 0;

@@ -133,3 +133,44 @@ def test_pitched_rows_at_every_unroll(X, H, unroll, width, pitch, rows):
     o = util.oracle_for(w)
     want = o.run2d(rec, propagate=True)
     compare_state(H, w, base, sizes, o, at_unroll(X.CG_CHECK | X.CG_PROPAGATE), want)
+
+
+@pytest.mark.parametrize("unroll", [1, 2, 4, 8])
+def test_checks_at_every_unroll(X, H, unroll, monkeypatch):
+    """Checks of all kinds at odd alignments and lengths around a wave's
+    iterations, many of their sides unallocated, outside the region or past
+    an end, so that a record has destination windows and no source byte, or
+    the other way round: in one launch, as a batch, in the order given, one
+    launch a record, and cut into segments."""
+    from tests import util
+    rng = np.random.default_rng(51)
+    hl, T = 150_001, 900
+    sizes = np.array([140_003, 5000])
+    w, base = edge_world(rng, hl, sizes)
+    n = rng.choice([1, 15, 16, 17, 1023, 1024, 1025, 4095, 4097, 8191, 16_400, 33_000, 70_001], T)
+    kind = rng.choice(3, T)
+    nowhere = W.DEV_BASE - 4096 + rng.integers(0, 64, T)
+
+    def device(k):
+        j = rng.integers(0, 2, T)
+        p = base[j] + rng.integers(0, 1 << 30, T) % sizes[j]
+        return np.where(rng.random(T) < 0.3, nowhere, p) if k else p
+    host = W.HOST_BASE - 40 + rng.integers(0, hl + 80, T)
+    rec = W.make_records(kind, np.where(kind == 0, host, device(1)).astype(np.uint64),
+                         np.where(kind == 1, host, device(1)).astype(np.uint64), n.astype(np.uint64))
+    want = util.oracle_for(w).run(rec)
+    for knobs, part, modes in (({"XC_SHADOW_INDEX": "0"}, slice(0, 200), (0,)),
+                               ({"XC_SHADOW_INDEX": "0"}, slice(0, T), (0, X.CG_KEEP_ORDER, X.CG_PLAIN)),
+                               ({"XC_SHADOW_INDEX": "0", "XC_REORDER_MIN": "1"}, slice(0, T), (0,)),
+                               ({"XC_SHADOW_INDEX": "0", "XC_REORDER_MIN": "1", "XC_HOST_LDS": "0"}, slice(0, T), (0,))):
+        for k, v in knobs.items():
+            monkeypatch.setenv(k, v)
+        dw = H.DeviceWorld(w)
+        try:
+            t = X.cg_get_tuning(dw.ctx)
+            t.unroll = unroll
+            X.cg_set_tuning(dw.ctx, t)
+            for mode in modes:
+                util.assert_verdicts_equal(dw.check(rec[part], X.CG_CHECK | mode), want[part], f"{knobs} mode {mode}")
+        finally:
+            dw.close()
