@@ -388,10 +388,14 @@ int check_pointers(cg_ctx *ctx, const uint64_t *ptrs_dev, uint64_t count, cg_ptr
 typedef struct cg_tuning {
     uint32_t block;          /* threads per block: 256 or 512 */
     uint32_t unroll;         /* 16-byte chunks in flight per lane: 1, 2, 4 or 8 */
-    uint32_t blocks_per_cu;  /* persistent blocks per compute unit */
+    uint32_t blocks_per_cu;  /* persistent blocks per compute unit: 1 to 16 */
     uint32_t tile_units;     /* 16-byte units per work tile (power of two, >= 4096) */
     uint32_t nontemporal;    /* 1: stream V with non-temporal loads */
-    uint32_t reserved[3];
+    uint32_t reserved[3];    /* [0] = 1, as in a new context: blocks_per_cu is not the
+                                caller's choice, and the scan kernel takes up to four
+                                times as many blocks; [0] = 0, or another blocks_per_cu
+                                than the context had: as many as it says.  The others
+                                are ignored */
 } cg_tuning;
 
 int cg_get_tuning(cg_ctx *ctx, cg_tuning *t);

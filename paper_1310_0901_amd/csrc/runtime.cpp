@@ -145,10 +145,13 @@ struct InFlight {
     hipEvent_t ev;
 };
 
+// the number of blocks is the library's choice, not the caller's (cg_tuning)
+bool spread_grid(const cg_tuning &t) { return t.reserved[0] == 1; }
+
 bool same_tuning(const cg_tuning &x, const cg_tuning &y)
 {
     return x.block == y.block && x.unroll == y.unroll && x.blocks_per_cu == y.blocks_per_cu &&
-           x.tile_units == y.tile_units && x.nontemporal == y.nontemporal;
+           x.tile_units == y.tile_units && x.nontemporal == y.nontemporal && spread_grid(x) == spread_grid(y);
 }
 
 }  // namespace
@@ -583,6 +586,7 @@ LaunchShape shape_of(cg_ctx *c, const cg_tuning &t)
     sh.tile_units = t.tile_units;
     sh.cus = (uint32_t)c->cu_count;
     sh.lds_after = c->host_lds == 2 ? 1u : 0u;
+    sh.spread = spread_grid(t) ? 1u : 0u;
     return sh;
 }
 
@@ -1080,7 +1084,8 @@ std::string tuning_json(const cg_tuning &t)
 {
     std::ostringstream o;
     o << "\"block\": " << t.block << ", \"unroll\": " << t.unroll << ", \"blocks_per_cu\": " << t.blocks_per_cu
-      << ", \"tile_units\": " << t.tile_units << ", \"nontemporal\": " << t.nontemporal;
+      << ", \"tile_units\": " << t.tile_units << ", \"nontemporal\": " << t.nontemporal
+      << ", \"spread\": " << (spread_grid(t) ? 1 : 0);
     return o.str();
 }
 
@@ -1219,9 +1224,13 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
     c->tuning.blocks_per_cu = 4;
     c->tuning.tile_units = 1u << 16;
     c->tuning.nontemporal = 1;
+    c->tuning.reserved[0] = 1;
     if (const char *e = getenv("XC_UNROLL")) c->tuning.unroll = (uint32_t)atoi(e);
     if (const char *e = getenv("XC_BLOCK")) c->tuning.block = (uint32_t)atoi(e);
-    if (const char *e = getenv("XC_BLOCKS_PER_CU")) c->tuning.blocks_per_cu = (uint32_t)atoi(e);
+    if (const char *e = getenv("XC_BLOCKS_PER_CU")) {
+        c->tuning.blocks_per_cu = (uint32_t)atoi(e);
+        c->tuning.reserved[0] = 0;
+    }
     if (const char *e = getenv("XC_TILE_UNITS")) c->tuning.tile_units = (uint32_t)atoi(e);
     if (const char *e = getenv("XC_NONTEMPORAL")) c->tuning.nontemporal = (uint32_t)atoi(e);
     if (const char *e = getenv("XC_REORDER_MIN")) c->reorder_min = strtoull(e, nullptr, 0);
@@ -1716,8 +1725,10 @@ int cg_set_tuning(cg_ctx *c, const cg_tuning *t)
 {
     if (!c || !t) return CG_EINVAL;
     if (!valid_tuning(*t)) return fail(c, CG_EINVAL, "tuning out of range");
-    c->tuning = *t;
-    c->tuning_prop = *t;
+    cg_tuning u = *t;
+    if (u.blocks_per_cu != c->tuning.blocks_per_cu) u.reserved[0] = 0;   // now the caller's choice
+    c->tuning = u;
+    c->tuning_prop = u;
     return CG_OK;
 }
 
@@ -1812,6 +1823,8 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
             if (parse_field(line, "block", &t.block) && parse_field(line, "unroll", &t.unroll) &&
                 parse_field(line, "blocks_per_cu", &t.blocks_per_cu) && parse_field(line, "tile_units", &t.tile_units) &&
                 parse_field(line, "nontemporal", &t.nontemporal) && valid_tuning(t)) {
+                t.reserved[0] = 0;
+                (void)parse_field(line, "spread", &t.reserved[0]);
                 target = t;
                 c->timing = was_timing;
                 if (best) *best = t;
@@ -1858,6 +1871,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
                 cg_tuning t = cur;
                 t.block = b;
                 t.blocks_per_cu = bpc;
+                t.reserved[0] = 0;
                 cands.push_back(t);
             }
         rc = try_set(cands);
@@ -1879,6 +1893,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
                 cg_tuning t = cur;
                 t.block = b;
                 t.blocks_per_cu = bpc;
+                t.reserved[0] = 0;
                 cands.push_back(t);
             }
         rc = try_set(cands);
@@ -1893,6 +1908,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
                 t.block = 256;
                 t.unroll = u;
                 t.blocks_per_cu = bpc;
+                t.reserved[0] = 0;
                 cands.push_back(t);
             }
         rc = try_set(cands);
@@ -2005,6 +2021,7 @@ extern "C" int cg_serve_run(cg_ctx *c, const cg_serve_event *ev, uint64_t n, con
     HIPTRY(c, hipSetDevice(c->dev));
     cg_tuning tun = c->tuning;
     tun.blocks_per_cu = cfg->blocks_per_cu ? cfg->blocks_per_cu : 1;
+    tun.reserved[0] = 0;
     if (!valid_tuning(tun)) return fail(c, CG_EINVAL, "serve: bad blocks_per_cu");
 
     std::vector<Slot> slots(S);

@@ -235,6 +235,7 @@ struct LaunchShape {
     uint32_t tile_units;
     uint32_t cus;   // compute units of the device
     uint32_t lds_after;   // host-source positions in a kernel of their own after the scan kernel (else side by side)
+    uint32_t spread;      // the scan kernel may take up to four times `grid` blocks
 };
 
 // Merge of a table version with the frees and allocations made since

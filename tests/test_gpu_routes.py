@@ -174,3 +174,49 @@ def test_checks_at_every_unroll(X, H, unroll, monkeypatch):
                 util.assert_verdicts_equal(dw.check(rec[part], X.CG_CHECK | mode), want[part], f"{knobs} mode {mode}")
         finally:
             dw.close()
+
+
+def test_blocks_per_cu_are_the_callers(X, H, monkeypatch):
+    """A caller's blocks_per_cu is the number of blocks launched: with one
+    16-byte load in flight per lane, one block of 256 threads per compute unit
+    streams the shadow at a fraction of the rate that four have (four blocks
+    are enough, so a launch of four times what is asked for shows no
+    difference).  A new context's own choice survives cg_get_tuning and
+    cg_set_tuning until the caller sets another number."""
+    monkeypatch.setenv("XC_SHADOW_INDEX", "0")
+    n, T = 1 << 20, 512
+    hv = torch.zeros(T * n, dtype=torch.uint8, device="cuda")
+    ha = torch.full((T * n // 64,), -1, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    ctx = X.cg_create(0, 4 << 20, 16)
+    try:
+        X.cg_host_register(ctx, W.HOST_BASE, T * n, hv.data_ptr(), ha.data_ptr())
+        X.shadow_alloc(ctx, W.DEV_BASE, n)
+        rec = W.make_records(np.zeros(T, np.int64), (W.HOST_BASE + n * np.arange(T)).astype(np.uint64),
+                             np.full(T, W.DEV_BASE, np.uint64), np.full(T, n, np.uint64))
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(T)
+        s = torch.cuda.current_stream().cuda_stream
+        X.cg_timing(ctx, True)
+
+        def ms():
+            got = []
+            for _ in range(5):
+                X.check_transfers(ctx, rt.data_ptr(), T, out.data_ptr(), X.CG_CHECK | X.CG_KEEP_ORDER, s)
+                got.append(X.cg_kernel_ms(ctx)[0])
+            return min(got)
+        t = X.cg_get_tuning(ctx)
+        assert (t.blocks_per_cu, list(t.reserved)) == (4, [1, 0, 0])
+        own = ms()
+        X.cg_set_tuning(ctx, t)
+        assert list(X.cg_get_tuning(ctx).reserved) == [1, 0, 0]
+        t.unroll, t.blocks_per_cu = 1, 1
+        X.cg_set_tuning(ctx, t)
+        assert list(X.cg_get_tuning(ctx).reserved) == [0, 0, 0]
+        one = ms()
+        t.blocks_per_cu = 4
+        X.cg_set_tuning(ctx, t)
+        four = ms()
+        assert one > 1.5 * four, f"blocks per CU: 1 {one:.3f} ms, 4 {four:.3f} ms"
+        assert own < 1.3 * four, f"the context's own choice {own:.3f} ms, 4 {four:.3f} ms"
+    finally:
+        X.cg_destroy(ctx)
