@@ -405,8 +405,9 @@ int cg_set_tuning(cg_ctx *ctx, const cg_tuning *t);
  * Time candidate launch shapes of the batched check on these records (each
  * run is a full check; out_dev is overwritten) and keep the fastest; *best
  * (may be NULL) receives it.  If cache_path is non-NULL the choice is read
- * from / appended to that JSON-lines file, keyed by device, CU count and a
- * workload signature.  Synchronous.
+ * from / appended to that JSON-lines file, keyed by device, CU count, a
+ * workload signature and the generation of the library's scan kernels (lines
+ * of another generation are left alone).  Synchronous.
  */
 int cg_autotune(cg_ctx *ctx, const cg_transfer *recs_dev, uint64_t count, cg_verdict *out_dev,
                 uint32_t mode, void *hip_stream, const char *cache_path, cg_tuning *best);

@@ -34,6 +34,10 @@ constexpr uint64_t kFillPiece = 1ull << 20;   // bytes per fill range
 constexpr uint64_t kFillCap = 1ull << 13;     // ranges per fill launch
 constexpr uint64_t kDeltaWords = 4096;        // a table delta this small is uploaded by a kernel
 constexpr int kFillSlots = 8;                 // staging ring for fill ranges
+// in the key of every line of the tuner's cache: a line measured on other scan
+// kernels, or by another meaning of the launch shape, is no choice for these.
+// Counted up with either.
+constexpr int kScanGeneration = 2;
 constexpr uint64_t kTilesCap = 1ull << 22;    // tile-start entries per workspace
 constexpr int kPooledEvents = 16;             // completion events made at set-up
 // launch shape for checks of mostly short pitched rows (measured on 4 KiB and
@@ -1813,7 +1817,8 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
     uint32_t lg = 0;
     while ((1ull << lg) < ctl.total_units) ++lg;
     std::ostringstream key;
-    key << c->arch << "/cu" << c->cu_count << "/n" << count << "/u2^" << lg << "/m" << mode << (reordered ? "/o" : "");
+    key << c->arch << "/cu" << c->cu_count << "/n" << count << "/u2^" << lg << "/m" << mode << (reordered ? "/o" : "")
+        << "/g" << kScanGeneration;
     if (cache_path) {
         std::ifstream in(cache_path);
         std::string line;

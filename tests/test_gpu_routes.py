@@ -220,3 +220,34 @@ def test_blocks_per_cu_are_the_callers(X, H, monkeypatch):
         assert own < 1.3 * four, f"the context's own choice {own:.3f} ms, 4 {four:.3f} ms"
     finally:
         X.cg_destroy(ctx)
+
+
+def test_tuner_measures_again_on_new_kernels(X, H, tmp_path, monkeypatch):
+    """cg_autotune takes its choice from a line that it wrote itself, and not
+    from a line whose key names no generation of the scan kernels or another
+    one."""
+    monkeypatch.setenv("XC_SHADOW_INDEX", "0")
+    rng = np.random.default_rng(3)
+    w, base = edge_world(rng, 400_000, np.array([100_000]))
+    rec = uploads(rng, 300, 400_000, base[0], 60_000)
+    cache = tmp_path / "tuning.jsonl"
+    dw = H.DeviceWorld(w)
+    try:
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(len(rec))
+        call = (dw.ctx, rt.data_ptr(), len(rec), out.data_ptr(), X.CG_CHECK, torch.cuda.current_stream().cuda_stream)
+        own = X.cg_autotune(*call, str(cache)).as_dict()
+        line = cache.read_text()
+        key = line.split('"')[3]
+        assert len(line.strip().split("\n")) == 1 and "/g" in key
+        # a shape the tuner does not try, so that it can only come from the file
+        shape = '"block": 512, "unroll": 1, "blocks_per_cu": 5, "tile_units": 131072, "nontemporal": 0'
+        head = key[:key.index("/g")]
+        cache.write_text("".join(f'{{"key": "{head}{g}", {shape}, "ms": 0.001}}\n' for g in ("", "/g1", "/g99")))
+        assert X.cg_autotune(*call, str(cache)).as_dict()["blocks_per_cu"] != 5
+        assert len(cache.read_text().strip().split("\n")) == 4
+        cache.write_text(f'{{"key": "{key}", {shape}, "ms": 0.001}}\n')
+        got = X.cg_autotune(*call, str(cache))
+        assert (got.block, got.unroll, got.blocks_per_cu, got.tile_units, got.nontemporal) == (512, 1, 5, 131072, 0)
+        assert own["blocks_per_cu"] != 5 and list(got.reserved) == [0, 0, 0]
+    finally:
+        dw.close()
