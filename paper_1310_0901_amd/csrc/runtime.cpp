@@ -1800,14 +1800,23 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
     const bool was_timing = c->timing;
     c->timing = true;
     c->tused = 0;
-    int rc = run_check(c, recs_dev, count, out_dev, mode | CG_EAGER | keep, s, target);
+    // (a batch worked in one launch leaves no total: its units come from a run of
+    // one launch per record)
+    const bool one_launch = count <= c->small_max;
+    int rc = run_check(c, recs_dev, count, out_dev, mode | (one_launch ? CG_PLAIN : CG_EAGER | keep), s, target);
     if (rc) { c->timing = was_timing; return rc; }
     HIPTRY(c, hipStreamSynchronize(s));
     c->tused = 0;
     c->iused = 0;
-    Ctl ctl;
-    HIPTRY(c, hipMemcpy(&ctl, c->ws[s]->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
-    if (ctl.total_units <= count) {
+    uint64_t total = 0;
+    if (one_launch) {
+        for (uint64_t t = 0; t < count; ++t) total += std::max<uint64_t>(c->ws[s]->h_weight[t], 1);
+    } else {
+        Ctl ctl;
+        HIPTRY(c, hipMemcpy(&ctl, c->ws[s]->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+        total = ctl.total_units;
+    }
+    if (total <= count) {
         // no record left to scan (the shadow indexes answered them, or they
         // are empty): the launch shape does not matter; keep it
         c->timing = was_timing;
@@ -1815,7 +1824,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
         return CG_OK;
     }
     uint32_t lg = 0;
-    while ((1ull << lg) < ctl.total_units) ++lg;
+    while ((1ull << lg) < total) ++lg;
     std::ostringstream key;
     key << c->arch << "/cu" << c->cu_count << "/n" << count << "/u2^" << lg << "/m" << mode << (reordered ? "/o" : "")
         << "/g" << kScanGeneration;
@@ -1867,9 +1876,17 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
     };
     std::vector<cg_tuning> cands;
     for (uint32_t u : {2u, 4u, 8u})
-        for (uint32_t nt : {0u, 1u}) { cg_tuning t = cur; t.unroll = u; t.nontemporal = nt; cands.push_back(t); }
+        for (uint32_t nt : {0u, 1u}) {
+            // (one launch loads as the check's shape says, propagating too)
+            if (one_launch && (mode & CG_PROPAGATE) && nt != cur.nontemporal) continue;
+            cg_tuning t = cur;
+            t.unroll = u;
+            t.nontemporal = nt;
+            cands.push_back(t);
+        }
     rc = try_set(cands);
-    if (!rc) {
+    // (a batch worked in one launch uses no more of the shape than these)
+    if (!rc && !one_launch) {
         cands.clear();
         for (uint32_t b : {256u, 512u})
             for (uint32_t bpc : {1u, 2u, 3u, 4u, 6u, 8u}) {
@@ -1881,7 +1898,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
             }
         rc = try_set(cands);
     }
-    if (!rc) {
+    if (!rc && !one_launch) {
         cands.clear();
         for (uint32_t tu : {1u << 12, 1u << 13, 1u << 14, 1u << 15, 1u << 16, 1u << 18}) {
             cg_tuning t = cur;
@@ -1890,7 +1907,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
         }
         rc = try_set(cands);
     }
-    if (!rc) {
+    if (!rc && !one_launch) {
         // the occupancy that suits a tile size may differ from the first pick
         cands.clear();
         for (uint32_t b : {256u, 512u})
@@ -1903,7 +1920,7 @@ int cg_autotune(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, cg_verdi
             }
         rc = try_set(cands);
     }
-    if (!rc) {
+    if (!rc && !one_launch) {
         // batches of short records are per-record latency: many waves with a
         // short loop can beat deep unrolling (measured on 4 KiB rows: -20 %)
         cands.clear();

@@ -251,3 +251,30 @@ def test_tuner_measures_again_on_new_kernels(X, H, tmp_path, monkeypatch):
         assert own["blocks_per_cu"] != 5 and list(got.reserved) == [0, 0, 0]
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("before", [0, 300, 3000])
+def test_tuner_keys_one_launch_batches_by_their_units(X, H, tmp_path, before, monkeypatch):
+    """cg_autotune on a batch worked in one launch, after `before` records in
+    another batch on the stream: its key holds its own units (4,096 of a
+    64 KiB upload), and only the unroll and the kind of load are chosen."""
+    monkeypatch.setenv("XC_SHADOW_INDEX", "0")
+    rng = np.random.default_rng(4)
+    w, base = edge_world(rng, 400_000, np.array([100_000]))
+    cache = tmp_path / "tuning.jsonl"
+    dw = H.DeviceWorld(w)
+    try:
+        if before:
+            dw.check(uploads(rng, before, 400_000, base[0], 60_000))
+        rec = W.make_records([0], np.array([W.HOST_BASE], np.uint64), np.array([base[0]], np.uint64),
+                             np.array([65_536], np.uint64))
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(1)
+        t0 = X.cg_get_tuning(dw.ctx)
+        t = X.cg_autotune(dw.ctx, rt.data_ptr(), 1, out.data_ptr(), X.CG_CHECK,
+                          torch.cuda.current_stream().cuda_stream, str(cache))
+        assert "/n1/u2^12/m1" in cache.read_text()
+        # what one launch does not use stays as it was
+        assert (t.block, t.blocks_per_cu, t.tile_units, t.reserved[0]) == \
+               (t0.block, t0.blocks_per_cu, t0.tile_units, t0.reserved[0])
+    finally:
+        dw.close()
