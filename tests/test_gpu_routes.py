@@ -278,3 +278,48 @@ def test_tuner_keys_one_launch_batches_by_their_units(X, H, tmp_path, before, mo
                (t0.block, t0.blocks_per_cu, t0.tile_units, t0.reserved[0])
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("count", [1, 2, 40, 600])
+def test_one_launch_records_of_several_blocks(X, H, count, kind):
+    """Records that one launch works in more than one block (above 128 KiB),
+    at lengths around the units of a block and around an iteration of all the
+    record's waves, at odd alignments, some reaching past an end, over holes
+    and undefined bytes: checked and carried, twice on one stream (the second
+    finds the accumulators as the first left them), by check_transfers and by
+    check_transfers_noalloc (which alone takes 600 in one launch)."""
+    from tests import util
+    rng = np.random.default_rng(7 * count + kind)
+    lens = np.array([65_536 * k + d for k in range(2, 7) for d in (-17, -1, 0, 1, 33)] + [500, 1_000_003])
+    n = rng.choice(lens, count) if count > 2 else np.array([1_000_003, 262_145][:count])
+    if count == 600:   # blocks of 512 threads, most records small
+        n = np.where(rng.random(count) < 0.9, rng.integers(1, 3000, count), n)
+    gap = rng.integers(1, 40, count)
+    pos = np.cumsum(n + gap) - n
+    far = int(pos[-1] + n[-1]) + 100
+    read = 1_300_001
+    sizes = np.array([read, far if kind != 1 else 64])
+    w, base = edge_world(rng, read + (far if kind == 1 else 0), sizes, dens=0.0005)
+    src = (W.HOST_BASE if kind == 0 else base[0]) + rng.integers(0, read - n + 1)
+    # (the allocations are 4,096 bytes apart: none of these starts in the one written)
+    past = rng.random(count) < 0.2
+    src = np.where(past, (W.HOST_BASE if kind == 0 else base[0]) + read - n + rng.integers(1, 4000, count), src)
+    dst = (W.HOST_BASE + read if kind == 1 else base[1]) + pos
+    rec = W.make_records(np.full(count, kind), src.astype(np.uint64), dst.astype(np.uint64), n.astype(np.uint64))
+    s = torch.cuda.current_stream().cuda_stream
+    rt, out = H.records_tensor(rec), H.verdicts_tensor(count)
+
+    def call(entry, mode):
+        def go(dw):
+            for _ in range(2):
+                out.zero_()
+                entry(dw.ctx, rt.data_ptr(), count, out.data_ptr(), mode, s)
+            torch.cuda.synchronize()
+            return H.verdicts_np(out, count)
+        return go
+    for entry in (X.check_transfers, X.check_transfers_noalloc):
+        compare_state(H, w, base, sizes, util.oracle_for(w), call(entry, X.CG_CHECK), util.oracle_for(w).run(rec))
+        o = util.oracle_for(w)
+        want = o.run(rec, propagate=True)
+        compare_state(H, w, base, sizes, o, call(entry, X.CG_CHECK | X.CG_PROPAGATE), want)
