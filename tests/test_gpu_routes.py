@@ -323,3 +323,59 @@ def test_one_launch_records_of_several_blocks(X, H, count, kind):
         o = util.oracle_for(w)
         want = o.run(rec, propagate=True)
         compare_state(H, w, base, sizes, o, call(entry, X.CG_CHECK | X.CG_PROPAGATE), want)
+
+
+@pytest.mark.parametrize("n0,nd,ni", [(0, 0, 1), (0, 0, 21), (1, 1, 1), (63, 0, 16), (255, 2, 31), (255, 0, 32), (256, 3, 31),
+                                      (257, 1, 32), (5000, 96, 0), (5000, 97, 0), (5000, 1, 133), (5000, 1000, 3),
+                                      (9000, 3, 31), (9000, 40, 20), (140_001, 3, 31), (140_001, 5000, 4000)])
+def test_tables_made_by_merge(X, n0, nd, ni):
+    """A table version made by merging nd frees and ni allocations, nd + 3 ni
+    words, into the one before (up to 96 words travel in the launch's
+    arguments, up to 4,096 through a small upload, more through a large one):
+    made by a merge, and every level right.  The entries and the top level are
+    read; the middle level (above 8,192 entries) and the fine level (above
+    131,072) answer 300,000 pointers."""
+    rng = np.random.default_rng(n0 + 7 * nd + ni)
+    step = 4096
+    old = W.DEV_BASE + step * 3 * np.arange(1, n0 + 1, dtype=np.int64)
+    ctx = X.cg_create(0, (n0 + ni + 16) * 512, n0 + ni + 16)
+    try:
+        if n0:
+            X.shadow_alloc_batch(ctx, old, np.full(n0, 300))
+        before = X.cg_table_read(ctx, n0 + 16)
+        kill = rng.choice(old, nd, replace=False)
+        if nd:
+            X.shadow_free_batch(ctx, kill)
+        # before, between, after and in place of the old entries
+        free = np.concatenate([kill, W.DEV_BASE + step * np.setdiff1d(np.arange(3 * n0 + 3 * ni + 9), 3 * np.arange(1, n0 + 1))])
+        new = np.unique(np.concatenate([kill[:ni // 2], rng.choice(np.setdiff1d(free, kill), ni - len(kill[:ni // 2]), replace=False)]))
+        size = rng.integers(1, 500, len(new))
+        if ni:
+            X.shadow_alloc_batch(ctx, new, size)
+        t = X.cg_table_read(ctx, n0 + ni + 16)
+        assert len(new) == ni and len(kill) == nd
+        assert t["merges"] == before["merges"] + 1 and t["full_uploads"] == before["full_uploads"]
+        live = {int(b): 300 for b in old}
+        for b in kill:
+            live.pop(int(b))
+        live.update({int(b): int(k) for b, k in zip(new, size)})
+        base = np.array(sorted(live), np.uint64)
+        end = base + np.array([live[int(b)] for b in base], np.uint64)
+        assert np.array_equal(t["base"], base) and np.array_equal(t["end"], end)
+        assert np.array_equal(t["top"], base[:: 1 << t["shift"]])
+        some = np.arange(len(base)) if len(base) < 300 else rng.choice(len(base), 300, replace=False)
+        for j in some:
+            assert X.shadow_ptr(ctx, int(base[j])) == t["pool"] + int(t["off"][j])
+        p = rng.choice(np.concatenate([base - 1, base, end - 1, end, end + 1, kill.astype(np.uint64)]), 300_000).astype(np.uint64)
+        pt = torch.from_numpy(p.view(np.int64)).cuda()
+        out = torch.zeros((len(p), 3), dtype=torch.int64, device="cuda")
+        X.check_pointers(ctx, pt.data_ptr(), len(p), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy().view(W.PTR_DTYPE).reshape(-1)
+        j = np.searchsorted(base, p, side="right") - 1
+        k = np.maximum(j, 0)
+        ok = (j >= 0) & (p <= end[k])
+        assert np.array_equal(got["flags"], np.where(ok, 0, X.CG_PTR_UNALLOC))
+        assert np.array_equal(got["base"], np.where(ok, base[k], 0)) and np.array_equal(got["avail"], np.where(ok, end[k] - p, 0))
+    finally:
+        X.cg_destroy(ctx)
