@@ -379,3 +379,41 @@ def test_tables_made_by_merge(X, n0, nd, ni):
         assert np.array_equal(got["base"], np.where(ok, base[k], 0)) and np.array_equal(got["avail"], np.where(ok, end[k] - p, 0))
     finally:
         X.cg_destroy(ctx)
+
+
+@pytest.mark.parametrize("host_lds", ["1", "0", "2"])
+@pytest.mark.parametrize("cap", ["30", "3000"])
+@pytest.mark.parametrize("large", [4, 40])
+def test_segments_beside_the_indexes(X, H, large, cap, host_lds, monkeypatch):
+    """A check of a few large records among many small ones, with the indexes
+    on and full (so that nothing or one space is answered from them): with
+    40 large ones the batch reads each of its granules more than 4 times and
+    is cut into segments, the large records into many; with 4 it reads them
+    fewer times and keeps its order.  (A batch that propagates always keeps its
+    order.)"""
+    from tests import util
+    for k, v in (("XC_REORDER_MIN", "1"), ("XC_SEG_MIN_LOG2", "4"), ("XC_SHADOW_INDEX", "2"), ("XC_SIDX_CAP", cap),
+                 ("XC_HOST_LDS", host_lds)):
+        monkeypatch.setenv(k, v)
+    rng = np.random.default_rng(large)
+    hl, sizes = 1_500_001, np.array([1_400_003, 1_300_007])
+    w, base = edge_world(rng, hl, sizes, dens=0.001)
+    T = 500
+    n = rng.integers(1, 3000, T)
+    n[rng.choice(T, large, replace=False)] = rng.integers(600_000, 1_200_000, large)
+    kind = rng.choice([0, 2], T)
+    src = np.where(kind == 0, W.HOST_BASE + rng.integers(0, hl - n + 1), base[0] + rng.integers(0, 1_400_003 - n + 1))
+    rec = W.make_records(kind, src.astype(np.uint64), np.full(T, base[1], np.uint64), n.astype(np.uint64))
+    # the rule's two sides: bytes read, and bytes of the granules they lie in
+    off = np.where(kind == 0, src - W.HOST_BASE, src - base[0])
+    grans = sum(len(np.unique(np.concatenate([np.arange(o >> 12, ((o + k - 1) >> 12) + 1) for o, k in zip(off[m], n[m])])))
+                for m in (kind == 0, kind == 2))
+    reads = int(n.sum()) / (4096 * grans)
+    assert (reads > 4.5) if large == 40 else (reads < 3.5), reads
+    want = util.oracle_for(w).run(rec)
+    dw = H.DeviceWorld(w)
+    try:
+        for mode in (X.CG_CHECK, X.CG_CHECK | X.CG_EAGER, X.CG_CHECK):
+            util.assert_verdicts_equal(dw.check(rec, mode), want, f"mode {mode}")
+    finally:
+        dw.close()
