@@ -194,8 +194,10 @@ int shadow_ptr(cg_ctx *ctx, uint64_t dev_addr, uint8_t **v_dev);
  *   region, the shadow pool) that its records read, once, into an index of
  *   their faulty 16-byte chunks, where that costs less than the scan it saves,
  *   and answers its records from it, with the same verdicts (the first such
- *   call on a stream allocates the index space: about 280 MB plus 90 bytes per
- *   64 KiB of the pool).  A host region above 64 GiB is not indexed.
+ *   call on a stream allocates that stream's index space: about 311 MB plus 89
+ *   bytes per 64 KiB of the pool; where there is no room for it, the stream's
+ *   batches are scanned).  A host region above 64 GiB that is registered after
+ *   that call is not indexed.
  * With CG_PROPAGATE every valid destination byte receives the source's V
  * byte, or 0xFF where the source byte is not valid; overlapping D2D records
  * are not propagated.  All records read the shadow as it was before the

@@ -114,6 +114,7 @@ struct Workspace {
     // shadow indexes of check-only segmented batches, host region and pool
     // (shadowindex.hip; allocated on first use)
     ShadowIndex hidx{}, pidx{};
+    bool sidx_refused = false;   // there was no room for them
 };
 
 struct TimingPair {
@@ -479,6 +480,18 @@ void add_fill(std::vector<FillRange> &rs, uint64_t ptr, uint64_t len, uint8_t v)
     }
 }
 
+void free_sidx(Workspace *w)
+{
+    for (ShadowIndex *x : {&w->hidx, &w->pidx}) {
+        void *hs[] = {x->uchunk, x->umask, x->ucum, x->nchunk, x->nmask, x->bcnt, x->sflag, x->state,
+                      x->smark, x->fmark, x->slist, x->mcnt};
+        for (void *p : hs)
+            if (p) (void)hipFree(p);
+        *x = ShadowIndex{};
+    }
+    w->sidx_refused = false;
+}
+
 void free_seg(Workspace *w)
 {
     void *ps[] = {w->rdesc, w->rweight, w->rlocal, w->rbsum, w->sfirst, w->sbsum, w->meta, w->srec, w->perm};
@@ -489,13 +502,7 @@ void free_seg(Workspace *w)
     w->rweight = w->rlocal = w->rbsum = w->sfirst = w->sbsum = w->meta = nullptr;
     w->srec = w->perm = nullptr;
     w->seg_cap = 0;
-    for (ShadowIndex *x : {&w->hidx, &w->pidx}) {
-        void *hs[] = {x->uchunk, x->umask, x->ucum, x->nchunk, x->nmask, x->bcnt, x->sflag, x->state,
-                      x->smark, x->fmark, x->slist, x->mcnt};
-        for (void *p : hs)
-            if (p) (void)hipFree(p);
-        *x = ShadowIndex{};
-    }
+    free_sidx(w);
 }
 
 void free_ws(Workspace *w)
@@ -840,44 +847,56 @@ int reserve_segments(cg_ctx *c, Workspace *w, uint64_t count, hipStream_t s)
 // The shadow indexes' buffers: lists of sidx_cap entries (the pool's
 // unaddressable list stays empty: one entry), block counts for a grid of 8
 // blocks per CU.
-int reserve_sidx(cg_ctx *c, Workspace *w)
+hipError_t alloc_sidx(cg_ctx *c, Workspace *w)
 {
-    if (w->pidx.state) return CG_OK;
-    if (!c->idx_read) {
-        HIPTRY(c, hipMalloc(&c->idx_read, 2 * 8));
-        HIPTRY(c, hipMemset(c->idx_read, 0, 2 * 8));
-    }
+    hipError_t e = hipSuccess;
+    auto get = [&](auto **p, uint64_t bytes, bool clear = false) {
+        if (e == hipSuccess) e = hipMalloc(p, bytes);
+        if (e == hipSuccess && clear) e = hipMemset(*p, 0, bytes);
+    };
+    if (!c->idx_read) get(&c->idx_read, 2 * 8, true);
     for (uint32_t space : {0u, 1u}) {
         ShadowIndex &x = space ? w->pidx : w->hidx;
         x.space = space;
         x.cap_u = c->sidx_cap;
         x.cap_n = space ? 1 : c->sidx_cap;
         x.grid = (uint32_t)std::max(c->cu_count, 1) * c->sidx_blocks_per_cu;
-        HIPTRY(c, hipMalloc(&x.uchunk, (x.cap_u + 1) * 8));
-        HIPTRY(c, hipMalloc(&x.umask, x.cap_u * 4));
-        HIPTRY(c, hipMalloc(&x.ucum, (x.cap_u + 1) * 8));
-        HIPTRY(c, hipMalloc(&x.nchunk, x.cap_n * 8));
-        HIPTRY(c, hipMalloc(&x.nmask, x.cap_n * 4));
-        HIPTRY(c, hipMalloc(&x.bcnt, 6ull * x.grid * 8));
-        // per step of 64 KiB of the pool, or of a host region of up to 64 GiB (a
-        // larger one is not indexed): 17 mark bytes, 16 list
-        // entries, and flags
+        get(&x.uchunk, (x.cap_u + 1) * 8);
+        get(&x.umask, x.cap_u * 4);
+        get(&x.ucum, (x.cap_u + 1) * 8);
+        get(&x.nchunk, x.cap_n * 8);
+        get(&x.nmask, x.cap_n * 4);
+        get(&x.bcnt, 6ull * x.grid * 8);
+        // 89 bytes per step of 64 KiB of the pool, or of a host region of up to 64
+        // GiB (one registered later that is larger is not indexed): 17 mark
+        // bytes, 16 list entries, and flags
         const uint64_t len = space ? c->palloc->capacity() : std::max<uint64_t>(c->region.hl, 64ull << 30);
         x.steps_cap = (len >> kIdxStepShift) + 1;
         x.mark_grid = (uint32_t)((x.steps_cap + 4095) / 4096);
-        HIPTRY(c, hipMalloc(&x.sflag, 8 * (x.steps_cap + 1)));
-        HIPTRY(c, hipMalloc(&x.slist, 64 * x.steps_cap));
+        get(&x.sflag, 8 * (x.steps_cap + 1));
+        get(&x.slist, 64 * x.steps_cap);
         // (the marking kernels clear the marks they read)
-        HIPTRY(c, hipMalloc(&x.smark, 4096ull * x.mark_grid));
-        HIPTRY(c, hipMemset(x.smark, 0, 4096ull * x.mark_grid));
-        HIPTRY(c, hipMalloc(&x.fmark, 65536ull * x.mark_grid));
-        HIPTRY(c, hipMemset(x.fmark, 0, 65536ull * x.mark_grid));
-        HIPTRY(c, hipMalloc(&x.mcnt, 8ull * x.mark_grid));
-        HIPTRY(c, hipMalloc(&x.state, kIdxState * 8));
-        HIPTRY(c, hipMemset(x.state, 0, kIdxState * 8));
+        get(&x.smark, 4096ull * x.mark_grid, true);
+        get(&x.fmark, 65536ull * x.mark_grid, true);
+        get(&x.mcnt, 8ull * x.mark_grid);
+        get(&x.state, kIdxState * 8, true);
         x.read = c->idx_read + space;
     }
-    HIPTRY(c, hipStreamSynchronize(nullptr));   // the cleared buffers, before any stream uses them
+    return e != hipSuccess ? e : hipStreamSynchronize(nullptr);   // the cleared buffers, before any stream uses them
+}
+
+// Reserves them on first use (w->pidx.state is then set).  Where there is no
+// room for them the stream's checks are scanned: its verdicts do not depend on
+// the indexes.
+int reserve_sidx(cg_ctx *c, Workspace *w)
+{
+    if (w->pidx.state || w->sidx_refused) return CG_OK;
+    const hipError_t e = alloc_sidx(c, w);
+    if (e == hipSuccess) return CG_OK;
+    free_sidx(w);
+    if (e != hipErrorOutOfMemory) return hip_fail(c, "shadow index space", e);
+    (void)hipGetLastError();   // (or the next launch would report it)
+    w->sidx_refused = true;
     return CG_OK;
 }
 
@@ -978,10 +997,13 @@ int run_check(cg_ctx *c, const cg_transfer *recs, uint64_t count, cg_verdict *ou
     }
     // a check without propagation, of more records than one launch takes and
     // not kept in its order: the shadow indexes answer what they can
-    if (c->shadow_index && (mode & (CG_CHECK | CG_PROPAGATE | CG_PLAIN | CG_KEEP_ORDER)) == CG_CHECK &&
-        count > c->small_max) {
+    const bool indexed = c->shadow_index && count > c->small_max &&
+                         (mode & (CG_CHECK | CG_PROPAGATE | CG_PLAIN | CG_KEEP_ORDER)) == CG_CHECK;
+    if (indexed) {
         rc = reserve_sidx(c, w);
         if (rc) return rc;
+    }
+    if (indexed && w->pidx.state) {
         w->hidx.always = w->pidx.always = c->shadow_index == 2 ? 1u : 0u;
         if (!seg) {
             plan.seg = false;
@@ -1537,12 +1559,15 @@ int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, c
     const LaunchShape sh = shape_of(c, tun);
     // a check without propagation: records worked as one transfer each (rows
     // back to back) are answered by the shadow indexes when they pay
-    const bool idx = c->shadow_index && mode == CG_CHECK;
+    bool idx = c->shadow_index && mode == CG_CHECK;
     if (idx) {
-        if (capturing && !w->pidx.state)
+        if (capturing && !w->pidx.state && !w->sidx_refused)
             return fail(c, CG_ESTATE, "check_transfers_2d under capture: make one call on this stream first");
         rc = reserve_sidx(c, w);
         if (rc) return rc;
+        idx = w->pidx.state != nullptr;
+    }
+    if (idx) {
         w->hidx.always = w->pidx.always = c->shadow_index == 2 ? 1u : 0u;
         set_index_args(a, w);
     }

@@ -417,3 +417,27 @@ def test_segments_beside_the_indexes(X, H, large, cap, host_lds, monkeypatch):
             util.assert_verdicts_equal(dw.check(rec, mode), want, f"mode {mode}")
     finally:
         dw.close()
+
+
+def test_no_room_for_the_indexes(X, H, monkeypatch):
+    """Checks on a stream for whose index space there is no room (lists of 2^36
+    entries): scanned, with the same verdicts, again and in other shapes, and
+    pitched ones as well."""
+    from tests import util
+    from tests.test_gpu_2d import check2d
+    monkeypatch.setenv("XC_SIDX_CAP", str(1 << 36))
+    rng = np.random.default_rng(77)
+    w, base = edge_world(rng, 300_000, np.array([300_000]))
+    rec = uploads(rng, 700, 300_000, base[0], rng.integers(1, 9000, 700))
+    want = util.oracle_for(w).run(rec)
+    r2 = np.zeros(300, W.RECORD2D_DTYPE)
+    r2["width"], r2["rows"], r2["spitch"], r2["dpitch"] = 100, 20, 100, 128
+    r2["src"], r2["dst"] = W.HOST_BASE + rng.integers(0, 290_000, 300), base[0]
+    dw = H.DeviceWorld(w)
+    try:
+        for mode in (X.CG_CHECK, X.CG_CHECK | X.CG_EAGER, X.CG_CHECK, X.CG_CHECK | X.CG_KEEP_ORDER):
+            util.assert_verdicts_equal(dw.check(rec, mode), want, f"mode {mode}")
+        util.assert_verdicts_equal(check2d(X, dw, r2, X.CG_CHECK), util.oracle_for(w).run2d(r2), "pitched")
+        assert X.cg_index_ms(dw.ctx)[2] == (0, 0)
+    finally:
+        dw.close()
