@@ -254,6 +254,30 @@ int hip_fail(cg_ctx *c, const char *what, hipError_t e)
         if (e_ != hipSuccess) return hip_fail(ctx, #call, e_); \
     } while (0)
 
+// While one of these lives, this thread may ask about events and wait for them
+// without ending a capture: a program may capture a stream in global mode, in
+// any of its threads, while it checks on another.
+struct BesideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~BesideCaptures()
+    {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+bool happened(hipEvent_t ev)
+{
+    BesideCaptures quiet;
+    return hipEventQuery(ev) == hipSuccess;
+}
+
+void wait_for(hipEvent_t ev)
+{
+    BesideCaptures quiet;
+    (void)hipEventSynchronize(ev);
+}
+
 // ctx stream waits for check u, unless that is known to be done
 int wait_use(cg_ctx *c, const Use &u)
 {
@@ -281,8 +305,7 @@ int ctx_end(cg_ctx *c)
 
 // Stream s waits for the context's latest state (a table version, fills),
 // unless that is known to have happened; whatever stream the handle names, it
-// then has nothing to wait for.  (A stream under capture always gets the wait,
-// which refuses the capture.)
+// then has nothing to wait for.  (A stream under capture always gets the wait.)
 int wait_ctx(cg_ctx *c, hipStream_t s)
 {
     if (!c->ctx_recorded) {
@@ -291,7 +314,7 @@ int wait_ctx(cg_ctx *c, hipStream_t s)
     }
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-        if (!c->ctx_done) c->ctx_done = hipEventQuery(c->ev_ctx) == hipSuccess;
+        if (!c->ctx_done) c->ctx_done = happened(c->ev_ctx);
         if (c->ctx_done) return CG_OK;
     }
     HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
@@ -415,8 +438,8 @@ void retire(cg_ctx *c, bool wait_all)
 {
     while (!c->inflight.empty()) {
         InFlight &f = c->inflight.front();
-        if (wait_all) (void)hipEventSynchronize(f.ev);
-        else if (hipEventQuery(f.ev) != hipSuccess) break;
+        if (wait_all) wait_for(f.ev);
+        else if (!happened(f.ev)) break;
         c->done_seq = f.seq;
         c->ev_pool.push_back(f.ev);
         c->inflight.pop_front();

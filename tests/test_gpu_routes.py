@@ -441,3 +441,51 @@ def test_no_room_for_the_indexes(X, H, monkeypatch):
         assert X.cg_index_ms(dw.ctx)[2] == (0, 0)
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+@pytest.mark.parametrize("entry", ["check_transfers", "check_transfers_noalloc", "check_pointers"])
+def test_checks_beside_a_capture(X, H, entry, mode):
+    """A program captures work of its own on one stream and checks on another
+    meanwhile, the shadow having been written just before: the check sees the
+    write, more checks than the context keeps events for go through, and the
+    capture stands and replays."""
+    from tests import util
+    rng = np.random.default_rng(9)
+    w, base = edge_world(rng, 100_000, np.array([100_000]))
+    rec = W.make_records(np.full(64, 2), (base[0] + 7 * np.arange(64)).astype(np.uint64),
+                         np.full(64, base[0] + 50_000, np.uint64), np.full(64, 300, np.uint64))
+    o = util.oracle_for(w)
+    o.vs[0][:40] = 0xFF
+    want = o.run(rec)
+    dw = H.DeviceWorld(w)
+    try:
+        side, other = torch.cuda.Stream(), torch.cuda.Stream()
+        rt, out = H.records_tensor(rec), H.verdicts_tensor(64)
+        pt = torch.zeros((64, 3), dtype=torch.int64, device="cuda")
+        x = torch.zeros(1000, device="cuda")
+
+        def check():
+            if entry == "check_pointers":
+                X.check_pointers(dw.ctx, rt.data_ptr(), 64, pt.data_ptr(), other.cuda_stream)
+            else:
+                getattr(X, entry)(dw.ctx, rt.data_ptr(), 64, out.data_ptr(), X.CG_CHECK, other.cuda_stream)
+        check()
+        torch.cuda.synchronize()
+        X.shadow_set(dw.ctx, int(base[0]), 40, 0xFF)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side, capture_error_mode=mode):
+            x += 1
+            for _ in range(300):
+                check()
+            x += 1
+        torch.cuda.synchronize()
+        if entry != "check_pointers":
+            util.assert_verdicts_equal(H.verdicts_np(out, 64), want)
+        for k in range(3):
+            g.replay()
+            check()
+            torch.cuda.synchronize()
+            assert bool((x == 2 * (k + 1)).all())
+    finally:
+        dw.close()
