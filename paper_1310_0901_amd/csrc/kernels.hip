@@ -1452,7 +1452,10 @@ __device__ __forceinline__ uint64_t search4(const uint64_t *a, uint64_t w, uint6
 
 // Few pointers (`few`) stage the top level of 1,024 entries instead: a few
 // thousand lookups do not repay 64 KiB (335 pointers against 11,734
-// allocations: 13.2 us with the middle level, 12.1 with the top level).
+// allocations: 13.2 us with the middle level, 12.1 with the top level).  Where
+// the line lies matters little: 262,143 pointers (top level) and 262,144
+// (middle level) took 10.8 and 10.6 us against 1,000 allocations, 12.9 and 12.3
+// against 10,000, 15.7 and 16.1 against 100,000, 25.1 and 24.2 against 975,000.
 __global__ void __launch_bounds__(1024) k_pointers(const DevState *stp, const uint64_t *ptrs, uint64_t count,
                                                    cg_ptr_check *out, bool few)
 {
@@ -2280,9 +2283,9 @@ __global__ void __launch_bounds__(512) k_plain(BatchArgs a, uint64_t t, uint64_t
 // kSmallUnits units), so that every block of the record agrees on them and
 // the unused ones leave after one load.  Block b of record t: waves 0 and 1
 // look up the record's source and destination pointers side by side, one
-// lane classifies it; the record's units are
-// split evenly over its blocks, and a block's share over its waves (the
-// wave-uniform loop).  A record of one block gets its whole verdict from that
+// lane classifies it; the record's iterations
+// are dealt out to its blocks' waves in turn (the wave-uniform loop).  A record
+// of one block gets its whole verdict from that
 // block.  Otherwise a block that finds something merges it into the record's
 // accumulator with atomics; the last of the record's blocks to finish (the
 // accumulator's counter) writes the whole verdict -- the range-derived fields

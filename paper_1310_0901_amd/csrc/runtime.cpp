@@ -833,8 +833,12 @@ int note_use(cg_ctx *c, hipStream_t s, Workspace *w = nullptr);
 // Checks without propagation of at least reorder_min records and at most
 // kSegMaxRecords are worked as source-block segments unless the caller keeps
 // the given order.  (A batch that propagates writes as many bytes as it reads,
-// so re-reads saved are worth little: 65,536 pieces of 16 B to 64 KiB took
-// 880 us as segments, 460 us in their order.)
+// so re-reads saved are worth little, few or many, of small records or large:
+// 65,536 pieces of 16 B to 64 KiB took 880 us as segments, 460 us in their order;
+// with cached loads on both sides, 20,000 records of 64 KiB read from 1 MiB 812
+// and 283 us, 2,000 of 1 MiB from 8 MiB 723 and 457, 20,000 of 256 KiB from 8 MiB
+// 1,866 and 1,073, from 1 GiB 2,417 and 2,113; the segments on the scan before
+// this one.)
 bool segmented(const cg_ctx *c, uint64_t count, uint32_t mode)
 {
     return !(mode & (CG_PLAIN | CG_KEEP_ORDER | CG_PROPAGATE)) && count >= 1 && count >= c->reorder_min && count <= kSegMaxRecords;
@@ -941,11 +945,12 @@ void set_index_args(BatchArgs &a, const Workspace *w)
 // iteration of its waves (64 such records: 29.8 us per call with 256 threads,
 // 26.1 with 1,024; 2 GiB carried in one record: 966 and 822 us), and no record
 // waits for a second round of blocks, each of which costs the lookups' chain
-// again.  Records of 64 bytes with 256, 512 and 1,024 threads: 512 of them 14.0,
-// 14.1 and 13.7 us, 1,024 14.1, 14.3 and 21.9, 2,048 14.1, 23.8 and 38.0, 4,096
-// 22.3, 42.7 and 70.0; of 64 KiB, checked: 512 of them 32.3, 25.6 and 21.7 us,
-// 1,024 33.3, 26.5 and 38.0, 4,096 66.6, 92.2 and 137.9.  And loads as a
-// check's, since few records share their sources.
+// again.  Records of 64 bytes checked with 256, 512 and 1,024 threads: 512 of
+// them 13.2, 13.4 and 13.1 us, 700 12.9, 13.0 and 16.1, 1,024 13.4, 13.6 and
+// 19.7, 2,048 13.4, 21.8 and 33.4, 4,096 20.7, 38.3 and 61.1; of 64 KiB: 512 of
+// them 26.8, 21.0 and 17.7 us, 700 23.4, 20.5 and 23.3, 1,024 27.9, 22.1 and 29.8,
+// 2,048 31.2, 39.3 and 54.4, 4,096 55.1, 73.6 and 103.9.  And loads as a check's,
+// since few records share their sources.
 LaunchShape small_shape(const cg_ctx *c, uint64_t count, LaunchShape sh)
 {
     const uint64_t cus = (uint64_t)c->cu_count;
@@ -1296,7 +1301,9 @@ int cg_create(cg_ctx **out, int hip_device, uint64_t shadow_pool_bytes, uint64_t
     // propagating: four windows per lane leave room for half the waves only,
     // and a batch's records often share their sources (65,536 pieces read from
     // 32 MiB of host region and 256 MiB of device shadow: 337 us with
-    // non-temporal loads, 243 us with cached ones)
+    // non-temporal loads, 243 us with cached ones; 20,000 records of 256 KiB from
+    // 8 MiB 1,898 and 1,071, from 1 GiB, where few bytes are read again, 2,235
+    // and 2,114; 20,000 of 60 to 400 KB from 256 MiB 1,653 and 1,342)
     c->tuning_prop = c->tuning;
     c->tuning_prop.unroll = 2;
     c->tuning_prop.nontemporal = 0;
@@ -1541,10 +1548,10 @@ int propagate_shadow(cg_ctx *c, const cg_transfer *recs_dev, uint64_t count, voi
 // check_transfers_2d without a wait: every 2D record is one position whose
 // units step through its rows (k_classify_2d, then the scan kernel over
 // pitched positions); no row count is needed on the host.  Under a caller's
-// stream capture only the four kernels are enqueued: the stream must already
-// wait for every table upload (an eager call on it since the last change),
-// and the bookkeeping events are left out (a replay reads the table of the
-// capture's time).
+// stream capture only the kernels are enqueued (three, eleven with the
+// indexes, two more above 262,144 records): the stream must already wait for every table upload (an
+// eager call on it since the last change), and the bookkeeping events are left
+// out (a replay reads the table of the capture's time).
 int check_2d_pitched(cg_ctx *c, const cg_transfer2d *recs_dev, uint64_t count, cg_verdict *out_dev, uint32_t mode,
                      hipStream_t s)
 {

@@ -269,9 +269,9 @@ __global__ void __launch_bounds__(kMarkT) k_sidx_mark_list(ShadowIndex h, Shadow
 // once), then examined; each wave notes in which of the 16 it met a faulty
 // chunk, so that the fill reads only those.  The granules of the slice are
 // read from the list 64 at a time, one per lane.  A block that met list entries
-// adds them to the index's running count and stops when the lists are full, so
-// that a space dense with faults costs a few per cent of its bytes before the
-// scan takes over.  Bound by HBM: 48.8 GB at 6.8-7.0 TB/s, where a plain read
+// adds them to the index's running count and stops when the entries of both
+// kinds together pass the room of both lists, so that a space dense with faults
+// costs a few per cent of its bytes before the scan takes over.  Bound by HBM: 48.8 GB at 6.8-7.0 TB/s, where a plain read
 // of the same shape reaches 0.87-0.89 of 8 TB/s.
 __device__ __forceinline__ void count_slice(const ShadowIndex &x, const Space &S)
 {
