@@ -266,17 +266,6 @@ struct BesideCaptures {
     }
 };
 
-bool happened(hipEvent_t ev)
-{
-    BesideCaptures quiet;
-    return hipEventQuery(ev) == hipSuccess;
-}
-
-void wait_for(hipEvent_t ev)
-{
-    BesideCaptures quiet;
-    (void)hipEventSynchronize(ev);
-}
 
 // ctx stream waits for check u, unless that is known to be done
 int wait_use(cg_ctx *c, const Use &u)
@@ -314,7 +303,10 @@ int wait_ctx(cg_ctx *c, hipStream_t s)
     }
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-        if (!c->ctx_done) c->ctx_done = happened(c->ev_ctx);
+        if (!c->ctx_done) {
+            BesideCaptures quiet;
+            c->ctx_done = hipEventQuery(c->ev_ctx) == hipSuccess;
+        }
         if (c->ctx_done) return CG_OK;
     }
     HIPTRY(c, hipStreamWaitEvent(s, c->ev_ctx, 0));
@@ -436,13 +428,16 @@ void add_fill(std::vector<FillRange> &rs, uint64_t ptr, uint64_t len, uint8_t v)
 // readers are all done go back to the allocator.
 void retire(cg_ctx *c, bool wait_all)
 {
-    while (!c->inflight.empty()) {
-        InFlight &f = c->inflight.front();
-        if (wait_all) wait_for(f.ev);
-        else if (!happened(f.ev)) break;
-        c->done_seq = f.seq;
-        c->ev_pool.push_back(f.ev);
-        c->inflight.pop_front();
+    {
+        BesideCaptures quiet;
+        while (!c->inflight.empty()) {
+            InFlight &f = c->inflight.front();
+            if (wait_all) (void)hipEventSynchronize(f.ev);
+            else if (hipEventQuery(f.ev) != hipSuccess) break;
+            c->done_seq = f.seq;
+            c->ev_pool.push_back(f.ev);
+            c->inflight.pop_front();
+        }
     }
     if (c->inflight.empty()) c->done_seq = c->check_seq;
     // released blocks are cleared to 0, so that a stale shadow left in the
