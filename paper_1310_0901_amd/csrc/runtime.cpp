@@ -428,7 +428,7 @@ void add_fill(std::vector<FillRange> &rs, uint64_t ptr, uint64_t len, uint8_t v)
 // readers are all done go back to the allocator.
 void retire(cg_ctx *c, bool wait_all)
 {
-    {
+    if (!c->inflight.empty()) {   // (an allocation asks too, mostly with nothing in flight)
         BesideCaptures quiet;
         while (!c->inflight.empty()) {
             InFlight &f = c->inflight.front();
