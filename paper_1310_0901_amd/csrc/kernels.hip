@@ -725,7 +725,8 @@ __device__ __forceinline__ void check_interior(uint64_t vbase, uint64_t abase, b
     }
 }
 
-// run_uniform for the checks of check_transfers.  A batch whose records read
+// run_uniform for the checks of check_transfers; G windows a lane at a
+// record's edges.  A batch whose records read
 // the same bytes again and again takes them from the caches at 20 TB/s, where
 // the waves' instructions count: the interior iterations follow each other, so
 // their range is found once per call, and an iteration is its loads, one test
@@ -735,7 +736,7 @@ __device__ __forceinline__ void check_interior(uint64_t vbase, uint64_t abase, b
 // that code, 55.5 so; with the host's segments in LDS 64.2 and 52.7, and in 1 MiB
 // tiles with non-temporal loads 69.5 and 64.3.  4,096 records of 64 KiB in one
 // launch 67 and 55 us.
-template <int U, bool NT>
+template <int U, bool NT, int G = (U > 4 ? 4 : U)>
 __device__ __forceinline__ void run_check(const DV &d, const Region &R, uint64_t k_begin, uint64_t k_end, Acc &acc,
                                           uint64_t step = 64u * U)
 {
@@ -743,7 +744,6 @@ __device__ __forceinline__ void run_check(const DV &d, const Region &R, uint64_t
     const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
     const uint64_t a16b = (uint64_t)R.a16;
     constexpr uint64_t N = 64u * U;   // units per iteration
-    constexpr int G = U > 4 ? 4 : U;
     k_begin = ufl64(k_begin);
     k_end = ufl64(k_end);
     step = ufl64(step);
@@ -1811,8 +1811,11 @@ __device__ __forceinline__ void run_pitched(const BatchArgs &a, const Region &R,
         return;
     }
     if constexpr (!PROP) {
-        if (P.uniform == kRowsContig) {   // one transfer
-            run_check<U, NT>(d0, R, k0, k1, acc);
+        // one transfer; its edges two windows at a time, for the registers (386
+        // copies of rows of 8,209 bytes 246.3 us with four, 244.8 with two; 1,500 of
+        // 4,030 bytes without an index 692 and 686)
+        if (P.uniform == kRowsContig) {
+            run_check<U, NT, (U > 2 ? 2 : U)>(d0, R, k0, k1, acc);
             return;
         }
     }
