@@ -1265,6 +1265,22 @@ __device__ __forceinline__ void mark_rows(const BatchArgs &a, const DevState &st
     if ((ds.ctl & CTL_DST_A) && ds.d_hi > ds.d_lo) side(0, dst_space_off(ds), P.dpitch);
 }
 
+// Whether the windows of a pitched record's rows that follow row 0 are aligned
+// chunks of their sources, each row at its own phase: in a check without
+// propagation, where nothing is written at the windows' places.  A host
+// source's A bits are then half words as well and no window is shifted.  Rows
+// of up to 16 bytes whose pitch does not keep row 0's phase stay one window
+// from their start each instead of two chunks.  Without an index, windows from
+// the rows' starts and aligned chunks: 4,096 copies of 1,280 rows of 4,032 bytes
+// at 4,096, 6.84 and 3.62 ms; 20,480 rows of 240 at 256, 7.00 and 3.72; 1,000
+// copies of 1,237 rows of 4,000 at 4,041, 1.70 and 0.84, to the host 1.92 and
+// 1.36; 50,000 of 17 at 33, 616 and 306 us; 100,000 of 16 at 17, to the host, 656
+// and 791.
+__device__ __forceinline__ bool rows_aligned(uint32_t mode, const Pitch &P)
+{
+    return !(mode & CG_PROPAGATE) && ((P.spitch & 15u) == 0 || P.width > 16);
+}
+
 // One lane per pitched 2D record: row 0 looked up and classified (its
 // descriptor is the position's), whether every row follows from it, the
 // units (rows * upr) and the verdict before any row is worked: row 0's when
@@ -1304,7 +1320,7 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
             const int64_t js = dev_src(r0) ? table_lookup(st.table, top, r0.src) : -1;
             const int64_t jd = dev_dst(r0) ? table_lookup(st.table, top, r0.dst) : -1;
             cg_verdict v0;
-            classify_rec(r0, a.mode, st, js, jd, ds, v0, true);
+            classify_rec(r0, a.mode, st, js, jd, ds, v0, !rows_aligned(a.mode, P));
             const Region &R = st.region;
             auto side_ok = [&](bool host, int64_t j, uint64_t p, uint64_t q) {
                 if (host) return R.hl > 0 && p >= R.hb && rows_inside(p, q, P.width, rows, R.hb, R.hb + R.hl);
@@ -1319,9 +1335,11 @@ __global__ void __launch_bounds__(kClassifyBlock) k_classify_2d(BatchArgs a, con
                 const uint64_t b = row_extent_bound(P, rows, st);
                 ext = b < ext ? b : ext;
             }
-            // rows that follow row 0 all have its units; any other row at most
-            // (ext + 14) / 16 + 2, the most any alignment gives
-            P.upr = uniform ? ds.units : (ext + 14) / 16 + 2;
+            // rows that follow row 0 all have its units, or, in aligned chunks that
+            // each row's own phase gives, at most (width + 14) / 16 + 1; any other
+            // row at most (ext + 14) / 16 + 2, the most any alignment gives
+            P.upr = !uniform ? (ext + 14) / 16 + 2
+                    : rows_aligned(a.mode, P) && (P.spitch & 15u) ? (P.width + 14) / 16 + 1 : ds.units;
             P.uniform = uniform ? kRowsUniform : 0u;
             // rows back to back on every side the check reads: one transfer
             // (in the rows' allocations, so its lookups are row 0's)
@@ -1401,6 +1419,21 @@ __device__ __forceinline__ DV dv_uniform(const Desc &x)
     u.a_src = (int64_t)ufl64((uint64_t)x.a_src); u.a_dst = (int64_t)ufl64((uint64_t)x.a_dst);
     u.e0 = ufl64(x.e0); u.units = ufl64(x.units); u.ctl = ufl32(x.ctl);
     return make_dv(u);
+}
+
+// Row r's descriptor when the rows' windows are aligned chunks (rows_aligned),
+// each row's at the phase of its own source.
+__device__ __forceinline__ DV row_chunks(const DV &d0, const Pitch &P, uint64_t r)
+{
+    DV d = d0;
+    const uint64_t s = d0.src_sh + d0.o + r * P.spitch;
+    d.o = (uint32_t)s & 15u;
+    const int64_t ro = (int64_t)d0.o - (int64_t)d.o;
+    d.src_sh = s - d.o;
+    d.a_src += ro + (int64_t)(r * P.spitch);
+    d.a_dst += ro + (int64_t)(r * P.dpitch);
+    d.units = ((P.width - 1 + d.o) >> 4) + 1;
+    return d;
 }
 
 // findings of one row (row-relative byte indices) into a record's
@@ -1697,8 +1730,9 @@ __global__ void __launch_bounds__(256) k_plan_tiles(BatchArgs a, uint32_t tile_u
 // than kFlatUnits units each, by the whole wave: the rows' units follow each
 // other with no gap (upr is a row's units), and each lane works its own unit
 // of an iteration in whichever row it falls, so that short rows and row ends
-// share iterations.  d is row 0's descriptor (o = 0); row r's source and
-// destination lie r * spitch and r * dpitch further on, at any alignment.
+// share iterations.  d is row 0's descriptor (o = 0 here); row r's source and
+// destination lie r * spitch and r * dpitch further on, at any alignment (a
+// check takes this way for rows of up to 16 bytes at most: rows_aligned).
 // Every byte of a row is valid; only a row's last window may pass its end.
 // Offsets are taken from the iteration's first row, in 32 bits (24-bit
 // products run at full rate), so the pitches are below kFlatPitch; rows
@@ -1711,6 +1745,70 @@ constexpr uint64_t kFlatUnits = 4096, kFlatPitch = 1u << 20;
 __device__ __forceinline__ bool rows_flat(const Pitch &P)
 {
     return P.uniform == kRowsUniform && P.upr < kFlatUnits && (P.spitch | P.dpitch) < kFlatPitch;
+}
+
+// run_rows_flat for a check whose rows' windows are aligned chunks
+// (rows_aligned): nothing is shifted, and one test over all windows tells that
+// a wave has no finding.  A row whose phase gives one chunk fewer than upr
+// loads its last one twice and keeps it once.
+template <int U, bool NT>
+__device__ __forceinline__ void check_rows_flat(const DV &d, const Pitch &P, const Region &R, uint64_t k0, uint64_t k1,
+                                                Acc &acc)
+{
+    const uint32_t lane = lane_id();
+    const uint32_t ur = (uint32_t)P.upr;
+    const uint32_t inv = ufl32((uint32_t)(0xFFFFFFFFu / ur) + 1u);   // n * inv >> 32 = n / ur for n < 2^13 (ur > 1)
+    const uint32_t sp = (uint32_t)P.spitch, dp = (uint32_t)P.dpitch;
+    const int32_t width = (int32_t)P.width;
+    const bool src_host = (d.ctl & CTL_SRC_HOST) != 0;
+    const bool dsta = (d.ctl & CTL_DST_A) != 0;
+    k0 = ufl64(k0);
+    k1 = ufl64(k1);
+    uint64_t rb = ufl64(k0 / ur);
+    uint32_t jb = ufl32((uint32_t)(k0 - rb * ur));   // row and unit of the iteration's first unit
+    for (uint64_t kb = k0; kb < k1; kb += 64u * U) {
+        // row rb's first chunk, the row's start in it, and the chunk's A bits
+        const uint64_t s = d.src_sh + d.o + rb * sp, sb = s & ~15ull;
+        const uint32_t so = (uint32_t)s & 15u;
+        const uint64_t ab = (uint64_t)R.a16 + ((uint64_t)(d.a_src + (int64_t)(d.o + rb * sp) - (int64_t)so) >> 3);
+        const uint32_t left = k1 - kb < 64u * U ? (uint32_t)(k1 - kb) : 64u * U;
+        u32x4 v[U];
+        uint32_t a[U], x[U];
+        int32_t i[U];   // the window's first byte in its row
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            // (lanes past the end work the last unit again and keep nothing)
+            const uint32_t c = 64u * j + lane;
+            const uint32_t n = jb + (c < left ? c : left - 1);
+            x[j] = ur > 1 ? __umulhi(n, inv) : n;   // rows past rb
+            const uint32_t b = __umul24(x[j], sp) + so;
+            i[j] = 16 * (int32_t)(n - __umul24(x[j], ur)) - (int32_t)(b & 15u);
+            const uint32_t rel = b + (uint32_t)(i[j] < width ? i[j] : i[j] - 16);
+            v[j] = ld16<NT>(sb + rel);
+            a[j] = src_host ? ld_half(ab + (rel >> 3)) : 0xFFFFu;
+        }
+        if (dsta) {
+            // (from 16 bits before row rb: a window may start before its row)
+            const AWords A(R, d.a_dst + (int64_t)(d.o + rb * dp) - 16);
+#pragma unroll
+            for (int j = 0; j < U; ++j) a[j] = A.bits((int32_t)__umul24(x[j], dp) + i[j] + 16);
+        }
+        uint32_t bad = 0;
+#pragma unroll
+        for (int j = 0; j < U; ++j) bad |= v[j].x | v[j].y | v[j].z | v[j].w | (a[j] ^ 0xFFFFu);
+        if (__ballot(bad != 0u)) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const uint32_t m = 64u * j + lane < left ? rmask32(-i[j], width - i[j]) : 0u;
+                const int64_t i0 = (int64_t)((rb + x[j]) * P.width) + i[j];
+                if (dsta) dst_findings(acc, i0, m & ~a[j]);
+                src_findings(acc, i0, v[j], src_host ? m & a[j] : m, src_host ? m & ~a[j] : 0u);
+            }
+        }
+        const uint32_t n = jb + 64u * U, dx = ur > 1 ? __umulhi(n, inv) : n;
+        rb += ufl32(dx);
+        jb = ufl32(n - dx * ur);
+    }
 }
 
 template <int U, bool NT, bool PROP>
@@ -1805,19 +1903,32 @@ __device__ __forceinline__ void run_pitched(const BatchArgs &a, const Region &R,
 {
     const Pitch P = ld_uniform(a.pitch + t);
     const DV d0 = load_desc_uniform(a.desc, t);
+    if constexpr (!PROP) {
+        const bool contig = P.uniform == kRowsContig;
+        if (contig || (P.uniform && rows_aligned(a.mode, P))) {
+            if (!contig && rows_flat(P)) {
+                check_rows_flat<U, NT>(d0, P, R, k0, k1, acc);
+                return;
+            }
+            // one transfer, or one per row; the edges two windows at a time, for the
+            // registers (386 copies of rows of 8,209 bytes 246.3 us with four, 244.8
+            // with two; 1,500 of 4,030 bytes without an index 692 and 686)
+            const uint64_t ra = contig ? 0 : k0 / P.upr, rb = contig ? 0 : (k1 - 1) / P.upr;
+            for (uint64_t r = ra; r <= rb; ++r) {
+                const uint64_t b = r * P.upr, j0 = k0 > b ? k0 - b : 0, j1 = k1 - b < P.upr ? k1 - b : P.upr;
+                const DV d = contig ? d0 : row_chunks(d0, P, r);
+                Acc x;
+                acc_reset(x);
+                run_check<U, NT, (U > 2 ? 2 : U)>(d, R, j0, j1 < d.units ? j1 : d.units, x);
+                acc_add_row(acc, x, 0u, NONE, r * P.width);
+            }
+            return;
+        }
+    }
     if (rows_flat(P)) {
         // (two windows per lane at most: each has a row's worth of indices)
         run_rows_flat<(U > 2 ? 2 : U), NT, PROP>(d0, P, R, k0, k1, acc);
         return;
-    }
-    if constexpr (!PROP) {
-        // one transfer; its edges two windows at a time, for the registers (386
-        // copies of rows of 8,209 bytes 246.3 us with four, 244.8 with two; 1,500 of
-        // 4,030 bytes without an index 692 and 686)
-        if (P.uniform == kRowsContig) {
-            run_check<U, NT, (U > 2 ? 2 : U)>(d0, R, k0, k1, acc);
-            return;
-        }
     }
     const DevState *st = a.st;
     const uint64_t r0 = k0 / P.upr;
@@ -1864,6 +1975,16 @@ __device__ __forceinline__ void run_unit_pitched(const BatchArgs &a, const Regio
         return;
     }
     const uint64_t r = (k | P.upr) >> 32 ? k / P.upr : (uint32_t)k / (uint32_t)P.upr, j = k - r * P.upr;
+    if constexpr (!PROP) {
+        if (P.uniform && rows_aligned(a.mode, P)) {
+            const DV d = row_chunks(load_desc(a.desc, t), P, r);
+            Acc x;
+            acc_reset(x);
+            if (j < d.units) run_unit<NT, false, true>(d, R, j, x);
+            acc_add_row(acc, x, 0u, NONE, r * P.width);
+            return;
+        }
+    }
     uint32_t rflags = 0;
     uint64_t rfirst = NONE;
     Desc x;

@@ -101,8 +101,10 @@ constexpr uint64_t kSmallUnits = 8192;       // units per block of a record in a
 // units past a row's own are empty), and the position's Desc is row 0's.
 // When `uniform` is non-zero, every row lies in row 0's allocation or in the
 // host region on each side, fully valid, so row r's descriptor is row 0's
-// moved by the pitches, with o = 0 and exactly upr units; otherwise each row
-// is looked up and classified where it is worked.
+// moved by the pitches: with o = 0 and exactly upr units, or, when the rows'
+// windows are aligned chunks of their sources (rows_aligned in kernels.hip),
+// with o and the units of the row's own phase; otherwise each row is looked
+// up and classified where it is worked.
 struct Pitch {
     uint64_t src, dst, width, rows, spitch, dpitch, upr;
     uint32_t kind, uniform;
